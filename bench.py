@@ -66,10 +66,10 @@ KERNEL_SYMBOL = {
     "tri_global": "k_tri_global", "tri_1024": "k_tri_lds<1024, 256>",
     "tri_512": "k_tri_lds<512, 256>", "tri_256": "k_tri_lds<256, 256>",
     "tri_128": "k_tri_lds<128, 256>", "tri_wave": "k_tri_lds<64, 64>",
-    "c4_window": "k_c4_window", "c4_med": "k_c4_hash<1024, 16384, 4>",
-    "c4_hash": "k_c4_hash<256, 4096, 4>", "closure": "k_closure", "c4_plan": "k_c4_plan",
+    "c4_window": "k_c4_window", "c4_med": "k_c4_filter<256, 8, 17, 15, 128, false, false>",
+    "c4_hash": "k_c4_tiny<false>", "closure": "k_closure", "c4_plan": "k_c4_plan",
     "build": "(CSR builder kernels)", "tri_hubs": "k_hub_insert", "c4_desc": "k_c4_desc",
-    "c4_bin": "k_c4_bin",
+    "c4_bin": "k_c4_filter<1024, 8, 20, 17, 512, false, false>",
 }
 
 

@@ -70,7 +70,7 @@ typedef struct {
 #define M4_SERIAL 0x40u         /* single graph: run the triangle and 4-cycle stages
                                    one after the other on one stream (by default
                                    they overlap on two streams, except when
-                                   4-cycle owners are binned)                      */
+                                   4-cycle owners take the large filter)           */
 #define M4_BASIS_WEDGE 0x80u    /* single graph: count 4-cycles with degree-ordered
                                    wedges, each at its highest vertex            */
 #define M4_BASIS_EDGE 0x100u    /* single graph: count 4-cycles and 4-paths from
@@ -106,12 +106,12 @@ enum {
   M4_K_TRI_WAVE,      /* ... out-degree <= tri_wave_max, one wavefront each    */
   M4_K_C4_PLAN,       /* 4-cycle wedge bounds and owner buckets                 */
   M4_K_C4_WINDOW,     /* 4-cycle owners with windows of dense LDS counters     */
-  M4_K_C4_MED,        /* ... medium wedge bound, 16384-slot LDS hash table     */
-  M4_K_C4_HASH,       /* ... small wedge bound, 4096-slot LDS hash table       */
+  M4_K_C4_MED,        /* ... medium wedge bound, LDS bitmap filter and table    */
+  M4_K_C4_HASH,       /* ... small wedge bound, LDS table or small filter       */
   M4_K_CLOSURE,       /* closure sums and exact inverse                         */
   M4_K_TRI_HUBS,      /* hub tables of the long out-lists (triangle probes)     */
   M4_K_C4_DESC,       /* 4-cycle window owners' segment descriptors             */
-  M4_K_C4_BIN,        /* 4-cycle owners binned by counter window                */
+  M4_K_C4_BIN,        /* 4-cycle owners spread over many windows, large filter  */
   M4_K_EDGE,          /* edge-anchor basis: adjacent pairs of A_e x B_e         */
   M4_NK = 16
 };
@@ -126,10 +126,8 @@ enum {
  *                   per scanned element, two per 8-byte table slot probed)
  *   4-cycle slots:  k_elems = wedge endpoints counted, k_rows = owners,
  *                   k_aux = lower neighbours (segments), k_aux2 = segment
- *                   visits (window slot), row entries read (table slots;
- *                   an owner counted in rank ranges reads its rows once per
- *                   pass) or row entries read by the histogram and scatter
- *                   passes (binned slot)
+ *                   visits (window slot) or walks over an owner's rows
+ *                   (filters; a tiny owner's endpoints for the table)
  *   edge basis:     k_elems = row entries scanned, k_rows = owners with an
  *                   out-neighbour, k_aux = (out-neighbour, neighbour) pairs
  *   closure:        k_elems = oriented edges, k_rows = vertices
@@ -245,7 +243,7 @@ typedef struct {
                             out-lists (4 m bytes) fit in the 256 MiB Infinity
                             Cache                                              */
   int32_t c4_light_max;  /* single graph: owners with wedge bound <= this use the
-                            LDS hash (1..2048, default 2048)                   */
+                            small table or filter (1..2048, default 2048)      */
   int32_t batch_variant; /* fused batched kernel: 0 = 1024 threads with 96 KiB of
                             LDS tiles (out-degrees up to 768), 1 = 512 threads
                             with 40 KiB (up to 448); default 0                 */
@@ -257,32 +255,29 @@ typedef struct {
                             scanning the list when that is cheaper (0 = never,
                             else 4..65536, default 32)                        */
   int32_t c4_med_max;    /* single graph: owners with wedge bound in
-                            (c4_light_max, c4_med_max] use the 16384-slot LDS
-                            hash in one pass, heavier ones the counter windows
-                            (0 = no medium bucket, else up to 12288, default
-                            12288)                                            */
+                            (c4_light_max, c4_med_max] use the medium LDS
+                            filter, heavier ones the counter windows (0 = no
+                            medium bucket, else up to 12288, default 12288)   */
   int32_t probe_w;       /* single graph: a triangle row is probed in the hub
                             table when probe_w * (probes) < 3 * (elements a
                             scan would read) (1..256, default 4), while the
                             hub tables fit in the 256 MiB Infinity Cache     */
   int32_t c4_med_win;    /* single graph: an owner with wedge bound in
-                            (12288, 65536] also uses the medium table, one
-                            pass per rank range of at most 12288 endpoints,
-                            when 16 * (windows it needs) >= c4_med_win *
+                            (12288, 65536] also uses the medium filter when
+                            16 * (windows it needs) >= c4_med_win *
                             ceil(bound / 12288), i.e. its endpoints are thin
                             over many windows (0 = never, default 64; needs
                             c4_med_max > 0)                                   */
   int32_t c4_bin_win;    /* single graph: an owner above the one-pass medium
                             bound whose endpoints span at least this many
-                            counter windows is counted by binning: its
-                            endpoints are sorted into per-window bins in
-                            device memory, then each bin is counted in LDS
-                            (0 = never, default 6)                            */
-  int32_t c4_bin_cap;    /* single graph: endpoints one binning workgroup's
-                            device scratch holds (0 = 2^20, else 64..2^24);
-                            an owner with more is binned in several rank
-                            ranges                                           */
-  int32_t c4_bin_dense;  /* single graph: an owner that c4_bin_win would bin
+                            counter windows is counted by the large LDS
+                            filter (0 = never, default 6)                     */
+  int32_t c4_bin_cap;    /* single graph: endpoints above the filter's bitmaps
+                            that one class of a large filtered owner is
+                            planned for (0 = 3/4 of its table, else 64..2^24);
+                            an owner with more is counted in several classes,
+                            one walk over its rows each                       */
+  int32_t c4_bin_dense;  /* single graph: an owner that c4_bin_win would filter
                             keeps the dense counter windows when its wedge
                             bound is at least this many endpoints per window
                             it needs (0 = never, else 64..2^20, default

@@ -264,13 +264,11 @@ Tuning tuning_for(const m4_ctx* c, const m4_opts* o) {
   if (o && o->tri_wave_max > 0) tu.tri_wave_max = tu.tri_wave_far = o->tri_wave_max;
   if (o && o->c4_light_max > 0) tu.c4_light_max = o->c4_light_max;
   if (o && o->c4_med_max != 0) tu.c4_med_max = o->c4_med_max < 0 ? 0 : o->c4_med_max;
-  // the light table holds C4_HASH_SLOTS keys at load <= 1/2, the medium one
-  // C4_MED_SLOTS keys at load <= 3/4 in one pass
   tu.c4_light_max = std::max(0, std::min(tu.c4_light_max, C4_HASH_SLOTS / 2));
   tu.c4_med_max = std::max(0, std::min(tu.c4_med_max, 3 * C4_MED_SLOTS / 4));
-  // the binned 4-cycle owners take scratch sized by the CU count, which a
-  // device budget and the fixed scratch do not provide for
-  if ((o && o->device_budget_bytes > 0) || c->no_alloc) tu.c4_bin_win = 0;
+  // the large filter cuts its rank ranges by the degrees' prefix sums, which
+  // the partitions of a budgeted call do not hold
+  if (o && o->device_budget_bytes > 0) tu.c4_bin_win = 0;
   return tu;
 }
 
@@ -316,9 +314,9 @@ void run_resident(m4_ctx* c, const int64_t* rp, const int32_t* col, int64_t n, i
   // on the context's second stream (forked from and joined back into s), so
   // that each fills the CUs the other's tail leaves idle (triangle kernels
   // are queued first: measured slightly ahead of the reverse order).  When
-  // 4-cycle owners are binned the stages run in order: the binning kernel
-  // keeps two persistent workgroups and all of the LDS on every CU, and
-  // sharing the CUs with the triangle kernels measured slower.
+  // 4-cycle owners take the large filter the stages run in order: its
+  // workgroup holds all of the LDS of its CU, and sharing the CUs with the
+  // triangle kernels measured slower.
   const size_t c4_bytes = c4_tmp_bytes(n);
   Arena at, ac;
   at.base = c->tmp.ptr;
@@ -438,7 +436,7 @@ extern "C" int m4_count_motifs4_ex(m4_ctx* ctx, const m4_csr* g, const m4_opts* 
   if (timing) M4_HIP(hipEventRecord(ctx->ev[6], s));
   Prep P;
   run_resident(ctx, rp, col, g->n, g->nnz, o, s, P, timing);
-  M4_HIP(hipMemcpyAsync(ctx->scal_host, ctx->scal, sizeof(Scal), hipMemcpyDeviceToHost, s));
+  M4_HIP(hipMemcpyAsync(ctx->scal_host, ctx->scal, kScalHead, hipMemcpyDeviceToHost, s));
   M4_HIP(hipStreamSynchronize(s));
   const Scal& h = *ctx->scal_host;
   if (h.err) return scal_error(ctx, h.err);
@@ -505,7 +503,7 @@ extern "C" int m4_edge_triangles(m4_ctx* ctx, const m4_csr* g, const m4_opts* o,
   edge_t_to_input(P, rp, col, dst, s);
   if (!g->on_device)
     M4_HIP(hipMemcpyAsync(t_out, dst, (size_t)g->nnz * 4, hipMemcpyDeviceToHost, s));
-  M4_HIP(hipMemcpyAsync(ctx->scal_host, ctx->scal, sizeof(Scal), hipMemcpyDeviceToHost, s));
+  M4_HIP(hipMemcpyAsync(ctx->scal_host, ctx->scal, kScalHead, hipMemcpyDeviceToHost, s));
   M4_HIP(hipStreamSynchronize(s));
   if (ctx->scal_host->err) return scal_error(ctx, ctx->scal_host->err);
   return M4_OK;
@@ -591,7 +589,7 @@ extern "C" int m4_count_orbits4(m4_ctx* ctx, const m4_csr* g, const m4_opts* o,
                gblocks ? reinterpret_cast<unsigned long long*>(ctx->big2.ptr + arr_bytes) : nullptr,
                gblocks, kmax, dst, ctx->num_cu, s);
   if (!g->on_device) M4_HIP(hipMemcpyAsync(orbits, dst, out_bytes, hipMemcpyDeviceToHost, s));
-  M4_HIP(hipMemcpyAsync(ctx->scal_host, ctx->scal, sizeof(Scal), hipMemcpyDeviceToHost, s));
+  M4_HIP(hipMemcpyAsync(ctx->scal_host, ctx->scal, kScalHead, hipMemcpyDeviceToHost, s));
   M4_HIP(hipStreamSynchronize(s));
   const Scal& h = *ctx->scal_host;
   if (h.err & 8) return set_error(ctx, M4_EINTERNAL, "per-vertex orbit inverse went negative");

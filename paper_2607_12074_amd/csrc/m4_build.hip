@@ -365,7 +365,7 @@ void degree_order(const int64_t* rp, const int32_t* col, int64_t n, int64_t nnz,
   int64_t* rtmp = tmp.take<int64_t>(radix_tmp_elems(n, 8));
   if (!kA || !kB || !vB || !rtmp) throw Fail(M4_EINTERNAL, "workspace too small (build)");
   k_degree<<<blocks_for(n, 1024), 1024, 0, s>>>(rp, n, kA, scal);
-  M4_HIP(hipMemcpyAsync(scal_host, scal, sizeof(Scal), hipMemcpyDeviceToHost, s));
+  M4_HIP(hipMemcpyAsync(scal_host, scal, kScalHead, hipMemcpyDeviceToHost, s));
   M4_HIP(hipStreamSynchronize(s));
   if (scal_host->err) throw Fail(M4_EINVAL, "CSR is not simple, symmetric and sorted");
   const uint32_t dmax = scal_host->dmax;

@@ -14,18 +14,20 @@
 // Vertices of degree <= 1 have rank < r1 and never contribute (c <= 1), so
 // endpoints below r1 are skipped.  Owners are split by the wedge bound
 // W_u = sum_{v in L(u)} (d(v) - 1):
-//   hash bucket   -- small W_u: 256 threads, 4096-slot open-addressing
-//                    table in LDS;
-//   medium bucket -- W_u up to 3/4 of 16384: 1024 threads, 16384-slot table;
-//   window bucket -- large W_u: one 1024-thread workgroup, dense counters in
-//                    LDS over windows of 128 KiB; a counter is 4 bits wide
-//                    for endpoints of degree <= 15, 8 bits for degree <= 255
-//                    and 32 bits beyond (c_u[w] never exceeds d(w)), so a
-//                    window spans up to 262144 ranks; every lower neighbour
-//                    keeps a cursor into its sorted row so each window reads
-//                    exactly its own endpoints.
-// A table costs per wedge; a window costs per rank of the owner's range, so
-// owners whose endpoints are sparse over many windows belong in a table.
+//   tiny bucket   -- W_u <= 256: one wavefront, a table in LDS;
+//   light, medium and large filter buckets -- one workgroup of 64, 256 or
+//                    1024 threads: LDS bitmaps tell the endpoints met once
+//                    from the others, which a table then counts;
+//   window bucket -- large W_u dense over the ranks: one 1024-thread
+//                    workgroup, dense counters in LDS over windows of
+//                    128 KiB; a counter is 4 bits wide for endpoints of
+//                    degree <= 15, 8 bits for degree <= 255 and 32 bits
+//                    beyond (c_u[w] never exceeds d(w)), so a window spans up
+//                    to 262144 ranks; every lower neighbour keeps a cursor
+//                    into its sorted row so each window reads exactly its own
+//                    endpoints.
+// A filter costs per wedge; a window costs per rank of the owner's range, so
+// owners whose endpoints are sparse over many windows belong in a filter.
 #include <limits.h>
 
 #include <algorithm>
@@ -53,12 +55,15 @@ struct C4Args {
   unsigned int* work;
   Scal* scal;
   uint32_t flags;
-  const int64_t* seg_off;  // window and binned owners: first descriptor of each owner
+  const int64_t* seg_off;  // window owners: first descriptor of each owner
   int4* desc;              // ... per-segment cursor descriptors
-  const int64_t* seg_pre;  // ... exclusive prefix of segment lengths within the owner
   const int32_t* seg_cnt;  // ... non-empty segments of each owner
-  int32_t* bins;           // binned owners: per-block scratch of bin_cap endpoints
-  int64_t bin_cap;
+  const int64_t* deg_pre;  // prefix sums of the degrees by rank
+  const int4* vmeta;       // per full row: offset, degree, lower neighbours, entries below r1
+  unsigned long long* n8;  // per-vertex 4-cycle credits (orbit counts), or null
+  int yb;                  // filtered owners: bits of a permuted rank
+  int grab;                // tiny owners: owners of a run
+  int class_cap;           // candidates a class of a filtered owner is planned for (0: 3/4 of its table)
   // counter zones of the window owners (ranks >= r1): 4-bit counters for
   // ranks [r1, z1) (degree <= 15), 8-bit for [z1, z2) (degree <= 255), 32-bit
   // from z2 on; aw and bw are the words of the first two zones
@@ -79,18 +84,33 @@ __global__ void k_zone_bounds(const int32_t* __restrict__ dr, int64_t n, int64_t
   out[i] = lo;
 }
 
-// Multi-pass medium owners (wedge bound above 3/4 of the table) are counted
-// over rank ranges cut from a histogram with bins of 2^hs ranks, 2^hs <=
-// C4_MED_BIN_MAX, so one bin never holds more distinct endpoints than a pass
-// may insert; their rank span must fit C4_MED_SLOTS such bins.  A wedge
-// bound of at most C4_MED_MAX needs at most 12 ranges.
-constexpr int C4_MED_BIN_MAX = 8192;
-constexpr int C4_MED_RANGES = 32;
-constexpr int64_t C4_MED_SPAN = (int64_t)C4_MED_SLOTS * C4_MED_BIN_MAX;
+// Owners with wedge bounds in (12288, C4_MED_MAX] join the medium bucket when
+// their endpoints are thin over many windows; the rule counts ranges of
+// C4_MED_CAP endpoints against windows.
 constexpr int64_t C4_MED_CAP = 3 * C4_MED_SLOTS / 4;
-// most counter windows of a binned owner (its per-bucket histogram, over
-// buckets 16 times finer, is in LDS)
-constexpr int C4_BIN_KMAX = 248;
+
+// Filtered owners: log2 of the bits of the first and second LDS bitmap of
+// each bucket (the first holds 2^(bits - 5) table slots afterwards).
+constexpr int C4_LIGHT_AB = 15, C4_LIGHT_BB = 13;
+constexpr int C4_MED_AB = 17, C4_MED_BB = 15;
+constexpr int C4_BIN_AB = 20, C4_BIN_BB = 17;
+constexpr int C4_DISP_BITS = 6;                  // distance of a slot from its home slot
+constexpr uint32_t C4_MAX_CLASSES = 1u << 16;
+constexpr uint32_t C4_KEY_MUL = 0x9E3779B1u, C4_KEY_INV = 0x0E8B2F51u;  // MUL x INV = 1 mod 2^32
+// endpoints of one rank range of a large filtered owner
+constexpr int64_t C4_BIN_RANGE = 131072;
+
+// Bits of a permuted rank for tables of 2^hb slots, and the first number of
+// lower neighbours whose counts do not fit beside the key in a slot.
+inline int c4_key_bits(int64_t n, int hb) {
+  int b = hb;
+  while ((int64_t(1) << b) < n) b++;
+  return b;
+}
+inline int32_t c4_count_limit(int64_t n, int hb) {
+  const int bits = 32 - C4_DISP_BITS - (c4_key_bits(n, hb) - hb);
+  return bits >= 31 ? INT_MAX : (bits <= 0 ? 0 : 1 << bits);
+}
 
 // Windows of dense counters owner u needs over ranks [r1, u); zb holds the
 // first ranks of degree > 15 and > 255 (the zone bounds).
@@ -105,33 +125,38 @@ __device__ __forceinline__ int64_t c4_windows(const int64_t* zb, int64_t r1, int
   return (words + C4_WIN_WORDS - 1) / C4_WIN_WORDS;
 }
 
-// Bucket of owner u with wedge bound w > 0.  A table pass costs about one
-// read of every wedge endpoint and a window costs a pass over the owner's
-// lower neighbours, so an owner above the single-pass bound goes to the
-// ranged table only when its endpoints are thin over many windows:
-// 16 windows >= med_win ranges (med_win 0: never).
-// Beyond the one-pass table, an owner whose endpoints span at least bin_win
-// windows (and at most C4_BIN_KMAX) is binned: its endpoints are sorted into
-// per-window bins in device memory before counting, so a window costs only
-// its own endpoints instead of a pass over every lower neighbour's cursor;
-// unless they average at least bin_dense per window, where a dense window's
-// fixed cost is small beside its endpoints.
+// Bucket of owner u with wedge bound w > 0 and nl lower neighbours.  Owners up
+// to C4_TINY_MAX wedges take one wavefront and a table, the ones above a
+// bitmap filter sized to their bound.  Beyond the one-pass medium bound a
+// dense window costs a pass over the owner's lower neighbours, so an owner
+// goes to the filter of the ranged medium bucket only when its endpoints are
+// thin over many windows (16 windows >= med_win ranges; med_win 0: never), to
+// the large filter when they span at least bin_win windows and average fewer
+// than bin_dense endpoints per window, and else keeps the dense windows.  A
+// filter needs its counts to fit beside the key (lower neighbours below its
+// limit); with credits (orbit counts) there are no dense windows and the
+// large filter takes the rest, or its variant with 64-bit slots.
 struct C4Plan {
   int light_max, med_max, med_win, bin_win, bin_dense;
   const int64_t* zb;
   int64_t r1;
+  int32_t lim_light, lim_med, lim_bin;
+  int credit;
 };
-__device__ __forceinline__ uint32_t c4_bucket(const C4Plan& pl, int64_t w, int64_t u) {
-  if (w <= pl.light_max) return CB_HASH;
-  if (pl.med_max > 0 && w <= pl.med_max && w <= C4_MED_CAP) return CB_MED;
+__device__ __forceinline__ uint32_t c4_bucket(const C4Plan& pl, int64_t w, int64_t u, int nl) {
+  if (w <= pl.light_max) {
+    if (w <= C4_TINY_MAX) return CB_TINY;
+    if (nl < pl.lim_light) return CB_HASH;
+  }
+  if (pl.med_max > 0 && w <= pl.med_max && w <= C4_MED_CAP && nl < pl.lim_med) return CB_MED;
   const int64_t nwin = c4_windows(pl.zb, pl.r1, u);
-  if (pl.bin_win > 0 && nwin >= pl.bin_win && nwin <= C4_BIN_KMAX &&
+  if (pl.bin_win > 0 && nwin >= pl.bin_win && nl < pl.lim_bin &&
       (pl.bin_dense <= 0 || w < (int64_t)pl.bin_dense * nwin))
     return CB_BIN;
-  if (pl.med_max <= 0) return CB_WIN;
-  if (pl.med_win > 0 && w <= C4_MED_MAX && u - pl.r1 < C4_MED_SPAN &&
+  if (pl.med_max > 0 && pl.med_win > 0 && w <= C4_MED_MAX && nl < pl.lim_med &&
       16 * nwin >= (int64_t)pl.med_win * ((w + C4_MED_CAP - 1) / C4_MED_CAP))
     return CB_MED;
+  if (pl.credit) return nl < pl.lim_bin ? CB_BIN : CB_WIDE;
   return CB_WIN;
 }
 
@@ -167,7 +192,7 @@ __global__ __launch_bounds__(256) void k_c4_plan(const int64_t* __restrict__ npt
   if (ok && j == 0) {
     wub[u] = s;
     uint32_t k = CB_NONE;
-    if (u >= r1 && nl >= 2 && s > 0) k = c4_bucket(pl, s, u);
+    if (u >= r1 && nl >= 2 && s > 0) k = c4_bucket(pl, s, u, nl);
     key[u] = k;
   }
 }
@@ -195,237 +220,559 @@ __global__ __launch_bounds__(1024) void k_c4_plan_big(const int64_t* __restrict_
   if (threadIdx.x == 0) {
     wub[u] = tot;
     uint32_t k = CB_NONE;
-    if (u >= r1 && nl >= 2 && tot > 0) k = c4_bucket(pl, tot, u);
+    if (u >= r1 && nl >= 2 && tot > 0) k = c4_bucket(pl, tot, u, nl);
     key[u] = k;
   }
 }
 
-// --------------------------------------------------------- hash buckets
-// Streams the wedge endpoints x in [r1, u) of owner u to fn: the rows of the
-// lower neighbours, NT at a time, are flattened by a scan of their lengths;
-// every thread takes UNR endpoints per round with their loads in flight
-// together.  Called by every thread of the workgroup.
-template <int NT, int UNR, class F>
-__device__ __forceinline__ void c4_endpoints(const C4Args& A, int32_t u, int nl, int64_t base,
-                                             int32_t* sst, int32_t* spref,
-                                             unsigned long long& reads, F&& fn) {
-  const int tid = threadIdx.x;
-  for (int c0 = 0; c0 < nl; c0 += NT) {
-    const int nc = nl - c0 < NT ? nl - c0 : NT;
-    int len = 0;
-    if (tid < nc) {
-      const int32_t v = A.ncol[base + c0 + tid];
-      sst[tid] = (int32_t)A.nptr[v];
-      len = A.row_len ? A.row_len[v] : A.dr[v];
+__device__ __forceinline__ int64_t readlane64(int64_t v, int l) {
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, l);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// ---------------------------------------------------- segment walks
+// The lower neighbours of an owner, taken from the highest rank down (the
+// longest rows first, so that the short ones fill the walk's tail), as
+// segments [first entry >= r1, row end) of the rank-space column array.
+// Segments are not cut at the owner: a walk stops by value.
+
+// Segments [s0, s0 + cnt) of owner row [base, base + nl) into LDS (and their
+// vertices, where VERT), from their first entry >= lo on, an empty one after
+// them.  Called by every thread of the workgroup.
+template <int NT, bool VERT>
+__device__ __forceinline__ void load_segs(const C4Args& A, int64_t base, int nl, int s0, int cnt,
+                                          int32_t lo, int2* sg, int32_t* sv) {
+  if (threadIdx.x == 0) sg[cnt] = make_int2(0, 0);
+  for (int j = threadIdx.x; j < cnt; j += NT) {
+    const int32_t v = A.ncol[base + nl - 1 - s0 - j];
+    if (A.vmeta) {
+      const int4 m = A.vmeta[v];  // row offset, degree, lower neighbours, entries below r1
+      const int64_t c = m.x + m.w, e = m.x + m.y;
+      sg[j] = make_int2((int)(lo > A.zr1 ? lower_index(A.ncol, c, e, lo) : c), (int)e);
+    } else {
+      // a partition stores row prefixes: one at most as long as the owner needs
+      const int64_t rs = A.nptr[v];
+      const int64_t e = rs + (A.row_len ? A.row_len[v] : A.dr[v]);
+      sg[j] = make_int2((int)lower_index(A.ncol, rs, e, lo), (int)e);
     }
-    int64_t tot;
-    const int64_t ex = block_excl_scan64<NT>(len, &tot);
-    if (tid < nc) spref[tid] = (int32_t)ex;
-    if (tid == 0) spref[nc] = (int32_t)tot;
-    __syncthreads();
-    const int total = (int)tot;
-    if (tid == 0) reads += (unsigned long long)total;
-    for (int q0 = 0; q0 < total; q0 += NT * UNR) {
-      int32_t w[UNR];
-#pragma unroll
-      for (int j = 0; j < UNR; j++) {
-        const int q = q0 + j * NT + tid;
-        w[j] = INT_MAX;
-        if (q < total) {
-          const int si = upper_index(spref, nc, q);
-          w[j] = A.ncol[sst[si] + (q - spref[si])];
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < UNR; j++)
-        if (w[j] >= A.r1 && w[j] < u) fn(w[j]);
-    }
-    __syncthreads();
+    if (VERT) sv[j] = v;
   }
 }
 
-// One owner at a time per workgroup, counting in an open-addressing table in
-// LDS (linear probing, keys inserted with compare-and-swap).  The table is
-// sized to a power of two of at least twice the wedge bound, capped at
-// SLOTS; the number of distinct endpoints never exceeds the wedge bound, so
-// while that bound is at most 3/4 of SLOTS a probe always ends.  Owners of
-// the medium bucket with a larger bound (1024 threads only) are counted in
-// rank ranges: a first pass histograms their endpoints over bins of ranks,
-// the bins are cut greedily into ranges of at most 3/4 SLOTS endpoints (or
-// one bin, which holds at most C4_MED_BIN_MAX distinct ranks), and every
-// range is one pass over the rows that inserts only its own endpoints.  Each
-// endpoint lies in exactly one range, so every c_u[w] is complete in its
-// pass.
-template <int NT, int SLOTS, int UNR>
-__global__ __launch_bounds__(NT) void k_c4_hash(C4Args A) {
+// Walks the entries below hi of segments [0, nseg): groups of GL lanes take
+// segments one at a time from *next (LDS, zero at the start), a step being
+// 4 GL entries as one aligned 16-byte load per lane.  A group that meets an
+// entry >= hi or the segment's end (both show in its last lane: entries
+// ascend, and the lanes past the end count as ended) takes its next segment
+// before it works on the step, so the following load is always in flight.
+// One LDS atomic per wavefront serves all of its groups that end in a step.
+// Groups without a segment hold the empty one at sg[nseg].  The per-entry
+// tests stay in vector registers (one unsigned compare for the segment, one
+// for hi): a version with lane-mask logic was bound by the scalar unit.
+//   ent(x)        the lane's four entries, INT_MAX where not of the segment
+//                 (an entry counts when it is below hi)
+//   fin(i, last)  after a step, by every lane of the wavefront; last is set
+//                 in the groups whose segment i (i < nseg) ended with it
+template <int GL, class Ent, class Fin>
+__device__ __forceinline__ void seg_walk(const int32_t* __restrict__ ncol, int32_t hi, int nseg,
+                                         int* next, const int2* sg, Ent&& ent, Fin&& fin) {
+  static_assert(4 * GL <= NCOL_PAD, "a step may read 4 GL entries past a cursor");
+  const int lane = threadIdx.x & (WAVE - 1), gl = lane & (GL - 1);
+  constexpr uint64_t LASTS = GL == 8 ? 0x8080808080808080ull : 0x8000800080008000ull;
+  static_assert(GL == 8 || GL == 16, "a group is 8 or 16 lanes");
+  const int4* __restrict__ ncol4 = reinterpret_cast<const int4*>(ncol);
+  // indices for the groups whose last lane is set in m (nonzero, uniform):
+  // a lane's value is its own group's when that is among them
+  auto grab = [&](uint64_t m) {
+    int b = 0;
+    if (lane == 0) b = atomicAdd(next, (int)__popcll(m));
+    return __builtin_amdgcn_readfirstlane(b) +
+           (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                          __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+  };
+  int i = min(grab(LASTS), nseg);
+  int2 s = sg[i];
+  int q4 = (s.x >> 2) + gl;           // the lane's 16-byte load
+  int off = (q4 << 2) - s.x;          // its first entry's place in the segment
+  int len = s.y - s.x;
+  int4 a = ncol4[q4];
+  while (__ballot(i < nseg)) {
+    const uint64_t ended = __ballot(max(a.w - hi, off + 4 - len) >= 0) & LASTS;
+    const int sh = lane | (GL - 1);
+    const bool last = (((sh < 32 ? (uint32_t)ended : (uint32_t)(ended >> 32)) >> (sh & 31)) & 1) != 0;
+    int ni = i, nq4 = q4 + GL, noff = off + 4 * GL, nlen = len;
+    if (ended) {
+      const int g = min(grab(ended), nseg);
+      const int2 t = sg[g];
+      const int t4 = (t.x >> 2) + gl;
+      ni = last ? g : ni;
+      nq4 = last ? t4 : nq4;
+      noff = last ? (t4 << 2) - t.x : noff;
+      nlen = last ? t.y - t.x : nlen;
+    }
+    const int4 nx = ncol4[nq4];
+    const int32_t x[4] = {(unsigned)off < (unsigned)len ? a.x : INT_MAX,
+                          (unsigned)(off + 1) < (unsigned)len ? a.y : INT_MAX,
+                          (unsigned)(off + 2) < (unsigned)len ? a.z : INT_MAX,
+                          (unsigned)(off + 3) < (unsigned)len ? a.w : INT_MAX};
+    ent(x);
+    fin(i, last && i < nseg);
+    i = ni;
+    q4 = nq4;
+    off = noff;
+    len = nlen;
+    a = nx;
+  }
+}
+
+__device__ __forceinline__ unsigned long long pairs_of(unsigned long long c) {
+  return c * (c - 1) / 2;
+}
+
+template <int GL>
+__device__ __forceinline__ unsigned long long lane_group_sum(unsigned long long v) {
+#pragma unroll
+  for (int o = GL / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
+  return v;
+}
+
+// --------------------------------------------------------- tiny bucket
+// One wavefront per owner with at most C4_TINY_MAX wedges: all endpoints in
+// an open-addressing table in LDS, sized to twice the bound.  CRED adds the
+// per-vertex credits to n8: C(c, 2) to the endpoint and the owner, the other
+// wedges of its endpoint to each middle vertex.
+template <bool CRED>
+__global__ __launch_bounds__(WAVE) void k_c4_tiny(C4Args A) {
+  constexpr int SLOTS = 2 * C4_TINY_MAX, SEGS = WAVE;
   __shared__ int32_t hkey[SLOTS];
   __shared__ uint32_t hcnt[SLOTS];
-  __shared__ int32_t sst[NT];
-  __shared__ int32_t spref[NT + 1];
-  __shared__ int32_t s_rng[C4_MED_RANGES + 1];
-  __shared__ int s_item, s_nr;
-  __shared__ uint32_t s_tot;
-  constexpr uint32_t CAP = 3 * SLOTS / 4;
-  const int tid = threadIdx.x;
+  __shared__ int2 sg[SEGS + 1];
+  __shared__ int32_t sv[CRED ? SEGS : 1];
+  __shared__ int s_next;
+  const int lane = threadIdx.x;
   const int64_t b0 = A.start[A.bucket], cnt = A.start[A.bucket + 1] - b0;
   u128_t acc = 0;
-  unsigned long long wedges = 0, owners = 0, segs = 0, reads = 0;
-  for (int i = tid; i < SLOTS; i += NT) {
+  unsigned long long wedges = 0, owners = 0, segs = 0;
+  for (int i = lane; i < SLOTS; i += WAVE) {
     hkey[i] = -1;
     hcnt[i] = 0;
   }
-  const int GRAB = NT >= 1024 ? 1 : 8;
-  int64_t item = 0, last = 0;
-  for (;;) {
-    if (item == last) {
-      if (tid == 0) s_item = (int)atomicAdd(A.work, (unsigned)GRAB);
-      __syncthreads();
-      item = s_item;
-      __syncthreads();
-      if (item >= cnt) break;
-      last = item + GRAB < cnt ? item + GRAB : cnt;
-    }
-    const int32_t u = A.order[b0 + item];
-    item++;
-    const int nl = A.dlo[u];
-    const int64_t base = A.nptr[u];
-    const int64_t wb = A.wub[u];
-    int S = 64;
-    while (S < 2 * wb && S < SLOTS) S <<= 1;
-    const uint32_t mask = (uint32_t)S - 1;
-    const int shift = 32 - __ffs(S) + 1;
-    if (tid == 0) {
+  // the owners cost about the same: runs of A.grab owners, dealt to the
+  // wavefronts in turn
+  for (int64_t first = (int64_t)blockIdx.x * A.grab; first < cnt;
+       first += (int64_t)gridDim.x * A.grab) {
+    // the owners of a run, one per lane
+    const int64_t mine = first + lane;
+    const bool have = lane < A.grab && mine < cnt;
+    const int32_t mu = have ? A.order[b0 + mine] : 0;
+    const int32_t mnl = have ? A.dlo[mu] : 0;
+    const int64_t mbase = have ? A.nptr[mu] : 0;
+    const int32_t mwb = have ? (int32_t)A.wub[mu] : 0;
+    const int nown = (int)std::min<int64_t>(A.grab, cnt - first);
+    for (int o = 0; o < nown; o++) {
+      const int32_t u = __builtin_amdgcn_readlane(mu, o);
+      const int nl = __builtin_amdgcn_readlane(mnl, o);
+      const int32_t wb = __builtin_amdgcn_readlane(mwb, o);
+      const int64_t base = readlane64(mbase, o);
+      int S = 64;
+      while (S < 2 * wb) S <<= 1;
+      const uint32_t mask = (uint32_t)S - 1;
+      const int shift = 32 - (__ffs(S) - 1);
       owners++;
       segs += (unsigned long long)nl;
-    }
-    // at most 3/4 S distinct keys: every probe meets x or a free slot within
-    // S steps (a longer one means a broken bound and is reported, not spun)
-    auto insert = [&](int32_t x) {
-      uint32_t h = ((uint32_t)x * 0x9E3779B1u) >> shift;
-      bool ok = false;
-      for (int probes = 0; probes < S; probes++) {
-        const int32_t k = hkey[h];
-        if (k == x) {
-          ok = true;
-          break;
+      // at most wb <= S / 2 distinct keys: a probe meets x or a free slot
+      // within S steps
+      auto insert = [&](int32_t x) {
+        uint32_t h = ((uint32_t)x * 0x9E3779B1u) >> shift;
+        for (int probes = 0; probes < S; probes++) {
+          const int32_t k = hkey[h];
+          if (k == x) return atomicAdd(&hcnt[h], 1u);
+          if (k == -1) {
+            const int32_t prev = atomicCAS(&hkey[h], -1, x);
+            if (prev == -1 || prev == x) return atomicAdd(&hcnt[h], 1u);
+          }
+          h = (h + 1) & mask;
         }
-        if (k == -1) {
-          const int32_t prev = atomicCAS(&hkey[h], -1, x);
-          if (prev == -1 || prev == x) {
-            ok = true;
+        atomicOr(&A.scal->err, ERR_PROBE);
+        return 0u;
+      };
+      for (int s0 = 0; s0 < nl; s0 += SEGS) {
+        const int nc = nl - s0 < SEGS ? nl - s0 : SEGS;
+        load_segs<WAVE, CRED>(A, base, nl, s0, nc, A.zr1, sg, sv);
+        if (lane == 0) s_next = 0;
+        wave_sync();
+        unsigned part = 0;
+        seg_walk<8>(A.ncol, u, nc, &s_next, sg,
+                    [&](const int32_t(&x)[4]) {
+#pragma unroll
+                      for (int k = 0; k < 4; k++)
+                        if (x[k] < u) {
+                          wedges++;
+                          part += insert(x[k]);
+                        }
+                    },
+                    [](int, bool) {});
+        acc += part;
+        wave_sync();
+      }
+      if (CRED) {
+        for (int s0 = 0; s0 < nl; s0 += SEGS) {
+          const int nc = nl - s0 < SEGS ? nl - s0 : SEGS;
+          if (nl > SEGS) load_segs<WAVE, CRED>(A, base, nl, s0, nc, A.zr1, sg, sv);
+          if (lane == 0) s_next = 0;
+          wave_sync();
+          unsigned long long cr = 0;
+          seg_walk<8>(A.ncol, u, nc, &s_next, sg,
+                      [&](const int32_t(&x)[4]) {
+#pragma unroll
+                        for (int k = 0; k < 4; k++)
+                          if (x[k] < u) {
+                            uint32_t h = ((uint32_t)x[k] * 0x9E3779B1u) >> shift;
+                            for (int pr = 0; hkey[h] != x[k] && pr < S; pr++) h = (h + 1) & mask;
+                            cr += hcnt[h] - 1;
+                          }
+                      },
+                      [&](int i, bool last) {
+                        if (!__ballot(last)) return;
+                        const unsigned long long t = lane_group_sum<8>(cr);
+                        if (last) {
+                          if ((lane & 7) == 0 && t) atomicAdd(&A.n8[sv[i]], t);
+                          cr = 0;
+                        }
+                      });
+          wave_sync();
+        }
+        unsigned long long own = 0;
+        for (int i = lane; i < S; i += WAVE) {
+          const unsigned long long c = hcnt[i];
+          if (c >= 2) {
+            own += pairs_of(c);
+            atomicAdd(&A.n8[hkey[i]], pairs_of(c));
+          }
+        }
+        own = lane_group_sum<WAVE>(own);
+        if (lane == 0 && own) atomicAdd(&A.n8[u], own);
+      }
+      for (int i = lane; i < S; i += WAVE) {
+        hkey[i] = -1;
+        hcnt[i] = 0;
+      }
+      wave_sync();
+    }
+  }
+  block_add_acc<WAVE>(A.scal, ACC_C4, acc);
+  if (A.flags & M4_STATS) {
+    block_add_u64<WAVE>(&A.scal->stat[ST_WEDGES], wedges);
+    block_add_u64<WAVE>(&A.scal->kstat[A.slot][0], wedges);
+    block_add_u64<WAVE>(&A.scal->kstat[A.slot][1], lane == 0 ? owners : 0);
+    block_add_u64<WAVE>(&A.scal->kstat[A.slot][2], lane == 0 ? segs : 0);
+    block_add_u64<WAVE>(&A.scal->kstat[A.slot][3], wedges);
+  }
+}
+
+// ------------------------------------------------------- filter buckets
+// Most wedge endpoints of a sparse owner are met once (88 % on the scale-24
+// web graph) and close no 4-cycle, so they are told apart before anything is
+// counted.  Per owner, one workgroup:
+//   1. a walk over the endpoints sets one bit per endpoint in an LDS bitmap
+//      (bit x mod 2^AB of rank x); an endpoint that finds its bit set also
+//      sets bit x mod 2^BB of a second one;
+//   2. a second walk counts exactly the endpoints whose bit is set in the
+//      second bitmap (those met twice, and a few that share bits with others)
+//      in a table laid over the first bitmap;
+//   3. CRED: a third walk adds to each middle vertex the other wedges of its
+//      endpoints, and a sweep of the table C(c, 2) to endpoints and owner.
+// Table slots: a rank is held as y = x K mod 2^yb (K odd: a bijection), home
+// slot = the high bits of y; a 32-bit slot keeps the rest of y, its distance
+// from the home slot (6 bits) and the count above them, which stays below
+// the owner's lower neighbours (the plan sends no owner whose number does
+// not fit).  WIDE slots hold rank + 1 and a 32-bit count.
+// An owner with more than C4_BIN_RANGE endpoints is counted in rank ranges
+// of about equal numbers of endpoints (an endpoint's chance to be rank x is
+// about proportional to the degree of x, and the row offsets are the
+// degrees' prefix sums).  A range with more candidates than the table holds
+// is counted in P classes of a second hash, one walk each; a class that
+// overflows the table is dropped, split in two and walked again, so every
+// owner ends.
+// Bound by vector issue (about 135 instructions per 256 entries, half of the
+// issue slots) and, at 16 wavefronts a CU, by the latency of a walk's one load
+// in flight.  Scale-24 web graph (268 M edges): the 395 K large owners (21.5 G
+// endpoints, 2.5 walks each) 103 ms, 209 ms when their endpoints were sorted
+// into bins in device memory; the 698 K medium ones (1.76 G) 9.0 ms, 33 ms in
+// 16384-slot tables with a search per endpoint; light and tiny ones 4.5 ms,
+// 18 ms.  Ranges of 82 K / 131 K / 164 K endpoints: 115 / 103 / 111 ms;
+// 512-thread workgroups, two a CU with half the bitmap: 167 ms.
+template <int AB, bool WIDE>
+struct FilterTable {
+  using Slot = std::conditional_t<WIDE, unsigned long long, uint32_t>;
+  static constexpr int HB = AB - 5 - (WIDE ? 1 : 0);  // home slot bits
+  static constexpr int N = 1 << HB;
+  static constexpr int PROBES = 1 << C4_DISP_BITS;
+  Slot* t;
+  uint32_t ymask, qmask;
+  int qb, cs;  // bits of y below the home slot; first bit of the count
+  __device__ __forceinline__ FilterTable(void* mem, int yb)
+      : t(static_cast<Slot*>(mem)),
+        ymask(yb >= 32 ? ~0u : (1u << yb) - 1u),
+        qmask(WIDE ? 0u : (1u << (yb - HB)) - 1u),
+        qb(yb - HB),
+        cs(WIDE ? 0 : yb - HB + C4_DISP_BITS) {}
+  // calls hit(slot pointer, its word) on the slot of x; false if none within
+  // PROBES of the home slot.  INS claims an empty slot (count 1, old count 0).
+  template <bool INS>
+  __device__ __forceinline__ bool find(int32_t x, unsigned long long& got) {
+    const uint32_t y = ((uint32_t)x * C4_KEY_MUL) & ymask;
+    uint32_t h = y >> qb;
+    const Slot one = WIDE ? Slot(1) : Slot(1) << cs;
+    const Slot idm = WIDE ? ~Slot(0xffffffffu) : one - 1;
+    Slot id = WIDE ? Slot((unsigned long long)(uint32_t)(x + 1) << 32) : Slot(y & qmask);
+    for (int d = 0; d < PROBES; d++) {
+      Slot w = t[h];
+      if (INS && w == 0) {
+        w = atomicCAS(&t[h], Slot(0), one | id);
+        if (w == 0) {
+          got = 0;
+          return true;
+        }
+      }
+      if ((w & idm) == id) {
+        if (INS) w = atomicAdd(&t[h], one);
+        got = count_of(w);
+        return true;
+      }
+      h = (h + 1) & (N - 1);
+      if (!WIDE) id += Slot(1) << qb;
+    }
+    return false;
+  }
+  __device__ __forceinline__ unsigned long long count_of(Slot w) const {
+    return WIDE ? (unsigned long long)(uint32_t)w : (unsigned long long)(w >> cs);
+  }
+  // the rank kept in slot i with word w
+  __device__ __forceinline__ uint32_t rank_of(int i, Slot w) const {
+    if (WIDE) return (uint32_t)((unsigned long long)w >> 32) - 1u;
+    const uint32_t home = ((uint32_t)i - ((uint32_t)(w >> qb) & (PROBES - 1u))) & (N - 1u);
+    return (((home << qb) | ((uint32_t)w & qmask)) * C4_KEY_INV) & ymask;
+  }
+};
+
+template <int NT, int GL, int AB, int BB, int SEGS, bool CRED, bool WIDE = false>
+__global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
+  using Table = FilterTable<AB, WIDE>;
+  constexpr int AW = 1 << (AB - 5), BW = 1 << (BB - 5);  // bitmap words
+  const unsigned long long CAP = A.class_cap > 0 ? A.class_cap : Table::N / 4 * 3;
+  __shared__ uint4 fa4[AW / 4];
+  __shared__ uint4 fb4[BW / 4];
+  __shared__ int2 sg[SEGS + 1];
+  __shared__ int32_t wq[NT / WAVE][2 * WAVE];  // per wavefront: candidates to count
+  __shared__ int32_t sv[CRED ? SEGS : 1];
+  __shared__ int s_item, s_next, s_over;
+  __shared__ unsigned s_dup;
+  uint32_t* fa = reinterpret_cast<uint32_t*>(fa4);
+  uint32_t* fb = reinterpret_cast<uint32_t*>(fb4);
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+  const int64_t b0 = A.start[A.bucket], cnt = A.start[A.bucket + 1] - b0;
+  Table tab(fa4, A.yb);
+  u128_t acc = 0;
+  unsigned long long wedges = 0, owners = 0, segs = 0, walks = 0;
+  // the first owner of a workgroup is its own; large owners then come from
+  // the work counter, asked one owner ahead; the many small ones are dealt
+  // in turn, since one counter serves only about 70 M atomics a second
+  constexpr bool DEAL = NT <= 256;
+  for (int64_t item = blockIdx.x; item < cnt;) {
+    unsigned ahead = 0;
+    if (!DEAL && tid == 0) ahead = atomicAdd(A.work, 1u);
+    const int64_t pos = cnt - 1 - item;  // heaviest owners (highest ranks) first
+    const int32_t u = __builtin_amdgcn_readfirstlane(A.order[b0 + pos]);
+    const int nl = __builtin_amdgcn_readfirstlane(A.dlo[u]);
+    const int64_t base = A.nptr[u];
+    const int64_t wb = A.wub[u];
+    const int R = (int)((wb + C4_BIN_RANGE - 1) / C4_BIN_RANGE);
+    owners++;
+    segs += (unsigned long long)nl;
+    unsigned long long own = 0;
+    int32_t lo = A.zr1;
+    for (int r = 0; r < R; r++) {
+      int32_t hi = u;
+      if (r + 1 < R) {
+        const int64_t c0 = A.deg_pre[A.r1], c1 = A.deg_pre[u];
+        hi = (int32_t)lower_index(A.deg_pre, (int64_t)lo, (int64_t)u,
+                                  c0 + (int64_t)((double)(c1 - c0) * (r + 1) / R));
+      }
+      if (hi <= lo) continue;
+      // ---- 1. the bitmaps
+      for (int i = tid; i < AW / 4; i += NT) fa4[i] = make_uint4(0, 0, 0, 0);
+      for (int i = tid; i < BW / 4; i += NT) fb4[i] = make_uint4(0, 0, 0, 0);
+      if (tid == 0) s_dup = 0;
+      // walks all segments, SEGS at a time; where they all fit they are
+      // loaded once per range
+      bool loaded = false;
+      auto walk = [&](auto&& ent, auto&& fin) {
+        for (int s0 = 0; s0 < nl; s0 += SEGS) {
+          const int nc = nl - s0 < SEGS ? nl - s0 : SEGS;
+          if (!loaded) load_segs<NT, CRED>(A, base, nl, s0, nc, lo, sg, sv);
+          loaded = nl <= SEGS;
+          if (tid == 0) s_next = 0;
+          __syncthreads();
+          seg_walk<GL>(A.ncol, hi, nc, &s_next, sg, ent, fin);
+          __syncthreads();
+        }
+        walks++;
+      };
+      unsigned dup = 0, valid = 0;
+      walk(
+          [&](const int32_t(&x)[4]) {
+            uint32_t bit[4], old[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+              const bool in = x[k] < hi;
+              bit[k] = in ? 1u << (x[k] & 31) : 0u;
+              valid += in;
+              old[k] = atomicOr(&fa[((uint32_t)x[k] >> 5) & (AW - 1)], bit[k]);
+            }
+            // without a branch: a lane that finds its bit clear sets nothing
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+              const uint32_t d = old[k] & bit[k];
+              dup += d != 0;
+              atomicOr(&fb[((uint32_t)x[k] >> 5) & (BW - 1)], d);
+            }
+          },
+          [](int, bool) {});
+      wedges += valid;
+      dup = (unsigned)lane_group_sum<WAVE>(dup);
+      if (lane == 0 && dup) atomicAdd(&s_dup, dup);
+      __syncthreads();
+      const unsigned long long nd = (unsigned)__builtin_amdgcn_readfirstlane((int)s_dup);
+      // ---- 2. the candidates, in P classes
+      // distinct candidates: an endpoint that found its bit set repeats a key
+      // or shares the bit with another key, and of the endpoints met once some
+      // have their bit of the smaller second bitmap set by others; never more
+      // than the ranks of the range
+      const unsigned long long est = std::min<unsigned long long>(
+          nd + (((unsigned long long)(wb / R) * nd) >> BB), (unsigned long long)(hi - lo));
+      uint32_t P = (uint32_t)std::min<unsigned long long>((est + CAP - 1) / CAP, C4_MAX_CLASSES);
+      if (nd == 0) P = 0;
+      for (uint32_t c = 0; c < P;) {
+        for (int i = tid; i < AW / 4; i += NT) fa4[i] = make_uint4(0, 0, 0, 0);
+        if (tid == 0) s_over = 0;
+        __syncthreads();
+        auto candidate = [&](int32_t x) {
+          const bool c1 = ((fb[((uint32_t)x >> 5) & (BW - 1)] >> (x & 31)) & 1) != 0 && x < hi;
+          if (P == 1) return c1;
+          return c1 && ((((uint32_t)x * 0x85EBCA6Bu) >> 16) * P) >> 16 == c;
+        };
+        // the candidates of a step are gathered in LDS and counted 64 at a
+        // time, one per lane: a fraction of the entries are candidates, and
+        // probing them in place would leave most lanes idle
+        bool over = false;
+        unsigned long long part = 0;
+        int qn = 0;  // uniform in the wavefront
+        int32_t* q = wq[tid / WAVE];
+        auto count_top = [&](int m) {
+          wave_sync();
+          if (lane < m) {
+            unsigned long long old = 0;
+            if (tab.template find<true>(q[qn - m + lane], old)) part += old;
+            else over = true;
+          }
+          qn -= m;
+          wave_sync();
+        };
+        walk(
+            [&](const int32_t(&x)[4]) {
+#pragma unroll
+              for (int k = 0; k < 4; k++) {
+                const bool is = candidate(x[k]);
+                const uint64_t m = __ballot(is);
+                if (is)
+                  q[qn + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] = x[k];
+                qn += __popcll(m);
+                if (qn >= WAVE) count_top(WAVE);
+              }
+            },
+            [](int, bool) {});
+        if (qn > 0) count_top(qn);
+        if (over) s_over = 1;
+        __syncthreads();
+        const int split = s_over;
+        __syncthreads();
+        if (split) {
+          if (P > C4_MAX_CLASSES / 2) {  // not met by any owner the plan sends here
+            if (tid == 0) atomicOr(&A.scal->err, ERR_RANGES);
             break;
           }
+          P *= 2;  // class c is 2c and 2c + 1 of the finer split
+          c *= 2;
+          continue;
         }
-        h = (h + 1) & mask;
-      }
-      if (!ok) {
-        atomicOr(&A.scal->err, ERR_PROBE);
-        return;
-      }
-      acc += atomicAdd(&hcnt[h], 1u);
-      wedges++;
-    };
-    if (NT < 1024 || wb <= (int64_t)CAP) {
-      c4_endpoints<NT, UNR>(A, u, nl, base, sst, spref, reads, insert);
-    } else {
-      // histogram of the endpoints over bins of 2^hs ranks (in hcnt)
-      const int32_t span = u - (int32_t)A.r1;
-      int hs = 0;
-      while ((span >> hs) >= SLOTS) hs++;
-      c4_endpoints<NT, UNR>(A, u, nl, base, sst, spref, reads, [&](int32_t x) {
-        atomicAdd(&hcnt[(x - (int32_t)A.r1) >> hs], 1u);
-      });
-      // exclusive prefix of the bins, in place
-      constexpr int PER = SLOTS / NT;
-      uint32_t loc[PER], sum = 0;
+        acc += part;
+        if (CRED) {
+          unsigned long long cr = 0;
+          walk(
+              [&](const int32_t(&x)[4]) {
 #pragma unroll
-      for (int i = 0; i < PER; i++) {
-        loc[i] = hcnt[tid * PER + i];
-        sum += loc[i];
-      }
-      int64_t tot;
-      uint32_t run = (uint32_t)block_excl_scan64<NT>((int64_t)sum, &tot);
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < PER; i++) {
-        hcnt[tid * PER + i] = run;
-        run += loc[i];
-      }
-      if (tid == 0) s_tot = (uint32_t)tot;
-      __syncthreads();
-      // greedy ranges: as many bins as fit in CAP endpoints, at least one
-      if (tid == 0) {
-        auto pre = [&](int b) { return b >= SLOTS ? s_tot : hcnt[b]; };
-        int nr = 0, lo = 0;
-        s_rng[0] = (int32_t)A.r1;
-        while (lo < SLOTS && nr < C4_MED_RANGES) {
-          const uint32_t p0 = pre(lo);
-          int l = lo + 1, h = SLOTS;  // largest b in [lo + 1, SLOTS] with pre(b) - p0 <= CAP
-          if (pre(l) - p0 > CAP) {
-            h = l;
-          } else {
-            while (l < h) {
-              const int mid = (l + h + 1) >> 1;
-              if (pre(mid) - p0 <= CAP) l = mid;
-              else h = mid - 1;
+                for (int k = 0; k < 4; k++)
+                  if (candidate(x[k])) {
+                    unsigned long long n = 1;
+                    (void)tab.template find<false>(x[k], n);
+                    cr += n - 1;
+                  }
+              },
+              [&](int i, bool last) {
+                if (!__ballot(last)) return;
+                const unsigned long long t = lane_group_sum<GL>(cr);
+                if (last) {
+                  if ((lane & (GL - 1)) == 0 && t) atomicAdd(&A.n8[sv[i]], t);
+                  cr = 0;
+                }
+              });
+          for (int i = tid; i < Table::N; i += NT) {
+            const typename Table::Slot w = tab.t[i];
+            const unsigned long long k = tab.count_of(w);
+            if (k >= 2) {
+              own += pairs_of(k);
+              atomicAdd(&A.n8[tab.rank_of(i, w)], pairs_of(k));
             }
-            h = l;
-          }
-          nr++;
-          const int64_t rk = (int64_t)A.r1 + ((int64_t)h << hs);
-          s_rng[nr] = h >= SLOTS || rk >= u ? u : (int32_t)rk;
-          lo = h;
-          if (s_rng[nr] >= u) break;
-        }
-        if (s_rng[nr] < u) {  // more ranges than planned for: not counted
-          atomicOr(&A.scal->err, ERR_RANGES);
-          nr = 0;
-        }
-        s_nr = nr;
-      }
-      __syncthreads();
-      for (int i = tid; i < SLOTS; i += NT) hcnt[i] = 0;
-      __syncthreads();
-      const int nr = s_nr;
-      for (int r = 0; r < nr; r++) {
-        const int32_t lo = s_rng[r], hi = s_rng[r + 1];
-        c4_endpoints<NT, UNR>(A, u, nl, base, sst, spref, reads, [&](int32_t x) {
-          if (x >= lo && x < hi) insert(x);
-        });
-        if (r + 1 < nr) {
-          for (int i = tid; i < S; i += NT) {
-            hkey[i] = -1;
-            hcnt[i] = 0;
           }
           __syncthreads();
         }
+        c++;
       }
+      lo = hi;
     }
-    for (int i = tid; i < S; i += NT) {
-      hkey[i] = -1;
-      hcnt[i] = 0;
+    if (CRED) {
+      own = lane_group_sum<WAVE>(own);
+      if (lane == 0 && own) atomicAdd(&A.n8[u], own);
     }
-    __syncthreads();
+    if (DEAL) {
+      item += gridDim.x;
+    } else {
+      __syncthreads();  // every thread has read the last s_item
+      if (tid == 0) s_item = (int)(gridDim.x + ahead);
+      __syncthreads();
+      item = __builtin_amdgcn_readfirstlane(s_item);
+    }
   }
-  block_add_u128<NT>(&A.scal->acc[ACC_C4], acc);
+  block_add_acc<NT>(A.scal, ACC_C4, acc);
   if (A.flags & M4_STATS) {
+    const unsigned long long b0v = tid == 0 ? 1 : 0;
     block_add_u64<NT>(&A.scal->stat[ST_WEDGES], wedges);
     block_add_u64<NT>(&A.scal->kstat[A.slot][0], wedges);
-    block_add_u64<NT>(&A.scal->kstat[A.slot][1], owners);
-    block_add_u64<NT>(&A.scal->kstat[A.slot][2], segs);
-    block_add_u64<NT>(&A.scal->kstat[A.slot][3], reads);
+    block_add_u64<NT>(&A.scal->kstat[A.slot][1], owners * b0v);
+    block_add_u64<NT>(&A.scal->kstat[A.slot][2], segs * b0v);
+    block_add_u64<NT>(&A.scal->kstat[A.slot][3], walks * b0v);
   }
 }
 
 // -------------------------------------------------------- window bucket
-// Segment descriptors of the window and binned owners: for lower neighbour v
-// of owner u the cursor into row v (first entry >= r1), the segment's end
-// (for a binned owner the position of u in row v: entries from there on are
-// not below u; for a window owner the row's end), and the values at the
-// cursor and 7 entries after it.  Only non-empty segments are
-// kept (a lower neighbour of degree 1, say, has none), packed from the
-// owner's first slot; seg_cnt[h] is their number and seg_pre (binned owners
-// only) the exclusive prefix of their lengths.  One block per owner.
+// Segment descriptors of the window owners: for lower neighbour v of owner u
+// the cursor into row v (first entry >= r1), the row's end, and the values at
+// the cursor and 7 entries after it.  Only non-empty segments are kept (a
+// lower neighbour of degree 1, say, has none), packed from the owner's first
+// slot; seg_cnt[h] is their number.  One block per owner.
 __global__ __launch_bounds__(256) void k_c4_desc(const int32_t* __restrict__ order,
                                                  const int64_t* __restrict__ start,
                                                  const int64_t* __restrict__ seg_off,
@@ -435,48 +782,33 @@ __global__ __launch_bounds__(256) void k_c4_desc(const int32_t* __restrict__ ord
                                                  const int4* __restrict__ vmeta,
                                                  const int32_t* __restrict__ row_len, int64_t r1,
                                                  int4* __restrict__ desc,
-                                                 int64_t* __restrict__ seg_pre,
                                                  int32_t* __restrict__ seg_cnt) {
   const int64_t h = blockIdx.x;
   const int32_t u = order[start[CB_WIN] + h];
   const int64_t so = seg_off[h], base = nptr[u];
   const int nl = dlo[u];
-  // binned owners walk positions and need each segment's exact end (u's
-  // place in the row); the window kernel stops at u by value, so its
-  // segments may run to the row's end
-  const bool exact = h >= start[CB_BIN] - start[CB_WIN];
-  int64_t run = 0, kept = 0;
+  int64_t kept = 0;
   for (int i0 = 0; i0 < nl; i0 += 256) {
     const int i = i0 + (int)threadIdx.x;
-    int64_t len = 0, c = 0, e = 0;
+    int64_t c = 0, e = 0;
     if (i < nl) {
       const int32_t v = ncol[base + i];
       if (vmeta) {
-        // full rows: one 16-byte record per vertex
         const int4 m = vmeta[v];
-        const int64_t rs = m.x;
-        // u is an out-neighbour of v: search the out-part of row v
-        e = exact ? lower_index(ncol, rs + m.z, rs + m.y, u) : rs + m.y;
-        c = rs + m.w;
+        e = m.x + m.y;
+        c = m.x + m.w;
       } else {
         const int64_t rs = nptr[v];
-        const int64_t rend = row_len ? rs + row_len[v] : nptr[v + 1];
-        e = exact ? lower_index(ncol, rs + dlo[v], rend, u) : rend;
+        e = row_len ? rs + row_len[v] : nptr[v + 1];
         // first entry >= r1, searched in the stored prefix
         c = lower_index(ncol, rs, e, (int32_t)r1);
       }
-      if (c > e) c = e;
-      len = e - c;
     }
-    int64_t tot, ktot;
-    const int64_t ex = block_excl_scan64<256>(len, &tot);
-    const int64_t kx = block_excl_scan64<256>(len > 0 ? 1 : 0, &ktot);
-    if (len > 0) {
-      const int64_t at = so + kept + kx;
-      desc[at] = make_int4((int)c, (int)e, ncol[c], c + 7 < e ? ncol[c + 7] : INT_MAX);
-      if (seg_pre) seg_pre[at] = run + ex;
-    }
-    run += tot;
+    int64_t ktot;
+    const int64_t kx = block_excl_scan64<256>(c < e ? 1 : 0, &ktot);
+    if (c < e)
+      desc[so + kept + kx] =
+          make_int4((int)c, (int)e, ncol[c], c + 7 < e ? ncol[c + 7] : INT_MAX);
     kept += ktot;
   }
   if (threadIdx.x == 0) seg_cnt[h] = (int32_t)kept;
@@ -497,7 +829,7 @@ __global__ void k_vmeta(const int64_t* __restrict__ nptr, const int32_t* __restr
 __global__ void k_c4_heavy_len(const int32_t* __restrict__ order, const int64_t* __restrict__ start,
                                const int32_t* __restrict__ dlo, int32_t* __restrict__ len) {
   const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t b = start[CB_WIN], H = start[CB_BIN + 1] - b;
+  const int64_t b = start[CB_WIN], H = start[CB_WIN + 1] - b;
   if (h < H) len[h] = dlo[order[b + h]];
 }
 
@@ -848,7 +1180,7 @@ __global__ __launch_bounds__(W_NT) void k_c4_window(C4Args A) {
       wlo = minz >= u ? uwords : zone_word(A, minz);
     }
   }
-  block_add_u128<W_NT>(&A.scal->acc[ACC_C4], acc);
+  block_add_acc<W_NT>(A.scal, ACC_C4, acc);
   if (A.flags & M4_STATS) {
     block_add_u64<W_NT>(&A.scal->stat[ST_WEDGES], wedges);
     block_add_u64<W_NT>(&A.scal->kstat[A.slot][0], wedges);
@@ -858,647 +1190,14 @@ __global__ __launch_bounds__(W_NT) void k_c4_window(C4Args A) {
   }
 }
 
-// ----------------------------------------------------------- binned bucket
-// One owner at a time per 512-thread workgroup (two per CU), heaviest first.
-// Its wedge endpoints are the concatenation of its non-empty segments (rows
-// of the lower neighbours from the first rank >= r1 up to u).  The counter
-// words of the ranks [r1, u) are cut into fine buckets of BF_WORDS words.
-//   pass 1: each wave walks a contiguous share of the concatenation, 64
-//           endpoints a step and BF_UNROLL steps in flight, and counts the
-//           endpoints per bucket in LDS (one atomic per run of lanes with
-//           the same segment and bucket); a block prefix turns the counts
-//           into bucket starts;
-//   pass 2: the same walk scatters the endpoints into their buckets in the
-//           block's device scratch (one cursor atomic per run);
-//   pass 3: waves take groups of consecutive buckets, a group being the
-//           buckets that start within one stretch of BF_GROUP positions of
-//           the scatter, and count each in a private 8 KiB LDS region: the
-//           group's small buckets in an open-addressing table of (rank,
-//           count) pairs, a bucket above BF_GROUP endpoints alone in dense
-//           zoned counters (it spans BF_WORDS words); every increment adds
-//           the counter's old value.  Dense buckets above BF_BIG endpoints
-//           are counted afterwards by the whole block.
-// No barrier is taken per bucket.  The scratch holds `cap` endpoints: an
-// owner with more is scattered in consecutive bucket ranges that fit, one
-// pass 2 and 3 per range; a single bucket above `cap` is counted straight
-// from the rows by a walk that keeps only its endpoints.
-constexpr int BN_NT = 512, BN_NW = BN_NT / WAVE;
-constexpr int BF_SHIFT = 11, BF_WORDS = 1 << BF_SHIFT;  // 8 KiB of counters per wave
-constexpr int BF_KMAX = 3968;    // fine buckets per owner (two workgroups' LDS per CU)
-constexpr int BF_GROUP = 192;    // scatter positions per group
-constexpr int BF_HBITS = BF_SHIFT - 1, BF_HSLOTS = 1 << BF_HBITS;  // 64-bit slots
-constexpr int BF_BIG = 4096;     // dense buckets above this: the whole block
-constexpr int BF_BIGLIST = 48;
-constexpr int BF_SB = 16;        // staging buffer entries per target (four 16-byte stores)
-constexpr int BF_NTS = 620;      // targets with a staging buffer (20 words each)
-constexpr int BF_PAD = 16;       // targets start at multiples of this many entries
-static_assert((int64_t)C4_BIN_KMAX * C4_WIN_WORDS <= (int64_t)BF_KMAX * BF_WORDS,
-              "a binned owner's fine buckets must fit the LDS histogram");
-static_assert(2 * BF_GROUP <= BF_HSLOTS / 2, "a hash group must keep its table half empty");
-static_assert(BF_KMAX + (4 + BF_SB) * BF_NTS <= BN_NW * BF_WORDS && (BF_KMAX + 4 * BF_NTS) % 4 == 0,
-              "scatter cursors and staging buffers fit the counter regions, the buffers 16-byte aligned");
-
-__device__ __forceinline__ int32_t fbin_of(const C4Args& A, int32_t x) {
-  return zone_word(A, x) >> BF_SHIFT;
-}
-
-// a wave-uniform value held in scalar registers (LDS and vector loads
-// return it in vector registers)
-__device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int64_t uni64(int64_t v) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-__device__ __forceinline__ int64_t readlane64(int64_t v, int l) {
-  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, l);
-  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// Per-wave view of 64 consecutive segments from sbase: lane j holds the
-// concatenated start of segment sbase + 1 + j (far beyond the end past the
-// last segment) and, for segment sbase + j, its row index minus its
-// concatenated start (so an endpoint at position q of that segment sits at
-// ncol[q + delta]; both are below 2^31).
-struct SegView {
-  int sbase;
-  int64_t B;
-  int32_t delta;
-};
-constexpr int64_t SEG_FAR = int64_t(1) << 62;
-constexpr int WALK_PER = 4;                     // positions per lane and step
-constexpr int WALK_STEP = WAVE * WALK_PER;      // positions per wave and step
-
-__device__ __forceinline__ void seg_view_load(const int4* __restrict__ D,
-                                              const int64_t* __restrict__ pre, int nl, int sbase,
-                                              SegView& v) {
-  const int j = sbase + (int)(threadIdx.x & (WAVE - 1));
-  v.sbase = sbase;
-  v.B = j + 1 < nl ? pre[j + 1] : SEG_FAR;
-  v.delta = j < nl ? (int32_t)((int64_t)D[j].x - pre[j]) : 0;
-}
-
-// Walks the endpoints [q_lo, q_hi) of one owner on one wave (s_lo: the
-// segment holding q_lo); emit(x, valid) sees every position once.  A step
-// gives each lane WALK_PER consecutive positions; the segment of each is the
-// view's boundaries at or below it, counted over the few boundaries inside
-// the step.  Where 64 segments end within a step (very short segments) the
-// step falls back to one position per lane.
-template <int WALK_UNROLL = 2, class F>
-__device__ __forceinline__ void bin_walk(const int32_t* __restrict__ ncol,
-                                         const int4* __restrict__ D,
-                                         const int64_t* __restrict__ pre, int nl, int64_t q_lo,
-                                         int64_t q_hi, int s_lo, F&& emit) {
-  const int lane = threadIdx.x & (WAVE - 1);
-  if (q_lo >= q_hi) return;
-  SegView v;
-  seg_view_load(D, pre, nl, s_lo, v);
-  int64_t q0 = q_lo;
-  while (q0 < q_hi) {
-    int64_t b63 = readlane64(v.B, WAVE - 1);
-    if (b63 <= q0 + WALK_STEP - 1) {
-      // the view may miss boundaries of this step: move it to the segment
-      // holding q0
-      seg_view_load(D, pre, nl, v.sbase + __popcll(__ballot(v.B <= q0)), v);
-      b63 = readlane64(v.B, WAVE - 1);
-    }
-    if (b63 > q0 + WALK_STEP * WALK_UNROLL - 1) {
-      // WALK_UNROLL steps of WALK_PER positions per lane, loads in flight together
-      int32_t xs[WALK_UNROLL][WALK_PER];
-      const int base_rel = __popcll(__ballot(v.B <= q0));
-      uint64_t inside = __ballot(v.B > q0 && v.B <= q0 + WALK_STEP * WALK_UNROLL - 1);
-      int rel[WALK_UNROLL][WALK_PER];
-#pragma unroll
-      for (int u = 0; u < WALK_UNROLL; u++)
-#pragma unroll
-        for (int k = 0; k < WALK_PER; k++) rel[u][k] = base_rel;
-      while (inside) {
-        const int j = __ffsll((long long)inside) - 1;
-        inside &= inside - 1;
-        const int64_t bj = readlane64(v.B, j);
-#pragma unroll
-        for (int u = 0; u < WALK_UNROLL; u++)
-#pragma unroll
-          for (int k = 0; k < WALK_PER; k++)
-            rel[u][k] += q0 + u * WALK_STEP + lane * WALK_PER + k >= bj ? 1 : 0;
-      }
-#pragma unroll
-      for (int u = 0; u < WALK_UNROLL; u++)
-#pragma unroll
-        for (int k = 0; k < WALK_PER; k++) {
-          const int64_t p = q0 + u * WALK_STEP + lane * WALK_PER + k;
-          const int32_t d = __shfl(v.delta, rel[u][k], WAVE);
-          xs[u][k] = p < q_hi ? ncol[p + d] : INT_MAX;
-        }
-#pragma unroll
-      for (int u = 0; u < WALK_UNROLL; u++)
-#pragma unroll
-        for (int k = 0; k < WALK_PER; k++)
-          emit(xs[u][k], q0 + u * WALK_STEP + lane * WALK_PER + k < q_hi);
-      q0 += WALK_STEP * WALK_UNROLL;
-    } else if (b63 > q0 + WALK_STEP - 1) {
-      int32_t xs[WALK_PER];
-      int rel[WALK_PER];
-      const int base_rel = __popcll(__ballot(v.B <= q0));
-      uint64_t inside = __ballot(v.B > q0 && v.B <= q0 + WALK_STEP - 1);
-#pragma unroll
-      for (int k = 0; k < WALK_PER; k++) rel[k] = base_rel;
-      while (inside) {
-        const int j = __ffsll((long long)inside) - 1;
-        inside &= inside - 1;
-        const int64_t bj = readlane64(v.B, j);
-#pragma unroll
-        for (int k = 0; k < WALK_PER; k++) rel[k] += q0 + lane * WALK_PER + k >= bj ? 1 : 0;
-      }
-#pragma unroll
-      for (int k = 0; k < WALK_PER; k++) {
-        const int64_t p = q0 + lane * WALK_PER + k;
-        const int32_t d = __shfl(v.delta, rel[k], WAVE);
-        xs[k] = p < q_hi ? ncol[p + d] : INT_MAX;
-      }
-#pragma unroll
-      for (int k = 0; k < WALK_PER; k++) emit(xs[k], q0 + lane * WALK_PER + k < q_hi);
-      q0 += WALK_STEP;
-    } else {
-      // one position per lane: after the move above at most 63 boundaries
-      // lie in (q0, q0 + 63], all in the view
-      int rel = __popcll(__ballot(v.B <= q0));
-      uint64_t inside = __ballot(v.B > q0 && v.B <= q0 + WAVE - 1);
-      while (inside) {
-        const int j = __ffsll((long long)inside) - 1;
-        inside &= inside - 1;
-        rel += q0 + lane >= readlane64(v.B, j) ? 1 : 0;
-      }
-      const int32_t d = __shfl(v.delta, rel, WAVE);
-      const bool valid = q0 + lane < q_hi;
-      emit(valid ? ncol[q0 + lane + d] : INT_MAX, valid);
-      q0 += WAVE;
-    }
-  }
-}
-
-// First b in [lo, hi] with key(b) >= target (key non-decreasing), hi + 1 if
-// none; hi - lo < 4096.  Two probes per lane.
-template <class KeyF>
-__device__ __forceinline__ int wave_first_ge(int lo, int hi, int64_t target, KeyF&& key) {
-  const int lane = threadIdx.x & (WAVE - 1);
-  int pb = lo + lane * WAVE + WAVE - 1;
-  if (pb > hi) pb = hi;
-  const uint64_t m1 = __ballot(lo + lane * WAVE <= hi && key(pb) >= target);
-  if (!m1) return hi + 1;
-  const int c = __ffsll((long long)m1) - 1;
-  const int b = lo + c * WAVE + lane;
-  const uint64_t m2 = __ballot(b <= hi && key(b) >= target);
-  return lo + c * WAVE + __ffsll((long long)m2) - 1;
-}
-
-// hash slot of rank x in a table of BF_HSLOTS (rank + 1, count) pairs
-__device__ __forceinline__ uint32_t bin_hash_inc(uint64_t* tab, int32_t x, int* err) {
-  const uint64_t key = (uint64_t)(uint32_t)(x + 1) << 32;
-  uint32_t h = ((uint32_t)x * 0x9E3779B1u) >> (32 - BF_HBITS);
-  for (int p = 0; p < BF_HSLOTS; p++) {
-    uint64_t cur = tab[h];
-    if (cur == 0) {
-      const uint64_t o = atomicCAS(reinterpret_cast<unsigned long long*>(&tab[h]), 0ull,
-                                   (unsigned long long)(key | 1u));
-      if (o == 0) return 0;
-      cur = o;
-    }
-    if ((cur & 0xffffffff00000000ull) == key)
-      return (uint32_t)atomicAdd(reinterpret_cast<unsigned long long*>(&tab[h]), 1ull);
-    h = (h + 1) & (BF_HSLOTS - 1);
-  }
-  atomicOr(err, ERR_PROBE);
-  return 0;
-}
-
-// The same for up to N endpoints of one lane (x < 0: none): the home slots
-// are read for all of them first, then the empty ones claimed and the
-// matching ones incremented, each step issued for all N before any result is
-// used; a lost claim or an occupied home slot probes on.
-template <int N>
-__device__ __forceinline__ uint64_t bin_hash_batch(uint64_t* tab, const int32_t (&x)[N], int* err) {
-  auto home = [](int32_t v) { return ((uint32_t)v * 0x9E3779B1u) >> (32 - BF_HBITS); };
-  auto key = [](int32_t v) { return (uint64_t)(uint32_t)(v + 1) << 32; };
-  uint64_t o[N];
-#pragma unroll
-  for (int k = 0; k < N; k++) o[k] = x[k] >= 0 ? tab[home(x[k])] : 1;  // 1: no endpoint
-  uint32_t won = 0;
-#pragma unroll
-  for (int k = 0; k < N; k++)
-    if (x[k] >= 0 && o[k] == 0) {
-      o[k] = atomicCAS(reinterpret_cast<unsigned long long*>(&tab[home(x[k])]), 0ull,
-                       (unsigned long long)(key(x[k]) | 1u));
-      if (o[k] == 0) won |= 1u << k;
-    }
-  uint64_t sum = 0;
-  uint32_t rest = 0;
-#pragma unroll
-  for (int k = 0; k < N; k++) {
-    if (x[k] < 0 || ((won >> k) & 1)) continue;
-    if ((o[k] & 0xffffffff00000000ull) == key(x[k]))
-      sum += (uint32_t)atomicAdd(reinterpret_cast<unsigned long long*>(&tab[home(x[k])]), 1ull);
-    else
-      rest |= 1u << k;
-  }
-#pragma unroll
-  for (int k = 0; k < N; k++)
-    if ((rest >> k) & 1) sum += bin_hash_inc(tab, x[k], err);
-  return sum;
-}
-
-__device__ __forceinline__ void region_clear(uint32_t* r) {
-  const int lane = threadIdx.x & (WAVE - 1);
-  uint4* r4 = reinterpret_cast<uint4*>(r);
-#pragma unroll
-  for (int k = lane; k < BF_WORDS / 4; k += WAVE) r4[k] = make_uint4(0, 0, 0, 0);
-}
-
-__global__ __launch_bounds__(BN_NT, 4) void k_c4_bin(C4Args A) {
-  __shared__ uint4 cnt4[BN_NW * BF_WORDS / 4];
-  __shared__ int32_t off[BF_KMAX + 1];
-  __shared__ int16_t bigl[BF_BIGLIST];
-  __shared__ int s_item, s_nbig, s_b1, s_next, s_nt;
-  uint32_t* cnt = reinterpret_cast<uint32_t*>(cnt4);
-  const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid / WAVE;
-  const int64_t b0i = A.start[A.bucket], cnt_items = A.start[A.bucket + 1] - b0i;
-  const int64_t hbase = b0i - A.start[CB_WIN];
-  // per block: the scratch plus up to 7 padding entries per target
-  int32_t* bins = A.bins + (int64_t)blockIdx.x * (A.bin_cap + BF_PAD * BF_KMAX);
-  uint32_t* mycnt = cnt + wid * BF_WORDS;
-  u128_t acc = 0;
-  // counters kept equal across a wave (scalar registers); lane 0 of each
-  // wave contributes its wave's, the block-wide ones counted by wave 0
-  unsigned long long wedges = 0, owners = 0, segs = 0, reads = 0;
-  region_clear(mycnt);
-  for (;;) {
-    if (tid == 0) s_item = (int)atomicAdd(A.work, 1u);
-    __syncthreads();
-    const int64_t item = uni(s_item);
-    if (item >= cnt_items) break;
-    const int64_t pos = cnt_items - 1 - item;  // heaviest owners (highest ranks) first
-    const int32_t u = uni(A.order[b0i + pos]);
-    const int64_t so = uni64(A.seg_off[hbase + pos]);
-    const int nl = uni(A.seg_cnt[hbase + pos]);
-    const int4* D = A.desc + so;
-    const int64_t* pre = A.seg_pre + so;
-    const int64_t total = uni64(nl > 0 ? pre[nl - 1] + (D[nl - 1].y - D[nl - 1].x) : 0);
-    const int32_t uwords = zone_words(A, u);
-    const int K = (uwords + BF_WORDS - 1) >> BF_SHIFT;
-    for (int i = tid; i <= K; i += BN_NT) off[i] = 0;
-    // each wave's contiguous share of the endpoints, in whole steps, and the
-    // segment holding its first endpoint
-    constexpr int SHARE = WALK_STEP * 2;
-    const int64_t steps = (total + SHARE - 1) / SHARE;
-    const int64_t q_lo = std::min(total, (steps * wid / BN_NW) * SHARE);
-    const int64_t q_hi = std::min(total, (steps * (wid + 1) / BN_NW) * SHARE);
-    int s_lo = 0;
-    if (q_lo < q_hi) {
-      // last segment with start <= q_lo: 64-ary search over the starts
-      int lo = 0, hi = nl - 1;
-      while (hi - lo >= WAVE) {
-        const int64_t stride = (hi - lo + WAVE) / WAVE;
-        const int64_t p = lo + stride * lane;
-        const uint64_t m = __ballot(p <= hi && pre[p] <= q_lo);
-        const int c = 63 - __clzll((long long)m);  // lane 0 (p = lo) always qualifies
-        const int nlo = (int)(lo + stride * c);
-        hi = (int)std::min<int64_t>(hi, nlo + stride - 1);
-        lo = nlo;
-      }
-      const uint64_t m = __ballot(lo + lane <= hi && pre[lo + lane] <= q_lo);
-      s_lo = lo + 63 - __clzll((long long)m);
-    }
-    owners++;
-    segs += (unsigned long long)nl;
-    __syncthreads();
-    // ---- pass 1: endpoints per bucket
-    bin_walk(A.ncol, D, pre, nl, q_lo, q_hi, s_lo, [&](int32_t x, bool valid) {
-      if (valid) atomicAdd(&off[fbin_of(A, x)], 1);
-    });
-    reads += (unsigned long long)total;
-    __syncthreads();
-    // exclusive prefix: off[b] = first scatter position of bucket b
-    {
-      constexpr int PER = (BF_KMAX + 1 + BN_NT - 1) / BN_NT;
-      int32_t v[PER];
-      int64_t sum = 0;
-#pragma unroll
-      for (int k = 0; k < PER; k++) {
-        const int b = tid * PER + k;
-        v[k] = b < K ? off[b] : 0;
-        sum += v[k];
-      }
-      int64_t tot;
-      int64_t run = block_excl_scan64<BN_NT>(sum, &tot);
-#pragma unroll
-      for (int k = 0; k < PER; k++) {
-        const int b = tid * PER + k;
-        if (b <= K) off[b] = (int32_t)run;
-        run += v[k];
-      }
-    }
-    __syncthreads();
-    int b0 = 0;
-    while (b0 < K) {
-      // ---- the next bucket range whose endpoints fit the scratch
-      const int64_t p0 = uni(off[b0]);
-      if (wid == 0) {
-        const int f = wave_first_ge(b0 + 1, K, p0 + A.bin_cap + 1,
-                                    [&](int b) { return (int64_t)off[b]; });
-        if (lane == 0) {
-          s_b1 = f - 1;
-          s_nbig = 0;
-        }
-      }
-      __syncthreads();
-      const int b1 = uni(s_b1);
-      const int64_t off_end = uni(off[b1]);  // first position past the range
-      if (b1 == b0) {
-        // one bucket alone beyond the scratch: counted straight from the rows
-        const int32_t wlo = b0 << BF_SHIFT;
-        uint64_t part = 0;
-        bin_walk(A.ncol, D, pre, nl, q_lo, q_hi, s_lo, [&](int32_t x, bool valid) {
-          if (valid && fbin_of(A, x) == b0) part += window_inc(A, cnt, wlo, x);
-        });
-        acc += part;
-        if (wid == 0) wedges += (unsigned long long)(off[b0 + 1] - off[b0]);
-        reads += (unsigned long long)total;
-        __syncthreads();
-        for (int i = tid; i < BF_WORDS; i += BN_NT) cnt[i] = 0;
-        if (tid == 0) off[b0] = off[b0 + 1];  // the end of bucket b0
-        __syncthreads();
-        b0++;
-        continue;
-      }
-      // ---- targets: runs of consecutive buckets that start within one
-      // stretch of BF_GROUP positions (hash targets), a bucket holding more
-      // than BF_GROUP endpoints alone (a dense target; it always ends its
-      // stretch).  Each bucket's target goes to off; the scatter state sits in
-      // the counter regions, unused until pass 3: per target its write
-      // cursor (bit 31: dense), and for the last BF_NTS targets a BF_SB-entry
-      // staging buffer (its fill and completion counts, and a tail cursor for
-      // endpoints that arrive while it is full).  Targets start at multiples
-      // of 8 scratch entries, so a full buffer leaves as aligned 16-byte
-      // stores instead of BF_SB scattered ones.
-      uint32_t* head = cnt;
-      uint32_t* tail = cnt + BF_KMAX;
-      uint32_t* tend = tail + BF_NTS;
-      uint32_t* fill = tend + BF_NTS;
-      uint32_t* done = fill + BF_NTS;
-      int32_t* stage = reinterpret_cast<int32_t*>(done + BF_NTS);
-      {
-        constexpr int PER = (BF_KMAX + BN_NT - 1) / BN_NT;
-        uint32_t beg = 0, big = 0;
-        // positions relative to p0 are below the scratch size (< 2^31)
-        for (int k = 0; k < PER; k++) {
-          const int b = b0 + tid * PER + k;
-          if (b < b1) {
-            const uint32_t sr = (uint32_t)(off[b] - p0), er = (uint32_t)(off[b + 1] - p0);
-            const uint32_t pr = b == b0 ? 0u : (uint32_t)(off[b - 1] - p0);
-            if (er - sr > BF_GROUP) big |= 1u << k;
-            if (b == b0 || er - sr > BF_GROUP || sr / BF_GROUP != pr / BF_GROUP) beg |= 1u << k;
-          }
-        }
-        int64_t ntot;
-        int t = (int)block_excl_scan64<BN_NT>(__popc(beg), &ntot) - 1;
-        // every read of a neighbour's entry of off is done (the scan
-        // synchronised); each thread now rewrites only its own entries.
-        // head[t] takes the target's first position for now.
-        for (int k = 0; k < PER; k++) {
-          const int b = b0 + tid * PER + k;
-          if (b < b1) {
-            if ((beg >> k) & 1) {
-              t++;
-              head[t] = (uint32_t)(off[b] - p0) | (((big >> k) & 1u) << 31);
-            }
-            off[b] = t;
-          }
-        }
-        if (tid == 0) s_nt = (int)ntot;
-        __syncthreads();
-        // padded starts: each target's count rounded up to a multiple of BF_PAD
-        const int nt = (int)ntot;
-        const int sb = nt > BF_NTS ? nt - BF_NTS : 0;  // first target with a buffer
-        const uint32_t span = (uint32_t)(off_end - p0);
-        uint32_t st[PER + 1], kinds = 0, psum = 0;
-        for (int k = 0; k <= PER; k++) {
-          const int tt = tid * PER + k;
-          st[k] = tt < nt ? head[tt] : span;
-          if (k < PER && (st[k] >> 31)) kinds |= 1u << k;
-          st[k] &= 0x7fffffffu;
-        }
-        for (int k = 0; k < PER; k++)
-          if (tid * PER + k < nt) psum += (st[k + 1] - st[k] + BF_PAD - 1) & ~(BF_PAD - 1u);
-        uint32_t ps = (uint32_t)block_excl_scan64<BN_NT>(psum, nullptr);
-        for (int k = 0; k < PER; k++) {
-          const int tt = tid * PER + k;
-          if (tt < nt) {
-            const uint32_t c = st[k + 1] - st[k];
-            head[tt] = ps | (((kinds >> k) & 1u) << 31);
-            if (tt >= sb) {
-              tail[tt - sb] = tend[tt - sb] = ps + c;
-              fill[tt - sb] = done[tt - sb] = 0;
-            }
-            ps += (c + BF_PAD - 1) & ~(BF_PAD - 1u);
-          }
-        }
-      }
-      __syncthreads();
-      const int ntargets = uni(s_nt);
-      // the last BF_NTS targets (the highest ranks, whose buckets of 32-bit
-      // counters span the fewest ranks and hold the most endpoints) have
-      // staging buffers
-      const int sbase = ntargets > BF_NTS ? ntargets - BF_NTS : 0;
-      // ---- pass 2: scatter the range's endpoints by target (one step in
-      // flight: its stores, not its loads, bound this pass)
-      bin_walk<1>(A.ncol, D, pre, nl, q_lo, q_hi, s_lo, [&](int32_t x, bool valid) {
-        bool flush = false;
-        int t = 0, sl = 0;
-        if (valid) {
-          const int w = fbin_of(A, x);
-          if (w >= b0 && w < b1) {
-            t = off[w];
-            sl = t - sbase;
-            if (sl >= 0) {
-              const uint32_t slot = atomicAdd(&fill[sl], 1u);
-              if (slot < BF_SB) {
-                stage[sl * BF_SB + slot] = x;
-                flush = atomicAdd(&done[sl], 1u) == BF_SB - 1;
-              } else {
-                bins[atomicSub(&tail[sl], 1u) - 1] = x;
-              }
-            } else {
-              bins[atomicAdd(&head[t], 1u) & 0x7fffffffu] = x;
-            }
-          }
-        }
-        if (flush) {
-          // every slot of the buffer is written: it leaves as aligned
-          // 16-byte stores, two at a time, and only then are the counters
-          // reset (no new entry lands in the buffer before that)
-          const int4* sv = reinterpret_cast<const int4*>(stage + sl * BF_SB);
-          const uint32_t at = atomicAdd(&head[t], (uint32_t)BF_SB) & 0x7fffffffu;
-          int4* dst = reinterpret_cast<int4*>(bins + at);
-#pragma unroll
-          for (int k = 0; k < BF_SB / 4; k += 2) {
-            const int4 v0 = sv[k], v1 = sv[k + 1];
-            dst[k] = v0;
-            dst[k + 1] = v1;
-          }
-          done[sl] = 0;
-          fill[sl] = 0;
-        }
-      });
-      reads += (unsigned long long)total;
-      __syncthreads();
-      // buffers still holding entries, then the target ends (bit 31: dense)
-      // move to off[b0 ..) and the regions are cleared
-      for (int t = sbase + tid; t < ntargets; t += BN_NT) {
-        const uint32_t at = head[t] & 0x7fffffffu;
-        for (uint32_t k = 0; k < done[t - sbase]; k++) bins[at + k] = stage[(t - sbase) * BF_SB + k];
-      }
-      __syncthreads();
-      for (int t = tid; t < ntargets; t += BN_NT)
-        off[b0 + t] = (int32_t)((t >= sbase ? tend[t - sbase] : head[t] & 0x7fffffffu) |
-                                (head[t] & 0x80000000u));
-      __syncthreads();
-      for (int i = tid; i < BN_NW * BF_WORDS / 4; i += BN_NT) cnt4[i] = make_uint4(0, 0, 0, 0);
-      if (tid == 0) {
-        s_next = 0;
-        s_nbig = 0;
-      }
-      __syncthreads();
-      // ---- pass 3: targets taken one at a time by waves; the next one is
-      // taken and its first endpoints loaded before the current is counted
-      uint64_t* tab = reinterpret_cast<uint64_t*>(mycnt);
-      constexpr int HPER = (2 * BF_GROUP + WAVE - 1) / WAVE;  // hash-target endpoints per lane
-      // target t occupies [tbeg(t), its end): ends are exact, starts padded
-      auto tbeg = [&](int t) -> int64_t {
-        return t == 0 ? 0
-                      : (int64_t)((((uint32_t)off[b0 + t - 1] & 0x7fffffffu) + BF_PAD - 1) &
-                                  ~(BF_PAD - 1u));
-      };
-      auto grab = [&]() {
-        int g = 0;
-        if (lane == 0) g = atomicAdd(&s_next, 1);
-        return uni(__shfl(g, 0, WAVE));
-      };
-      struct Tgt {
-        int t;
-        bool dense;
-        int64_t s, e;
-      };
-      auto fetch = [&](int t, Tgt& T, int32_t (&xv)[HPER]) {
-        T.t = t;
-        T.dense = false;
-        T.s = T.e = 0;
-        if (t < ntargets) {
-          const uint32_t ev = (uint32_t)uni(off[b0 + t]);
-          T.s = uni64(tbeg(t));
-          T.e = ev & 0x7fffffffu;
-          T.dense = (ev >> 31) != 0;
-        }
-#pragma unroll
-        for (int k = 0; k < HPER; k++) {
-          const int64_t q = T.s + lane + k * WAVE;
-          xv[k] = q < T.e ? bins[q] : -1;
-        }
-      };
-      Tgt cur, nxt;
-      int32_t xc[HPER], xn[HPER];
-      fetch(grab(), nxt, xn);
-      while (nxt.t < ntargets) {
-        cur = nxt;
-#pragma unroll
-        for (int k = 0; k < HPER; k++) xc[k] = xn[k];
-        fetch(grab(), nxt, xn);
-        const int64_t n_e = cur.e - cur.s;
-        if (n_e == 0) continue;
-        if (!cur.dense) {
-          // a hash target: fewer than 2 * BF_GROUP endpoints, all loaded
-          acc += bin_hash_batch(tab, xc, &A.scal->err);
-          wedges += (unsigned long long)n_e;
-          wave_sync();
-          region_clear(mycnt);
-          wave_sync();
-          continue;
-        }
-        const int l = fbin_of(A, __shfl(xc[0], 0, WAVE));
-        if (n_e > BF_BIG) {
-          if (lane == 0) {
-            const int k = atomicAdd(&s_nbig, 1);
-            if (k < BF_BIGLIST) bigl[k] = (int16_t)cur.t;
-          }
-          continue;
-        }
-        // ---- one dense bucket in this wave's region
-        const int32_t wlo = l << BF_SHIFT;
-        uint64_t part = 0;
-#pragma unroll
-        for (int k = 0; k < HPER; k++)
-          if (xc[k] >= 0) part += window_inc(A, mycnt, wlo, xc[k]);
-        int64_t q = cur.s + HPER * WAVE + lane;
-        for (; q + 3 * WAVE < cur.e; q += 4 * WAVE) {
-          int32_t xv[4];
-#pragma unroll
-          for (int k = 0; k < 4; k++) xv[k] = bins[q + k * WAVE];
-#pragma unroll
-          for (int k = 0; k < 4; k++) part += window_inc(A, mycnt, wlo, xv[k]);
-        }
-        for (; q < cur.e; q += WAVE) part += window_inc(A, mycnt, wlo, bins[q]);
-        acc += part;
-        wedges += (unsigned long long)n_e;
-        wave_sync();
-        region_clear(mycnt);
-        wave_sync();
-      }
-      __syncthreads();
-      // dense targets too large for one wave: the whole block, one region
-      // (listed, or found by a scan of the targets when the list overflowed)
-      const int nbig = uni(s_nbig);
-      auto count_big = [&](int t) {
-        const int64_t bs = tbeg(t), be = off[b0 + t] & 0x7fffffff;
-        const int32_t wlo = fbin_of(A, bins[bs]) << BF_SHIFT;
-        uint64_t part = 0;
-        for (int64_t q = bs + tid; q < be; q += BN_NT) part += window_inc(A, cnt, wlo, bins[q]);
-        acc += part;
-        if (wid == 0) wedges += (unsigned long long)(be - bs);
-        __syncthreads();
-        for (int i = tid; i < BF_WORDS; i += BN_NT) cnt[i] = 0;
-        __syncthreads();
-      };
-      if (nbig <= BF_BIGLIST) {
-        for (int k = 0; k < nbig; k++) count_big(bigl[k]);
-      } else {
-        for (int t = 0; t < ntargets; t++) {
-          const uint32_t ev = (uint32_t)off[b0 + t];
-          if ((ev >> 31) && (int64_t)(ev & 0x7fffffffu) - tbeg(t) > BF_BIG) count_big(t);
-        }
-      }
-      b0 = b1;
-      __syncthreads();
-    }
-  }
-  block_add_u128<BN_NT>(&A.scal->acc[ACC_C4], acc);
-  if (A.flags & M4_STATS) {
-    const unsigned long long wv = lane == 0 ? wedges : 0, b0v = tid == 0 ? 1 : 0;
-    block_add_u64<BN_NT>(&A.scal->stat[ST_WEDGES], wv);
-    block_add_u64<BN_NT>(&A.scal->kstat[A.slot][0], wv);
-    block_add_u64<BN_NT>(&A.scal->kstat[A.slot][1], owners * b0v);
-    block_add_u64<BN_NT>(&A.scal->kstat[A.slot][2], segs * b0v);
-    block_add_u64<BN_NT>(&A.scal->kstat[A.slot][3], reads * b0v);
-  }
-}
-
 inline unsigned blocks_for(int64_t n, int nt) { return (unsigned)ceil_div(n > 0 ? n : 1, nt); }
 
 }  // namespace
 
 Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, uint32_t flags,
                Arena& tmp, hipStream_t s, int num_cu, KTimer* kt,
-               const std::function<char*(size_t)>& big_scratch, bool* binned) {
+               const std::function<char*(size_t)>& big_scratch, bool* binned,
+               unsigned long long* n8) {
   const int64_t n = P.n;
   if (n == 0 || P.m == 0) return [](hipStream_t) {};
   int64_t* wub = tmp.take<int64_t>(n);
@@ -1520,7 +1219,8 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
   int64_t* zbounds = start + C4_START_SLOTS;
   k_zone_bounds<<<1, 64, 0, s>>>(P.dr, n, zbounds);
   C4Plan pl{tu.c4_light_max, tu.c4_med_max, tu.c4_med_win, tu.c4_bin_win, tu.c4_bin_dense,
-            zbounds, C.r1};
+            zbounds, C.r1, c4_count_limit(n, C4_LIGHT_AB - 5), c4_count_limit(n, C4_MED_AB - 5),
+            c4_count_limit(n, C4_BIN_AB - 5), n8 ? 1 : 0};
   // rows by degree: <= 64 with 8 lanes, <= 4096 with a wavefront, longer
   // rows with a workgroup
   const int64_t b64 = C.bound[4], b4096 = C.bound[7];
@@ -1539,21 +1239,15 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
   M4_HIP(hipMemcpyAsync(hstart.data(), start, sizeof(int64_t) * hstart.size(),
                         hipMemcpyDeviceToHost, s));
   M4_HIP(hipStreamSynchronize(s));
-  // counter zones of the window and binned owners
+  // counter zones of the window owners
   const int64_t z1 = std::max<int64_t>(hstart[C4_START_SLOTS], C.r1);
   const int64_t z2 = std::max<int64_t>(hstart[C4_START_SLOTS + 1], z1);
   const int64_t aw = (z1 - C.r1 + 7) >> 3, bw = (z2 - z1 + 3) >> 2;
-  // window and binned owners are adjacent in the bucket order: one set of
-  // segment descriptors serves both
-  const int64_t H = hstart[CB_BIN + 1] - hstart[CB_WIN];
-  const int64_t HB = hstart[CB_BIN + 1] - hstart[CB_BIN];
-  if (binned) *binned = HB > 0;
+  auto owners = [&hstart](int b) { return hstart[b + 1] - hstart[b]; };
+  const int64_t H = owners(CB_WIN);
+  if (binned) *binned = owners(CB_BIN) + owners(CB_WIDE) > 0;
   int4* desc = nullptr;
-  int64_t* seg_pre = nullptr;
   int32_t* seg_cnt = nullptr;
-  int32_t* bins = nullptr;
-  int64_t bin_cap = 0;
-  unsigned bin_grid = 0;
   if (H > 0) {
     k_c4_heavy_len<<<blocks_for(H, 256), 256, 0, s>>>(order, start, P.dlo, hlen);
     scan_i32(hlen, H, seg_off, stmp, s);
@@ -1562,27 +1256,10 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
     M4_HIP(hipStreamSynchronize(s));
     const size_t db = ((size_t)(nseg > 0 ? nseg : 1) * sizeof(int4) + 255) & ~size_t(255);
     const size_t cb = ((size_t)H * 4 + 255) & ~size_t(255);
-    // length prefixes: binned owners only (their slots, after the window owners')
-    const size_t pb = HB > 0 ? ((size_t)(nseg > 0 ? nseg : 1) * 8 + 255) & ~size_t(255) : 0;
-    // binned owners: two workgroups per CU, each with a scratch of at most
-    // 2^20 endpoints by default (no owner has more endpoints than the graph
-    // has CSR entries)
-    size_t bb = 0;
-    if (HB > 0) {
-      const int64_t cap = tu.c4_bin_cap > 0 ? tu.c4_bin_cap : int64_t(1) << 20;
-      bin_cap = (std::min<int64_t>(cap, std::max<int64_t>(P.nnz, 1)) + BF_PAD - 1) &
-                ~int64_t(BF_PAD - 1);
-      bin_grid = (unsigned)std::min<int64_t>(2 * (int64_t)num_cu, HB);
-      bb = (size_t)bin_grid * (size_t)(bin_cap + BF_PAD * BF_KMAX) * 4;
-    }
-    char* scr = big_scratch(db + cb + pb + bb);
+    char* scr = big_scratch(db + cb);
     if (!scr) throw Fail(M4_ENOMEM, "no room for 4-cycle segment descriptors");
     desc = reinterpret_cast<int4*>(scr);
     seg_cnt = reinterpret_cast<int32_t*>(scr + db);
-    if (HB > 0) {
-      seg_pre = reinterpret_cast<int64_t*>(scr + db + cb);
-      bins = reinterpret_cast<int32_t*>(scr + db + cb + pb);
-    }
   }
   if (kt) kt->end(M4_K_C4_PLAN, s);
 
@@ -1600,10 +1277,10 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
   A.flags = flags;
   A.seg_off = seg_off;
   A.desc = desc;
-  A.seg_pre = seg_pre;
   A.seg_cnt = seg_cnt;
-  A.bins = bins;
-  A.bin_cap = bin_cap;
+  A.vmeta = vmeta;
+  A.deg_pre = P.deg_pre ? P.deg_pre : P.nptr;
+  A.n8 = n8;
   A.z1 = (int32_t)z1;
   A.z2 = (int32_t)z2;
   A.aw = (int32_t)aw;
@@ -1611,49 +1288,52 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
   A.zr1 = (int32_t)C.r1;
   // everything below runs on the launch stream, after the plan above
   return [=](hipStream_t ls) mutable {
-    if (H > 0) {
-      if (kt) kt->begin(M4_K_C4_DESC, ls);
-      // with stored prefixes only the partition's rows are valid: no full pass
-      if (!P.row_len)
-        k_vmeta<<<blocks_for(n, 256), 256, 0, ls>>>(P.nptr, P.ncol, P.dr, P.dlo, n, C.r1, vmeta);
-      k_c4_desc<<<(unsigned)H, 256, 0, ls>>>(order, start, seg_off, P.nptr, P.dlo, P.ncol,
-                                             P.row_len ? nullptr : vmeta, P.row_len, C.r1,
-                                             desc, seg_pre, seg_cnt);
-      if (kt) kt->end(M4_K_C4_DESC, ls);
-    }
-    // heavy owners first: one 1024-thread workgroup per CU
-    if (HB > 0) {
-      A.bucket = CB_BIN;
-      A.slot = M4_K_C4_BIN;
-      A.work = &scal->work_c4[CB_BIN];
-      if (kt) kt->begin(M4_K_C4_BIN, ls);
-      k_c4_bin<<<bin_grid, BN_NT, 0, ls>>>(A);
-      if (kt) kt->end(M4_K_C4_BIN, ls);
-    }
-    if (hstart[CB_WIN + 1] > hstart[CB_WIN]) {
-      A.bucket = CB_WIN;
-      A.slot = M4_K_C4_WINDOW;
-      A.work = &scal->work_c4[CB_WIN];
-      if (kt) kt->begin(M4_K_C4_WINDOW, ls);
-      k_c4_window<<<(unsigned)num_cu, W_NT, 0, ls>>>(A);
-      if (kt) kt->end(M4_K_C4_WINDOW, ls);
-    }
-    if (hstart[CB_MED + 1] > hstart[CB_MED]) {
-      A.bucket = CB_MED;
-      A.slot = M4_K_C4_MED;
-      A.work = &scal->work_c4[CB_MED];
-      if (kt) kt->begin(M4_K_C4_MED, ls);
-      k_c4_hash<1024, C4_MED_SLOTS, 4><<<(unsigned)num_cu, 1024, 0, ls>>>(A);
-      if (kt) kt->end(M4_K_C4_MED, ls);
-    }
-    if (hstart[CB_HASH + 1] > hstart[CB_HASH]) {
-      A.bucket = CB_HASH;
-      A.slot = M4_K_C4_HASH;
-      A.work = &scal->work_c4[CB_HASH];
-      if (kt) kt->begin(M4_K_C4_HASH, ls);
-      k_c4_hash<256, C4_HASH_SLOTS, 4><<<(unsigned)(num_cu * 4), 256, 0, ls>>>(A);
-      if (kt) kt->end(M4_K_C4_HASH, ls);
-    }
+    if (hstart[CB_N] == hstart[CB_TINY]) return;  // no owner at all
+    // with stored prefixes only the partition's rows are valid: no full pass
+    if (kt) kt->begin(M4_K_C4_DESC, ls);
+    if (!P.row_len)
+      k_vmeta<<<blocks_for(n, 256), 256, 0, ls>>>(P.nptr, P.ncol, P.dr, P.dlo, n, C.r1, vmeta);
+    if (H > 0)
+      k_c4_desc<<<(unsigned)H, 256, 0, ls>>>(order, start, seg_off, P.nptr, P.dlo, P.ncol, vmeta,
+                                             P.row_len, C.r1, desc, seg_cnt);
+    if (kt) kt->end(M4_K_C4_DESC, ls);
+    auto run = [&](int bucket, int slot, int hb, auto&& kernel, int nt, int64_t most, int grab) {
+      const int64_t cnt = hstart[bucket + 1] - hstart[bucket];
+      if (cnt <= 0) return;
+      A.bucket = bucket;
+      A.slot = slot;
+      A.work = &scal->work_c4[bucket];
+      A.yb = c4_key_bits(n, hb);
+      A.class_cap = bucket == CB_BIN || bucket == CB_WIDE ? tu.c4_bin_cap : 0;
+      A.grab = grab;
+      if (kt) kt->begin(slot, ls);
+      kernel<<<(unsigned)std::min<int64_t>(most, ceil_div(cnt, grab)), nt, 0, ls>>>(A);
+      if (kt) kt->end(slot, ls);
+    };
+    auto filter = [&](int bucket, int slot, int hb, auto&& plain, auto&& cred, int nt,
+                      int per_cu) {
+      run(bucket, slot, hb, n8 ? cred : plain, nt, (int64_t)num_cu * per_cu, 1);
+    };
+    // heavy owners first
+    if (n8)
+      run(CB_WIDE, M4_K_C4_BIN, C4_BIN_AB - 7,
+          k_c4_filter<1024, 16, C4_BIN_AB - 1, C4_BIN_BB, 512, true, true>, 1024, num_cu, 1);
+    filter(CB_BIN, M4_K_C4_BIN, C4_BIN_AB - 5,
+           k_c4_filter<1024, 8, C4_BIN_AB, C4_BIN_BB, 512, false>,
+           k_c4_filter<1024, 8, C4_BIN_AB, C4_BIN_BB, 512, true>, 1024, 1);
+    run(CB_WIN, M4_K_C4_WINDOW, 1, k_c4_window, W_NT, num_cu, 1);
+    filter(CB_MED, M4_K_C4_MED, C4_MED_AB - 5,
+           k_c4_filter<256, 8, C4_MED_AB, C4_MED_BB, 128, false>,
+           k_c4_filter<256, 8, C4_MED_AB, C4_MED_BB, 128, true>, 256, 6);
+    filter(CB_HASH, M4_K_C4_HASH, C4_LIGHT_AB - 5,
+           k_c4_filter<64, 8, C4_LIGHT_AB, C4_LIGHT_BB, 64, false>,
+           k_c4_filter<64, 8, C4_LIGHT_AB, C4_LIGHT_BB, 64, true>, 64, 24);
+    // a wavefront takes up to 16 owners at once where that still fills the
+    // device (32 wavefronts a CU), fewer where it would not
+    const int64_t waves = (int64_t)num_cu * 32;
+    const int64_t tiny = hstart[CB_TINY + 1] - hstart[CB_TINY];
+    run(CB_TINY, M4_K_C4_HASH, 1, n8 ? k_c4_tiny<true> : k_c4_tiny<false>, WAVE, waves,
+        (int)std::max<int64_t>(1, std::min<int64_t>(16, tiny / waves)));
   };
 }
 

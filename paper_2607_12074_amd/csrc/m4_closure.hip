@@ -52,30 +52,37 @@ __global__ __launch_bounds__(CL_NT) void k_closure(const int64_t* __restrict__ n
     }
     St += st;
   }
-  block_add_u128<CL_NT>(&scal->acc[ACC_S], S);
-  block_add_u128<CL_NT>(&scal->acc[ACC_P], P);
-  block_add_u128<CL_NT>(&scal->acc[ACC_D], D);
-  block_add_u128<CL_NT>(&scal->acc[ACC_PAW2], Paw2);
-  block_add_u128<CL_NT>(&scal->acc[ACC_SUMT], St);
+  block_add_acc<CL_NT>(scal, ACC_S, S);
+  block_add_acc<CL_NT>(scal, ACC_P, P);
+  block_add_acc<CL_NT>(scal, ACC_D, D);
+  block_add_acc<CL_NT>(scal, ACC_PAW2, Paw2);
+  block_add_acc<CL_NT>(scal, ACC_SUMT, St);
 }
 
 // status: 0 ok, 3 a count >= 2^64, 7 internal check failed
 __global__ void k_finalize(Scal* scal, int zbasis) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const u128_t K4 = load_u128(&scal->acc[ACC_K4]), D = load_u128(&scal->acc[ACC_D]);
-  u128_t C4 = load_u128(&scal->acc[ACC_C4]);
+  // one accumulator per lane, then the inverse on the first
+  __shared__ U128 tot[ACC_N + 1];
+  if (threadIdx.x <= ACC_N) {
+    const u128_t v = load_acc(scal, threadIdx.x);
+    tot[threadIdx.x] = U128{(unsigned long long)v, (unsigned long long)(v >> 64)};
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  const u128_t K4 = load_u128(&tot[ACC_K4]), D = load_u128(&tot[ACC_D]);
+  u128_t C4 = load_u128(&tot[ACC_C4]);
   int zstatus = 0;
   if (zbasis) {
     // edge-anchor basis: Z = 4 * cycle (each induced 4-cycle is an adjacent
     // pair of A_e x B_e for each of its four edges), and a 4-cycle subgraph
     // is an induced 4-cycle, a diamond (D_ni - 6 K4) or one of the three in
     // a 4-clique
-    const u128_t Z = load_u128(&scal->acc[ACC_Z]);
+    const u128_t Z = load_u128(&tot[ACC_Z]);
     if (Z % 4 != 0 || D < 3 * K4) zstatus = 7;
     else C4 = Z / 4 + D - 3 * K4;
   }
-  const u128_t in[7] = {K4, C4, load_u128(&scal->acc[ACC_S]), load_u128(&scal->acc[ACC_P]), D,
-                        load_u128(&scal->acc[ACC_PAW2]), load_u128(&scal->acc[ACC_SUMT])};
+  const u128_t in[7] = {K4, C4, load_u128(&tot[ACC_S]), load_u128(&tot[ACC_P]), D,
+                        load_u128(&tot[ACC_PAW2]), load_u128(&tot[ACC_SUMT])};
   const int st = finalize_basis(in, scal->out, scal->basis);
   scal->status = zstatus ? zstatus : st;
 }

@@ -42,6 +42,20 @@ __device__ __forceinline__ void block_add_u128(U128* dst, u128_t v) {
   __syncthreads();
 }
 
+// The same into the block's stripe of accumulator `which`.
+template <int NT>
+__device__ __forceinline__ void block_add_acc(Scal* scal, int which, u128_t v) {
+  block_add_u128<NT>(&scal->acc[blockIdx.x & (ACC_STRIPES - 1)][which], v);
+}
+
+// Sum of the stripes of accumulator `which`.
+__device__ __forceinline__ u128_t load_acc(const Scal* scal, int which) {
+  u128_t s = 0;
+#pragma unroll 8
+  for (int i = 0; i < ACC_STRIPES; i++) s += load_u128(&scal->acc[i][which]);
+  return s;
+}
+
 template <int NT>
 __device__ __forceinline__ void block_add_u64(unsigned long long* dst, unsigned long long v) {
   __shared__ unsigned long long red;

@@ -115,7 +115,7 @@ __global__ __launch_bounds__(256) void k_edge_pairs(const int64_t* __restrict__ 
       }
     }
   }
-  block_add_u128<256>(&scal->acc[ACC_Z], z);
+  block_add_acc<256>(scal, ACC_Z, z);
   if (flags & M4_STATS) {
     block_add_u64<256>(&scal->kstat[M4_K_EDGE][0], scanned);
     block_add_u64<256>(&scal->kstat[M4_K_EDGE][1], owners);

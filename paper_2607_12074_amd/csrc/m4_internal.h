@@ -5,6 +5,7 @@
 // its row holding the neighbours of higher rank.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <functional>
@@ -35,7 +36,7 @@ enum Stat { ST_STEPS = 0, ST_WEDGES, ST_LOOKUPS, ST_HITS, ST_COST, ST_N = 8 };
 // Triangle-owner buckets by out-degree k = d+(u).
 enum TriBucket { TB_NONE = 0, TB_WAVE, TB_LDS, TB_GLOBAL, TB_N = 4 };
 // 4-cycle-owner buckets by wedge bound.
-enum C4Bucket { CB_NONE = 0, CB_HASH, CB_MED, CB_WIN, CB_BIN, CB_N = 5 };
+enum C4Bucket { CB_NONE = 0, CB_TINY, CB_HASH, CB_MED, CB_WIN, CB_BIN, CB_WIDE, CB_N = 7 };
 // radix digits of the 4-cycle bucket keys and slots of their bucket starts
 constexpr int C4_KEY_BITS = 4;
 constexpr int C4_START_SLOTS = (1 << C4_KEY_BITS) + 1;
@@ -44,8 +45,9 @@ constexpr int C4_START_SLOTS = (1 << C4_KEY_BITS) + 1;
 constexpr int TRI_LDS_MAX = 1024;
 // 4-cycle window: 32768 words (128 KiB of LDS) of zoned counters.
 constexpr int C4_WIN_WORDS = 32768;
-constexpr int C4_HASH_SLOTS = 4096;   // light owners: 256 threads, load <= 1/2
-constexpr int C4_MED_SLOTS = 16384;   // medium owners: 1024 threads, load <= 3/4
+constexpr int C4_TINY_MAX = 256;      // tiny owners: one wavefront, a table of twice the bound
+constexpr int C4_HASH_SLOTS = 4096;   // twice the largest wedge bound of the light bucket
+constexpr int C4_MED_SLOTS = 16384;   // 4/3 of the largest bound of the medium bucket's first rule
 constexpr int C4_MED_MAX = 65536;     // largest wedge bound of the medium bucket
 // Entries of slack after the last row of a rank-space CSR, so that 16-byte
 // vector loads aligned below a cursor may run past the end of the array.
@@ -56,8 +58,13 @@ constexpr int ERR_INVALID = 1;  // malformed CSR (M4_VALIDATE)
 constexpr int ERR_RANGES = 2;   // ranged 4-cycle plan exceeded its bound
 constexpr int ERR_PROBE = 4;    // an open-addressing probe ran past its table size
 
+// Stripes of the accumulators: atomics on one address complete one after the
+// other (about 14 ns each on the MI355X, whatever adds them), so each
+// workgroup adds into the 128-byte stripe its index picks, and the stripes
+// are summed at the end.
+constexpr int ACC_STRIPES = 32;
+
 struct Scal {
-  U128 acc[ACC_N + 1];
   unsigned long long stat[ST_N];
   unsigned int dmax;
   int err;
@@ -72,7 +79,9 @@ struct Scal {
   unsigned long long kstat[M4_NK][4];  // per kernel slot: elems, rows, aux, aux2
   int status;
   int pad;
+  alignas(128) U128 acc[ACC_STRIPES][ACC_N + 1];  // not read back to the host
 };
+constexpr size_t kScalHead = offsetof(Scal, acc);
 
 struct Prep {
   int64_t n = 0, nnz = 0, m = 0;
@@ -89,6 +98,7 @@ struct Prep {
   // may be stored as a prefix of row_len[v] entries (null: full rows).
   int64_t own_lo = 0, own_hi = -1;
   const int32_t* row_len = nullptr;
+  const int64_t* deg_pre = nullptr;  // prefix sums of the degrees by rank (null: nptr)
   int64_t hi() const { return own_hi < 0 ? n : own_hi; }
 };
 
@@ -125,8 +135,9 @@ struct Tuning {
   int probe_w = 4;          // weight of a hub-table probe against a scanned element (x 1/3)
   int c4_med_win = 64;      // ranged medium owners: 16 windows >= this per range (0: none)
   int c4_bin_win = 6;       // owners above the one-pass medium bound whose endpoints span at
-                            // least this many counter windows are binned by window (0: never)
-  int c4_bin_cap = 0;       // endpoints of a binning workgroup's scratch (0: 2^20)
+                            // least this many counter windows take the large filter (0: never)
+  int c4_bin_cap = 0;       // candidates one class of a large filtered owner is planned for
+                            // (0: 3/4 of its table)
   int c4_bin_dense = 16384; // endpoints per window from which an owner keeps dense windows (0: never)
   int probe_w_far = 16;     // probe_w when the hub tables do not fit in the Infinity Cache
   int tri_wave_far = 64;    // tri_wave_max when the out-lists do not fit in the Infinity Cache
@@ -256,11 +267,13 @@ BasisChoice choose_basis(const Prep& P, const Tuning& tu, uint32_t flags, bool b
                          Scal* scal, unsigned long long* host_pair, hipStream_t s);
 Launch edge_plan(const Prep& P, Scal* scal, uint32_t flags, int num_cu, KTimer* kt);
 
-// m4_c4.hip (binned, if given, is set when owners go to the binning kernel,
-// which holds every CU with persistent workgroups and all of their LDS)
+// m4_c4.hip (binned, if given, is set when owners go to the large filter,
+// which holds every CU with a persistent workgroup and all of its LDS; n8, if
+// given, receives the per-vertex 4-cycle credits of every rank)
 Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, uint32_t flags,
                Arena& tmp, hipStream_t s, int num_cu, KTimer* kt,
-               const std::function<char*(size_t)>& big_scratch, bool* binned = nullptr);
+               const std::function<char*(size_t)>& big_scratch, bool* binned = nullptr,
+               unsigned long long* n8 = nullptr);
 inline void c4_run(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, uint32_t flags,
                    Arena& tmp, hipStream_t s, int num_cu, KTimer* kt,
                    const std::function<char*(size_t)>& big_scratch) {

@@ -102,7 +102,7 @@ extern "C" int m4_count_motifs4_noalloc(m4_ctx* ctx, const m4_csr* g, const m4_o
     oo.flags &= ~(uint32_t)(M4_TIMING | M4_FORCE_PARTITION);
     Prep P;
     run_resident(ctx, g->row_ptr, g->col, g->n, g->nnz, &oo, s, P, false);
-    M4_HIP(hipMemcpyAsync(ctx->scal_host, ctx->scal, sizeof(Scal), hipMemcpyDeviceToHost, s));
+    M4_HIP(hipMemcpyAsync(ctx->scal_host, ctx->scal, kScalHead, hipMemcpyDeviceToHost, s));
     M4_HIP(hipStreamSynchronize(s));
     const Scal& h = *ctx->scal_host;
     if (h.err) return scal_error(ctx, h.err);

@@ -311,7 +311,7 @@ int count_partitioned(m4_ctx* c, const m4_csr* g, const m4_opts* o, uint64_t out
   hipStream_t s = (o && o->hip_stream) ? (hipStream_t)o->hip_stream : c->stream;
   const uint32_t flags = o ? o->flags : 0;
   Tuning tu = tuning_for(c, o);
-  // the binned 4-cycle owners need scratch a partition's budget cannot spare
+  // no large filter: a partition does not hold the degrees' prefix sums
   tu.c4_bin_win = 0;
   const int64_t n = g->n, nnz = g->nnz, m = nnz / 2;
   uint64_t budget = o ? o->device_budget_bytes : 0;
@@ -752,7 +752,7 @@ int count_partitioned(m4_ctx* c, const m4_csr* g, const m4_opts* o, uint64_t out
     }
   }
   finalize_run(c->scal, s);
-  M4_HIP(hipMemcpyAsync(c->scal_host, c->scal, sizeof(Scal), hipMemcpyDeviceToHost, s));
+  M4_HIP(hipMemcpyAsync(c->scal_host, c->scal, kScalHead, hipMemcpyDeviceToHost, s));
   M4_HIP(hipStreamSynchronize(s));
   t_phase[3] = now_ms() - t_mark;
   const Scal& h = *c->scal_host;

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(NT, 5) void k_tri_lds(TriArgs A) {
       owners++;
     }
   }
-  block_add_u128<NT>(&A.scal->acc[ACC_K4], k4);
+  block_add_acc<NT>(A.scal, ACC_K4, k4);
   if (A.flags & M4_STATS) {
     block_add_u64<NT>(&A.scal->stat[ST_STEPS], steps);
     block_add_u64<NT>(&A.scal->stat[ST_LOOKUPS], looks);
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(NT) void k_tri_global(TriArgs A) {
     owners++;
     __threadfence();
   }
-  block_add_u128<NT>(&A.scal->acc[ACC_K4], k4);
+  block_add_acc<NT>(A.scal, ACC_K4, k4);
   if (A.flags & M4_STATS) {
     block_add_u64<NT>(&A.scal->stat[ST_STEPS], steps);
     block_add_u64<NT>(&A.scal->stat[ST_LOOKUPS], looks);
