@@ -66,7 +66,7 @@ void batch_release(m4_ctx* c);
 }  // namespace m4
 
 size_t m4_ctx::held_bytes() const {
-  return prep.cap + tmp.cap + big.cap + big2.cap + input.cap + tout.cap + extra.cap +
+  return prep.cap + tmp.cap + big.cap + big2.cap + big3.cap + input.cap + tout.cap + extra.cap +
          m4::batch_held_bytes(this) + sizeof(m4::Scal);
 }
 
@@ -77,6 +77,7 @@ void m4_ctx::release_resident() {
   tmp.release();
   big.release();
   big2.release();
+  big3.release();
   input.release();
   tout.release();
   m4::batch_release(this);
@@ -187,6 +188,7 @@ extern "C" void m4_ctx_destroy(m4_ctx* c) {
   c->tmp.release();
   c->big.release();
   c->big2.release();
+  c->big3.release();
   c->input.release();
   c->tout.release();
   c->extra.release();
@@ -554,16 +556,20 @@ extern "C" int m4_count_orbits4(m4_ctx* ctx, const m4_csr* g, const m4_opts* o,
   Classes C{};
   build_prep(rp, col, n, g->nnz, (flags & M4_VALIDATE) != 0, P, C, ctx->scal, ctx->scal_host, a,
              s);
-  a.used = 0;
+  // the triangle and 4-cycle stages keep their workspaces side by side
+  const size_t c4_bytes = c4_tmp_bytes(n);
+  Arena at, ac;
+  at.base = ctx->tmp.ptr;
+  at.cap = ctx->tmp.cap - c4_bytes;
+  ac.base = ctx->tmp.ptr + at.cap;
+  ac.cap = c4_bytes;
   auto big = [ctx, s](size_t bytes) -> char* {
     ctx->big.ensure(bytes, s);
     return ctx->big.ptr;
   };
-  tri_run(P, ctx->scal, tu, flags, 0, a, s, ctx->num_cu, big, nullptr);
+  tri_run(P, ctx->scal, tu, flags, 0, at, s, ctx->num_cu, big, nullptr);
   // statistics (8 n words) and the bitmap slices of out-degrees above the
-  // LDS bound in big2; the 4-cycle counters (4 n bytes per workgroup, 8 n
-  // from degree 2^16, at most 16 GiB, at most one workgroup per CU: more
-  // workgroups measured slower, their counters crowding the caches) in big
+  // LDS bound in big2
   const int kmax = local_dplus_max(P, ctx->scal, s);
   const size_t arr_bytes = align256((size_t)n * 8 * 8);
   int gblocks = 0;
@@ -574,18 +580,19 @@ extern "C" int m4_count_orbits4(m4_ctx* ctx, const m4_csr* g, const m4_opts* o,
     g_bytes = (size_t)gblocks * per;
   }
   ctx->big2.ensure(arr_bytes + g_bytes, s);
-  const bool wide = C.dmax >= 65536;
-  const int64_t cword = wide ? 8 : 4;
-  const int cblocks = (int)std::max<int64_t>(
-      1, std::min<int64_t>((int64_t(16) << 30) / ((int64_t)n * cword), (int64_t)ctx->num_cu));
-  ctx->big.ensure((size_t)cblocks * (size_t)n * (size_t)cword, s);
+  unsigned long long* arrays = reinterpret_cast<unsigned long long*>(ctx->big2.ptr);
+  auto big3 = [ctx, s](size_t bytes) -> char* {
+    ctx->big3.ensure(bytes, s);
+    return ctx->big3.ptr;
+  };
+  const Launch cycles = c4_plan(P, C, ctx->scal, tu, flags, ac, s, ctx->num_cu, nullptr, big3,
+                                nullptr, arrays + 5 * n);
   unsigned long long* dst = reinterpret_cast<unsigned long long*>(orbits);
   if (!g->on_device) {
     ctx->tout.ensure(out_bytes, s);
     dst = reinterpret_cast<unsigned long long*>(ctx->tout.ptr);
   }
-  local_orbits(P, C, ctx->scal, reinterpret_cast<unsigned long long*>(ctx->big2.ptr),
-               ctx->big.ptr, wide, cblocks,
+  local_orbits(P, C, ctx->scal, arrays, cycles,
                gblocks ? reinterpret_cast<unsigned long long*>(ctx->big2.ptr + arr_bytes) : nullptr,
                gblocks, kmax, dst, ctx->num_cu, s);
   if (!g->on_device) M4_HIP(hipMemcpyAsync(orbits, dst, out_bytes, hipMemcpyDeviceToHost, s));

@@ -58,7 +58,10 @@ struct C4Args {
   const int64_t* seg_off;  // window owners: first descriptor of each owner
   int4* desc;              // ... per-segment cursor descriptors
   const int32_t* seg_cnt;  // ... non-empty segments of each owner
-  const int64_t* deg_pre;  // prefix sums of the degrees by rank
+  // large filtered owners: parts {owner, first rank, end rank, endpoints
+  // expected}, the rank ranges that are counted apart (null: whole owners)
+  const int4* parts;
+  int64_t npart;           // parts of this bucket
   const int4* vmeta;       // per full row: offset, degree, lower neighbours, entries below r1
   unsigned long long* n8;  // per-vertex 4-cycle credits (orbit counts), or null
   int yb;                  // filtered owners: bits of a permuted rank
@@ -97,8 +100,13 @@ constexpr int C4_BIN_AB = 20, C4_BIN_BB = 17;
 constexpr int C4_DISP_BITS = 6;                  // distance of a slot from its home slot
 constexpr uint32_t C4_MAX_CLASSES = 1u << 16;
 constexpr uint32_t C4_KEY_MUL = 0x9E3779B1u, C4_KEY_INV = 0x0E8B2F51u;  // MUL x INV = 1 mod 2^32
-// endpoints of one rank range of a large filtered owner
+// Direct counters: graphs of at most C4_DIRECT_N vertices, and parts of large
+// filtered owners over at most C4_DIRECT_SPAN ranks.
+constexpr int C4_DIRECT_N = 8192;
+constexpr int32_t C4_DIRECT_SPAN = 262144;
+// endpoints of one part of a large filtered owner; most parts
 constexpr int64_t C4_BIN_RANGE = 131072;
+constexpr int C4_MAX_PARTS = 4096;
 
 // Bits of a permuted rank for tables of 2^hb slots, and the first number of
 // lower neighbours whose counts do not fit beside the key in a slot.
@@ -471,6 +479,120 @@ __global__ __launch_bounds__(WAVE) void k_c4_tiny(C4Args A) {
   }
 }
 
+// ------------------------------------------------------- direct counters
+// The endpoints of owner u in ranks [lo, end) counted with one 32-bit LDS
+// counter per rank, over windows of WORDS ranks: one walk counts (the old
+// values are the sum), CRED takes a second walk for the middle vertices and a
+// sweep of the counters for endpoints and owner.  Where a window holds many
+// endpoints per rank this beats a filter, which would count nearly all of
+// them in its table.  Called by every thread of the workgroup; the counters
+// need not be clear.
+template <int NT, int WORDS, int SEGS, bool CRED>
+__device__ __forceinline__ void count_direct(const C4Args& A, uint4* cnt4, int2* sg, int32_t* sv,
+                                             int* next, int64_t base, int nl, int32_t lo,
+                                             int32_t end, u128_t& acc, unsigned long long& wedges,
+                                             unsigned long long& own) {
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(cnt4);
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+  for (; lo < end; lo += WORDS) {
+    const int32_t hi = end - lo < WORDS ? end : lo + WORDS;
+    for (int i = tid; i < (hi - lo + 3) / 4; i += NT) cnt4[i] = make_uint4(0, 0, 0, 0);
+    bool loaded = false;
+    auto walk = [&](auto&& ent, auto&& fin) {
+      for (int s0 = 0; s0 < nl; s0 += SEGS) {
+        const int nc = nl - s0 < SEGS ? nl - s0 : SEGS;
+        if (!loaded) load_segs<NT, CRED>(A, base, nl, s0, nc, lo, sg, sv);
+        loaded = nl <= SEGS;
+        if (tid == 0) *next = 0;
+        __syncthreads();
+        seg_walk<8>(A.ncol, hi, nc, next, sg, ent, fin);
+        __syncthreads();
+      }
+    };
+    unsigned long long part = 0;
+    walk(
+        [&](const int32_t(&x)[4]) {
+          uint32_t old[4];
+#pragma unroll
+          for (int k = 0; k < 4; k++) {
+            const bool in = x[k] < hi;
+            old[k] = in ? atomicAdd(&cnt[x[k] - lo], 1u) : 0u;
+            wedges += in;
+          }
+#pragma unroll
+          for (int k = 0; k < 4; k++) part += old[k];
+        },
+        [](int, bool) {});
+    acc += part;
+    if (CRED) {
+      unsigned long long cr = 0;
+      walk(
+          [&](const int32_t(&x)[4]) {
+#pragma unroll
+            for (int k = 0; k < 4; k++)
+              if (x[k] < hi) cr += cnt[x[k] - lo] - 1;
+          },
+          [&](int i, bool last) {
+            if (!__ballot(last)) return;
+            const unsigned long long t = lane_group_sum<8>(cr);
+            if (last) {
+              if ((lane & 7) == 0 && t) atomicAdd(&A.n8[sv[i]], t);
+              cr = 0;
+            }
+          });
+      for (int i = tid; i < hi - lo; i += NT) {
+        const unsigned long long c = cnt[i];
+        if (c >= 2) {
+          own += pairs_of(c);
+          atomicAdd(&A.n8[lo + i], pairs_of(c));
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// Graphs of at most C4_DIRECT_N vertices: every owner above the tiny bound,
+// whatever its bucket (one window, no cursors, no bitmaps, and no bucket size
+// that the host has to wait for).
+template <bool CRED>
+__global__ __launch_bounds__(256) void k_c4_direct(C4Args A) {
+  constexpr int NT = 256, SEGS = 256;
+  __shared__ uint4 cnt4[C4_DIRECT_N / 4];
+  __shared__ int2 sg[SEGS + 1];
+  __shared__ int32_t sv[CRED ? SEGS : 1];
+  __shared__ int s_next;
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+  const int64_t b0 = A.start[CB_HASH], items = A.start[CB_N] - b0;
+  u128_t acc = 0;
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+    const int64_t at = b0 + items - 1 - item;  // heaviest owners (highest ranks) first
+    const int32_t u = __builtin_amdgcn_readfirstlane(A.order[at]);
+    const int nl = __builtin_amdgcn_readfirstlane(A.dlo[u]);
+    unsigned long long own = 0, wedges = 0;
+    count_direct<NT, C4_DIRECT_N, SEGS, CRED>(A, cnt4, sg, sv, &s_next, A.nptr[u], nl, A.zr1, u,
+                                              acc, wedges, own);
+    if (CRED) {
+      own = lane_group_sum<WAVE>(own);
+      if (lane == 0 && own) atomicAdd(&A.n8[u], own);
+    }
+    if (A.flags & M4_STATS) {
+      // the slot of the owner's bucket
+      const int slot = at < A.start[CB_HASH + 1]  ? M4_K_C4_HASH
+                       : at < A.start[CB_MED + 1] ? M4_K_C4_MED
+                       : at < A.start[CB_WIN + 1] ? M4_K_C4_WINDOW
+                                                  : M4_K_C4_BIN;
+      const unsigned long long one = tid == 0 ? 1 : 0;
+      block_add_u64<NT>(&A.scal->stat[ST_WEDGES], wedges);
+      block_add_u64<NT>(&A.scal->kstat[slot][0], wedges);
+      block_add_u64<NT>(&A.scal->kstat[slot][1], one);
+      block_add_u64<NT>(&A.scal->kstat[slot][2], one * (unsigned long long)nl);
+      block_add_u64<NT>(&A.scal->kstat[slot][3], one);
+    }
+  }
+  block_add_acc<NT>(A.scal, ACC_C4, acc);
+}
+
 // ------------------------------------------------------- filter buckets
 // Most wedge endpoints of a sparse owner are met once (88 % on the scale-24
 // web graph) and close no 4-cycle, so they are told apart before anything is
@@ -488,21 +610,26 @@ __global__ __launch_bounds__(WAVE) void k_c4_tiny(C4Args A) {
 // from the home slot (6 bits) and the count above them, which stays below
 // the owner's lower neighbours (the plan sends no owner whose number does
 // not fit).  WIDE slots hold rank + 1 and a 32-bit count.
-// An owner with more than C4_BIN_RANGE endpoints is counted in rank ranges
-// of about equal numbers of endpoints (an endpoint's chance to be rank x is
-// about proportional to the degree of x, and the row offsets are the
-// degrees' prefix sums).  A range with more candidates than the table holds
+// An owner with more than C4_BIN_RANGE endpoints is counted in parts: rank
+// ranges of about equal numbers of endpoints, each by any workgroup, so that
+// no single owner keeps one CU busy after the others have ended.  A part with
+// more candidates than the table holds
 // is counted in P classes of a second hash, one walk each; a class that
 // overflows the table is dropped, split in two and walked again, so every
 // owner ends.
 // Bound by vector issue (about 135 instructions per 256 entries, half of the
 // issue slots) and, at 16 wavefronts a CU, by the latency of a walk's one load
 // in flight.  Scale-24 web graph (268 M edges): the 395 K large owners (21.5 G
-// endpoints, 2.5 walks each) 103 ms, 209 ms when their endpoints were sorted
-// into bins in device memory; the 698 K medium ones (1.76 G) 9.0 ms, 33 ms in
-// 16384-slot tables with a search per endpoint; light and tiny ones 4.5 ms,
-// 18 ms.  Ranges of 82 K / 131 K / 164 K endpoints: 115 / 103 / 111 ms;
-// 512-thread workgroups, two a CU with half the bitmap: 167 ms.
+// endpoints, about 2.5 walks each) 91 ms, 209 ms when their endpoints were
+// sorted into bins in device memory; the 698 K medium ones (1.76 G) 8.8 ms,
+// 33 ms in 16384-slot tables with a search per endpoint; light and tiny ones
+// 4.5 ms, 18 ms.  Parts of 98 K / 131 K / 196 K endpoints: 97 / 91 / 104 ms;
+// direct counters for parts of up to 33 K / 131 K / 262 K / 524 K ranks: 98 /
+// 95 / 91 / 99 ms; 512-thread workgroups, two a CU with half the bitmap:
+// 167 ms (at 103).  Whole owners instead of parts: 103 ms, and the credits of
+// the web 2^21 graph 51 ms instead of 20, of the social 2^18 graph 38 instead
+// of 2.6 (one hub kept one CU busy); with one global atomic per wedge into n
+// counters per workgroup they took 336 and 19 ms.
 template <int AB, bool WIDE>
 struct FilterTable {
   using Slot = std::conditional_t<WIDE, unsigned long long, uint32_t>;
@@ -572,7 +699,8 @@ __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
   uint32_t* fa = reinterpret_cast<uint32_t*>(fa4);
   uint32_t* fb = reinterpret_cast<uint32_t*>(fb4);
   const int tid = threadIdx.x, lane = tid & (WAVE - 1);
-  const int64_t b0 = A.start[A.bucket], cnt = A.start[A.bucket + 1] - b0;
+  const int64_t b0 = A.start[A.bucket];
+  const int64_t cnt = A.parts ? A.npart : A.start[A.bucket + 1] - b0;
   Table tab(fa4, A.yb);
   u128_t acc = 0;
   unsigned long long wedges = 0, owners = 0, segs = 0, walks = 0;
@@ -584,23 +712,24 @@ __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
     unsigned ahead = 0;
     if (!DEAL && tid == 0) ahead = atomicAdd(A.work, 1u);
     const int64_t pos = cnt - 1 - item;  // heaviest owners (highest ranks) first
-    const int32_t u = __builtin_amdgcn_readfirstlane(A.order[b0 + pos]);
+    int4 part;
+    if (A.parts) part = A.parts[pos];
+    else part.x = A.order[b0 + pos];
+    const int32_t u = __builtin_amdgcn_readfirstlane(part.x);
     const int nl = __builtin_amdgcn_readfirstlane(A.dlo[u]);
     const int64_t base = A.nptr[u];
-    const int64_t wb = A.wub[u];
-    const int R = (int)((wb + C4_BIN_RANGE - 1) / C4_BIN_RANGE);
-    owners++;
+    const int32_t lo = A.parts ? __builtin_amdgcn_readfirstlane(part.y) : A.zr1;
+    const int32_t hi = A.parts ? __builtin_amdgcn_readfirstlane(part.z) : u;
+    const unsigned long long wb =
+        A.parts ? (unsigned long long)part.w : (unsigned long long)A.wub[u];
+    owners += lo == A.zr1;
     segs += (unsigned long long)nl;
     unsigned long long own = 0;
-    int32_t lo = A.zr1;
-    for (int r = 0; r < R; r++) {
-      int32_t hi = u;
-      if (r + 1 < R) {
-        const int64_t c0 = A.deg_pre[A.r1], c1 = A.deg_pre[u];
-        hi = (int32_t)lower_index(A.deg_pre, (int64_t)lo, (int64_t)u,
-                                  c0 + (int64_t)((double)(c1 - c0) * (r + 1) / R));
-      }
-      if (hi <= lo) continue;
+    if (NT == 1024 && hi - lo <= C4_DIRECT_SPAN) {
+      // a dense part: the first bitmap's words as counters
+      count_direct<NT, AW, SEGS, CRED>(A, fa4, sg, sv, &s_next, base, nl, lo, hi, acc, wedges, own);
+      walks++;
+    } else if (lo < hi) {
       // ---- 1. the bitmaps
       for (int i = tid; i < AW / 4; i += NT) fa4[i] = make_uint4(0, 0, 0, 0);
       for (int i = tid; i < BW / 4; i += NT) fb4[i] = make_uint4(0, 0, 0, 0);
@@ -651,7 +780,7 @@ __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
       // have their bit of the smaller second bitmap set by others; never more
       // than the ranks of the range
       const unsigned long long est = std::min<unsigned long long>(
-          nd + (((unsigned long long)(wb / R) * nd) >> BB), (unsigned long long)(hi - lo));
+          nd + ((wb * nd) >> BB), (unsigned long long)(hi - lo));
       uint32_t P = (uint32_t)std::min<unsigned long long>((est + CAP - 1) / CAP, C4_MAX_CLASSES);
       if (nd == 0) P = 0;
       for (uint32_t c = 0; c < P;) {
@@ -741,7 +870,6 @@ __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
         }
         c++;
       }
-      lo = hi;
     }
     if (CRED) {
       own = lane_group_sum<WAVE>(own);
@@ -826,11 +954,43 @@ __global__ void k_vmeta(const int64_t* __restrict__ nptr, const int32_t* __restr
   vmeta[v] = make_int4((int)rs, dr[v], dlo[v], cut);
 }
 
+// Lengths of the heavy owners' lists: segment descriptors of a window owner,
+// parts of a large filtered one (the two are adjacent in the bucket order).
 __global__ void k_c4_heavy_len(const int32_t* __restrict__ order, const int64_t* __restrict__ start,
-                               const int32_t* __restrict__ dlo, int32_t* __restrict__ len) {
+                               const int32_t* __restrict__ dlo, const int64_t* __restrict__ wub,
+                               int64_t H, int32_t* __restrict__ len) {
   const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t b = start[CB_WIN], H = start[CB_WIN + 1] - b;
-  if (h < H) len[h] = dlo[order[b + h]];
+  if (h >= H) return;
+  const int32_t u = order[start[CB_WIN] + h];
+  if (h < start[CB_WIN + 1] - start[CB_WIN]) {
+    len[h] = dlo[u];
+  } else {
+    const int64_t k = (wub[u] + C4_BIN_RANGE - 1) / C4_BIN_RANGE;
+    len[h] = (int32_t)(k < C4_MAX_PARTS ? k : C4_MAX_PARTS);
+  }
+}
+
+// The parts of the large filtered owners: rank ranges of about equal numbers
+// of endpoints (an endpoint's chance to be rank x is about proportional to the
+// degree of x, and the row offsets are the degrees' prefix sums).  One thread
+// per part; off holds the first part of each owner.
+__global__ void k_c4_parts(const int32_t* __restrict__ owner, const int64_t* __restrict__ wub,
+                           const int64_t* __restrict__ nptr, const int64_t* __restrict__ off,
+                           int64_t H, int64_t total, int64_t r1, int4* __restrict__ parts) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= total) return;
+  const int64_t h = lower_index(off, (int64_t)0, H, i + 1) - 1;  // the owner whose parts hold i
+  const int32_t u = owner[h];
+  const int64_t p = i - off[h], k = off[h + 1] - off[h];
+  const int64_t d0 = nptr[r1], d1 = nptr[u];
+  auto cut = [&](int64_t q) -> int32_t {
+    if (q <= 0) return (int32_t)r1;
+    if (q >= k) return u;
+    return (int32_t)lower_index(nptr, r1, (int64_t)u,
+                                d0 + (int64_t)((double)(d1 - d0) * (double)q / (double)k));
+  };
+  const int64_t w = (wub[u] + k - 1) / k;
+  parts[i] = make_int4(u, cut(p), cut(p + 1), (int)(w < INT_MAX ? w : INT_MAX));
 }
 
 constexpr int W_NT = 1024, W_GL = 8, W_NG = W_NT / W_GL, W_SHORT = 8;
@@ -993,7 +1153,6 @@ __global__ __launch_bounds__(W_NT) void k_c4_window(C4Args A) {
   const int tid = threadIdx.x;
   const int g = tid / W_GL, gl = tid & (W_GL - 1);
   const int64_t b0 = A.start[A.bucket], cnt_items = A.start[A.bucket + 1] - b0;
-  const int64_t hbase = b0 - A.start[CB_WIN];
   const int4* __restrict__ ncol4 = reinterpret_cast<const int4*>(A.ncol);
   const int4 kNone = make_int4(0, 0, INT_MAX, INT_MAX);
   u128_t acc = 0;
@@ -1009,8 +1168,8 @@ __global__ __launch_bounds__(W_NT) void k_c4_window(C4Args A) {
     // heaviest owners (highest ranks) first
     const int64_t pos = cnt_items - 1 - item;
     const int32_t u = A.order[b0 + pos];
-    const int64_t so = A.seg_off[hbase + pos];
-    const int nl = A.seg_cnt[hbase + pos];
+    const int64_t so = A.seg_off[pos];
+    const int nl = A.seg_cnt[pos];
     int4* D = A.desc + so;
     // owners with at most W_BATCH segments keep each thread's descriptors in
     // registers from window to window
@@ -1207,17 +1366,25 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
   // bucket starts (C4_START_SLOTS), then the two zone bounds
   int64_t* start = tmp.take<int64_t>(C4_START_SLOTS + 2);
   int32_t* hlen = tmp.take<int32_t>(n);
-  int64_t* seg_off = tmp.take<int64_t>(n + 1);
+  int64_t* hoff = tmp.take<int64_t>(n + 2);
   int64_t* stmp = tmp.take<int64_t>(scan_tmp_elems(n));
   // per-row records of full rows (a partition stores row prefixes instead)
   int4* vmeta = P.row_len ? nullptr : tmp.take<int4>(n);
-  if (!wub || !key || !order || !rtmp || !start || !hlen || !seg_off || !stmp ||
+  if (!wub || !key || !order || !rtmp || !start || !hlen || !hoff || !stmp ||
       (!P.row_len && !vmeta))
     throw Fail(M4_EINTERNAL, "workspace too small (c4)");
   fill_u32(&scal->work_c4[0], 0, 8, s);
-  // zone bounds first: the planner needs every owner's window count
+  // W_u <= d (d - 1) of the largest degree d: where that leaves only the light
+  // buckets the host does not wait for the bucket sizes; the kernels read them
+  // on the device, and their grids are bounded by n
+  const int64_t wmost = (int64_t)C.dmax * (C.dmax - 1);
+  const bool small = n <= C4_DIRECT_N && !P.row_len;  // direct counters above the tiny bound
+  const bool light_only = small || (wmost <= tu.c4_light_max &&
+                                    (wmost <= C4_TINY_MAX ||
+                                     C.dmax < c4_count_limit(n, C4_LIGHT_AB - 5)));
+  // zone bounds first: the planner needs every heavy owner's window count
   int64_t* zbounds = start + C4_START_SLOTS;
-  k_zone_bounds<<<1, 64, 0, s>>>(P.dr, n, zbounds);
+  if (!light_only || small) k_zone_bounds<<<1, 64, 0, s>>>(P.dr, n, zbounds);
   C4Plan pl{tu.c4_light_max, tu.c4_med_max, tu.c4_med_win, tu.c4_bin_win, tu.c4_bin_dense,
             zbounds, C.r1, c4_count_limit(n, C4_LIGHT_AB - 5), c4_count_limit(n, C4_MED_AB - 5),
             c4_count_limit(n, C4_BIN_AB - 5), n8 ? 1 : 0};
@@ -1236,30 +1403,56 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
                                                          pl, wub, key, P.own_lo, P.hi());
   radix_pass(key, nullptr, n, 0, C4_KEY_BITS, nullptr, order, rtmp, start, s);
   std::array<int64_t, C4_START_SLOTS + 2> hstart;
-  M4_HIP(hipMemcpyAsync(hstart.data(), start, sizeof(int64_t) * hstart.size(),
-                        hipMemcpyDeviceToHost, s));
-  M4_HIP(hipStreamSynchronize(s));
+  if (light_only) {
+    // at most n owners in each light bucket, none elsewhere
+    hstart.fill(wmost > C4_TINY_MAX ? 2 * n : n);
+    hstart[CB_TINY] = 0;
+    hstart[CB_HASH] = n;
+  } else {
+    M4_HIP(hipMemcpyAsync(hstart.data(), start, sizeof(int64_t) * hstart.size(),
+                          hipMemcpyDeviceToHost, s));
+    M4_HIP(hipStreamSynchronize(s));
+  }
   // counter zones of the window owners
   const int64_t z1 = std::max<int64_t>(hstart[C4_START_SLOTS], C.r1);
   const int64_t z2 = std::max<int64_t>(hstart[C4_START_SLOTS + 1], z1);
   const int64_t aw = (z1 - C.r1 + 7) >> 3, bw = (z2 - z1 + 3) >> 2;
   auto owners = [&hstart](int b) { return hstart[b + 1] - hstart[b]; };
-  const int64_t H = owners(CB_WIN);
-  if (binned) *binned = owners(CB_BIN) + owners(CB_WIDE) > 0;
+  const int64_t HW = owners(CB_WIN);
+  // a partition takes whole owners: it does not hold the degrees' prefix sums
+  const int64_t HB = P.row_len ? 0 : hstart[CB_WIDE + 1] - hstart[CB_BIN];
+  if (binned) *binned = hstart[CB_WIDE + 1] > hstart[CB_BIN];
   int4* desc = nullptr;
   int32_t* seg_cnt = nullptr;
-  if (H > 0) {
-    k_c4_heavy_len<<<blocks_for(H, 256), 256, 0, s>>>(order, start, P.dlo, hlen);
-    scan_i32(hlen, H, seg_off, stmp, s);
+  int4* parts = nullptr;
+  std::array<int64_t, 3> pfirst{0, 0, 0};  // first parts of the two buckets, their end
+  if (HW + HB > 0) {
+    k_c4_heavy_len<<<blocks_for(HW + HB, 256), 256, 0, s>>>(order, start, P.dlo, wub, HW + HB,
+                                                           hlen);
+    int64_t* poff = hoff + HW + 1;
+    scan_i32(hlen, HW, hoff, stmp, s);
+    scan_i32(hlen + HW, HB, poff, stmp, s);
     int64_t nseg = 0;
-    M4_HIP(hipMemcpyAsync(&nseg, seg_off + H, 8, hipMemcpyDeviceToHost, s));
+    M4_HIP(hipMemcpyAsync(&nseg, hoff + HW, 8, hipMemcpyDeviceToHost, s));
+    if (HB > 0) {
+      for (int b = CB_BIN; b <= CB_WIDE; b++)
+        M4_HIP(hipMemcpyAsync(&pfirst[b + 1 - CB_BIN], poff + hstart[b + 1] - hstart[CB_BIN], 8,
+                              hipMemcpyDeviceToHost, s));
+    }
     M4_HIP(hipStreamSynchronize(s));
-    const size_t db = ((size_t)(nseg > 0 ? nseg : 1) * sizeof(int4) + 255) & ~size_t(255);
-    const size_t cb = ((size_t)H * 4 + 255) & ~size_t(255);
-    char* scr = big_scratch(db + cb);
+    auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
+    const size_t db = al((size_t)(nseg > 0 ? nseg : 1) * sizeof(int4));
+    const size_t cb = al((size_t)std::max<int64_t>(HW, 1) * 4);
+    const size_t pb = HB > 0 ? al((size_t)pfirst[2] * sizeof(int4)) : 0;
+    char* scr = big_scratch(db + cb + pb);
     if (!scr) throw Fail(M4_ENOMEM, "no room for 4-cycle segment descriptors");
     desc = reinterpret_cast<int4*>(scr);
     seg_cnt = reinterpret_cast<int32_t*>(scr + db);
+    if (HB > 0) {
+      parts = reinterpret_cast<int4*>(scr + db + cb);
+      k_c4_parts<<<blocks_for(pfirst[2], 256), 256, 0, s>>>(
+          order + hstart[CB_BIN], wub, P.nptr, poff, HB, pfirst[2], C.r1, parts);
+    }
   }
   if (kt) kt->end(M4_K_C4_PLAN, s);
 
@@ -1275,11 +1468,10 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
   A.r1 = C.r1;
   A.scal = scal;
   A.flags = flags;
-  A.seg_off = seg_off;
+  A.seg_off = hoff;
   A.desc = desc;
   A.seg_cnt = seg_cnt;
   A.vmeta = vmeta;
-  A.deg_pre = P.deg_pre ? P.deg_pre : P.nptr;
   A.n8 = n8;
   A.z1 = (int32_t)z1;
   A.z2 = (int32_t)z2;
@@ -1293,13 +1485,18 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
     if (kt) kt->begin(M4_K_C4_DESC, ls);
     if (!P.row_len)
       k_vmeta<<<blocks_for(n, 256), 256, 0, ls>>>(P.nptr, P.ncol, P.dr, P.dlo, n, C.r1, vmeta);
-    if (H > 0)
-      k_c4_desc<<<(unsigned)H, 256, 0, ls>>>(order, start, seg_off, P.nptr, P.dlo, P.ncol, vmeta,
-                                             P.row_len, C.r1, desc, seg_cnt);
+    if (HW > 0)
+      k_c4_desc<<<(unsigned)HW, 256, 0, ls>>>(order, start, hoff, P.nptr, P.dlo, P.ncol, vmeta,
+                                              P.row_len, C.r1, desc, seg_cnt);
     if (kt) kt->end(M4_K_C4_DESC, ls);
     auto run = [&](int bucket, int slot, int hb, auto&& kernel, int nt, int64_t most, int grab) {
-      const int64_t cnt = hstart[bucket + 1] - hstart[bucket];
+      int64_t cnt = hstart[bucket + 1] - hstart[bucket];
       if (cnt <= 0) return;
+      A.parts = nullptr;
+      if (parts && bucket >= CB_BIN) {
+        A.parts = parts + pfirst[bucket - CB_BIN];
+        A.npart = cnt = pfirst[bucket - CB_BIN + 1] - pfirst[bucket - CB_BIN];
+      }
       A.bucket = bucket;
       A.slot = slot;
       A.work = &scal->work_c4[bucket];
@@ -1314,6 +1511,16 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
                       int per_cu) {
       run(bucket, slot, hb, n8 ? cred : plain, nt, (int64_t)num_cu * per_cu, 1);
     };
+    const int64_t waves = (int64_t)num_cu * 32;
+    if (small) {
+      // the owners of every bucket above the tiny one: a kernel for all
+      if (wmost > C4_TINY_MAX) {
+        hstart[CB_HASH + 1] = 2 * n;
+        filter(CB_HASH, M4_K_C4_HASH, 1, k_c4_direct<false>, k_c4_direct<true>, 256, 4);
+      }
+      run(CB_TINY, M4_K_C4_HASH, 1, n8 ? k_c4_tiny<true> : k_c4_tiny<false>, WAVE, waves, 1);
+      return;
+    }
     // heavy owners first
     if (n8)
       run(CB_WIDE, M4_K_C4_BIN, C4_BIN_AB - 7,
@@ -1330,7 +1537,6 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
            k_c4_filter<64, 8, C4_LIGHT_AB, C4_LIGHT_BB, 64, true>, 64, 24);
     // a wavefront takes up to 16 owners at once where that still fills the
     // device (32 wavefronts a CU), fewer where it would not
-    const int64_t waves = (int64_t)num_cu * 32;
     const int64_t tiny = hstart[CB_TINY + 1] - hstart[CB_TINY];
     run(CB_TINY, M4_K_C4_HASH, 1, n8 ? k_c4_tiny<true> : k_c4_tiny<false>, WAVE, waves,
         (int)std::max<int64_t>(1, std::min<int64_t>(16, tiny / waves)));

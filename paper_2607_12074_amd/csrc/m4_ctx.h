@@ -80,7 +80,7 @@ struct m4_ctx {
   m4::Scal* scal_host = nullptr;  // pinned
   hipStream_t stream2 = nullptr;  // the 4-cycle stage, overlapped with the triangle stage
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
-  m4::DevBuf prep, tmp, big, big2, input, tout, extra;
+  m4::DevBuf prep, tmp, big, big2, big3, input, tout, extra;
   hipEvent_t ev[m4::kNumEvents] = {};
   m4::KTimer ktimer;
   m4::Tuning tune;

@@ -36,7 +36,7 @@ enum Stat { ST_STEPS = 0, ST_WEDGES, ST_LOOKUPS, ST_HITS, ST_COST, ST_N = 8 };
 // Triangle-owner buckets by out-degree k = d+(u).
 enum TriBucket { TB_NONE = 0, TB_WAVE, TB_LDS, TB_GLOBAL, TB_N = 4 };
 // 4-cycle-owner buckets by wedge bound.
-enum C4Bucket { CB_NONE = 0, CB_TINY, CB_HASH, CB_MED, CB_WIN, CB_BIN, CB_WIDE, CB_N = 7 };
+enum C4Bucket { CB_NONE = 0, CB_TINY, CB_HASH, CB_MED, CB_WIN, CB_BIN, CB_WIDE, CB_N };
 // radix digits of the 4-cycle bucket keys and slots of their bucket starts
 constexpr int C4_KEY_BITS = 4;
 constexpr int C4_START_SLOTS = (1 << C4_KEY_BITS) + 1;
@@ -98,7 +98,6 @@ struct Prep {
   // may be stored as a prefix of row_len[v] entries (null: full rows).
   int64_t own_lo = 0, own_hi = -1;
   const int32_t* row_len = nullptr;
-  const int64_t* deg_pre = nullptr;  // prefix sums of the degrees by rank (null: nptr)
   int64_t hi() const { return own_hi < 0 ? n : own_hi; }
 };
 
@@ -252,8 +251,8 @@ inline void tri_run(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags,
 
 // m4_local.hip: per-vertex orbit counts of a prepared graph (t complete)
 void local_orbits(const Prep& P, const Classes& C, Scal* scal, unsigned long long* arrays,
-                  void* cscr, bool wide, int cblocks, unsigned long long* gscr, int gblocks,
-                  int kmax, unsigned long long* out, int num_cu, hipStream_t s);
+                  const Launch& cycles, unsigned long long* gscr, int gblocks, int kmax,
+                  unsigned long long* out, int num_cu, hipStream_t s);
 size_t local_glob_stride_words(int kmax);
 int local_dplus_max(const Prep& P, Scal* scal, hipStream_t s);
 

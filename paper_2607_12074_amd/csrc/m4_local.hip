@@ -36,8 +36,8 @@
 //                  on N+(u) as bitmap rows (LDS up to out-degree 512, device
 //                  scratch beyond); every triangle credits its three vertices
 //                  for N12, every 4-clique (row ANDs) its four for N14
-//   k_loc_cycles   per 4-cycle owner u (highest vertex): wedge counters c[w]
-//                  over the lower neighbours' rows; u and w gain C(c[w], 2),
+//   4-cycle stage  (m4_c4.hip, with credits) per owner u (highest vertex) the
+//                  wedges c[w] of every endpoint w; u and w gain C(c[w], 2),
 //                  a middle vertex v the c[w] - 1 other middles of its wedge
 //   k_loc_final    per vertex: the neighbour sums of N4 and N9, the inverse,
 //                  and the row of the caller's vertex id
@@ -54,10 +54,7 @@ constexpr int LOC_NT = 256;
 constexpr int LOC_NW = LOC_NT / WAVE;
 constexpr int LOC_K_LDS = 512;             // out-degree bound of the LDS bitmap
 constexpr int LOC_W_LDS = LOC_K_LDS / 64;  // its words per row
-constexpr int LOC_SINGLE = 65536;          // heaviest 4-cycle owners taken one at a time
-constexpr int LOC_CHUNK = 32;              // ... the rest in runs of this many ranks
 constexpr int LOC_TRI_CHUNK = 16;          // triangle owners per grab
-constexpr int CYC_NT = 512, CYC_NW = CYC_NT / WAVE;  // 4-cycle credits: 8 wavefronts per counter array
 constexpr int ERR_LOCAL = 8;               // an orbit inverse went negative
 
 struct LocIn {
@@ -339,92 +336,6 @@ __global__ __launch_bounds__(LOC_NT) void k_loc_cliques(LocIn in, LocArrays L, i
   }
 }
 
-// 4-cycle owners u (their highest vertex), heaviest first.  Each block keeps
-// n wedge counters of type CT, all zero between owners: the low half counts
-// a wedge endpoint's wedges in the first pass, the high half its visits in
-// the second, whose last visitor credits the endpoint and clears the
-// counter.  An endpoint's wedges come from distinct lower neighbours of u,
-// so 16-bit halves hold them while degrees stay below 2^16.  The counters of
-// the highest ranks (the hubs, where most wedges end) sit in LDS, the rest
-// in the block's slice of device scratch.
-constexpr int LOC_HOT_BYTES = 128 * 1024;
-
-template <typename CT>
-__device__ __forceinline__ CT hot_or_dev_add(CT* hot, CT* c, int32_t w, int64_t hot_base, CT v) {
-  return w >= hot_base ? atomicAdd(&hot[w - hot_base], v) : atomicAdd(&c[w], v);
-}
-
-template <typename CT>
-__global__ __launch_bounds__(CYC_NT) void k_loc_cycles(LocIn in, int64_t r1, LocArrays L,
-                                                       CT* cscr, unsigned int* work) {
-  constexpr int HALF = (int)sizeof(CT) * 4;
-  constexpr CT LOC_LOW = (CT(1) << HALF) - 1;
-  constexpr int HOT = LOC_HOT_BYTES / (int)sizeof(CT);
-  __shared__ CT hot[HOT];
-  __shared__ int64_t s_g;
-  const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = tid / WAVE;
-  const int64_t n = in.n;
-  const int64_t hot_base = n > HOT ? n - HOT : 0;
-  CT* c = cscr + (int64_t)blockIdx.x * n;
-  for (int i = tid; i < HOT; i += CYC_NT) hot[i] = 0;
-  for (;;) {
-    if (tid == 0) s_g = (int64_t)atomicAdd(work, 1u);
-    __syncthreads();
-    const int64_t g = s_g;
-    __syncthreads();
-    int64_t hi, lo;  // owners hi, hi - 1, ..., lo + 1
-    if (g < LOC_SINGLE) {
-      hi = n - 1 - g;
-      lo = hi - 1;
-    } else {
-      hi = n - 1 - LOC_SINGLE - (g - LOC_SINGLE) * LOC_CHUNK;
-      lo = hi - LOC_CHUNK;
-    }
-    if (hi < r1) break;
-    if (lo < r1 - 1) lo = r1 - 1;
-    for (int64_t u = hi; u > lo; u--) {
-      const int nl = in.dlo[u];
-      if (nl < 2) continue;
-      const int64_t ub = in.nptr[u];
-      // pass 1: c[w] for the wedges u - v - w with v, w below u; the old
-      // values sum to the cycles at u
-      unsigned long long pairs = 0;
-      for (int i = wv; i < nl; i += CYC_NW) {
-        const int32_t v = in.ncol[ub + i];
-        const int64_t vb = in.nptr[v];
-        const int64_t pe = lower_index(in.ncol, vb, vb + in.dr[v], (int32_t)u);
-        for (int64_t p = vb + lane; p < pe; p += WAVE)
-          pairs += (unsigned long long)(hot_or_dev_add(hot, c, in.ncol[p], hot_base, CT(1)) &
-                                        LOC_LOW);
-      }
-      __syncthreads();
-      // pass 2: a middle vertex v shares each of its wedges with c[w] - 1
-      // others; the c[w]-th visit of w gives w its C(c[w], 2) cycles with
-      // u and clears the counter
-      for (int i = wv; i < nl; i += CYC_NW) {
-        const int32_t v = in.ncol[ub + i];
-        const int64_t vb = in.nptr[v];
-        const int64_t pe = lower_index(in.ncol, vb, vb + in.dr[v], (int32_t)u);
-        unsigned long long acc = 0;
-        for (int64_t p = vb + lane; p < pe; p += WAVE) {
-          const int32_t w = in.ncol[p];
-          const CT old = hot_or_dev_add(hot, c, w, hot_base, CT(1) << HALF);
-          const unsigned long long k = (unsigned long long)(old & LOC_LOW);
-          acc += k - 1;
-          if ((unsigned long long)(old >> HALF) == k - 1) {
-            if (w >= hot_base) atomicExch(&hot[w - hot_base], CT(0));
-            else atomicExch(&c[w], CT(0));
-            if (k >= 2) atomicAdd(&L.N8[w], k * (k - 1) / 2);
-          }
-        }
-        acc = group_sum<WAVE>(acc);
-        if (lane == 0 && acc) atomicAdd(&L.N8[v], acc);
-      }
-      block_add_u64<CYC_NT>(&L.N8[u], pairs);
-    }
-  }
-}
-
 __device__ __forceinline__ __int128 c3(__int128 d) { return d >= 3 ? d * (d - 1) * (d - 2) / 6 : 0; }
 
 template <int G>
@@ -495,12 +406,12 @@ __global__ void k_loc_dplus_max(const int32_t* __restrict__ dplus, int64_t n,
 }  // namespace
 
 // Orbit counts of the prepared graph P (t complete) into out (uint64[n][11],
-// device memory, caller's vertex ids).  arrays: 8 n words; cscr: the 4-cycle
-// counters, cblocks x n of 32 bits (64 when wide: degrees of 2^16 and more); gscr: the bitmap slices of out-degrees above
-// the LDS bound (kmax > LOC_K_LDS), gblocks slices.
+// device memory, caller's vertex ids).  arrays: 8 n words; cycles: the 4-cycle
+// stage, adding its credits to the words from 5 n on; gscr: the bitmap slices
+// of out-degrees above the LDS bound (kmax > LOC_K_LDS), gblocks slices.
 void local_orbits(const Prep& P, const Classes& C, Scal* scal, unsigned long long* arrays,
-                  void* cscr, bool wide, int cblocks, unsigned long long* gscr, int gblocks,
-                  int kmax, unsigned long long* out, int num_cu, hipStream_t s) {
+                  const Launch& cycles, unsigned long long* gscr, int gblocks, int kmax,
+                  unsigned long long* out, int num_cu, hipStream_t s) {
   const int64_t n = P.n;
   LocIn in{P.nptr, P.optr, P.ncol, P.dr, P.dlo, P.dplus, P.t, P.perm, n};
   LocArrays L{arrays,         arrays + n,     arrays + 2 * n, arrays + 3 * n,
@@ -525,15 +436,7 @@ void local_orbits(const Prep& P, const Classes& C, Scal* scal, unsigned long lon
         in, L, std::min<int64_t>(C.bound[5], n), LOC_K_LDS + 1, kmax, gscr, stride,
         &scal->work[1], scal);
   }
-  if (cblocks > 0) {
-    fill_u32(cscr, 0, (size_t)cblocks * (size_t)n * (wide ? 2 : 1), s);
-    if (wide)
-      k_loc_cycles<unsigned long long><<<(unsigned)cblocks, CYC_NT, 0, s>>>(
-          in, C.r1, L, reinterpret_cast<unsigned long long*>(cscr), &scal->work[2]);
-    else
-      k_loc_cycles<unsigned int><<<(unsigned)cblocks, CYC_NT, 0, s>>>(
-          in, C.r1, L, reinterpret_cast<unsigned int*>(cscr), &scal->work[2]);
-  }
+  cycles(s);
   if (b64 > 0) k_loc_final<8><<<grid_for(b64, 8), 256, 0, s>>>(in, 0, b64, L, out, scal);
   if (n > b64) k_loc_final<64><<<grid_for(n - b64, 64), 256, 0, s>>>(in, b64, n, L, out, scal);
 }
