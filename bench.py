@@ -63,9 +63,9 @@ WORKLOADS = {
 TRI_SLOTS = {1: "tri_global", 2: "tri_1024", 3: "tri_512", 4: "tri_256", 5: "tri_128",
              6: "tri_wave"}
 KERNEL_SYMBOL = {
-    "tri_global": "k_tri_global", "tri_1024": "k_tri_lds<1024, 256>",
-    "tri_512": "k_tri_lds<512, 256>", "tri_256": "k_tri_lds<256, 256>",
-    "tri_128": "k_tri_lds<128, 256>", "tri_wave": "k_tri_lds<64, 64>",
+    "tri_global": "k_tri_global", "tri_1024": "k_tri_large<1024, 256>",
+    "tri_512": "k_tri_lds<512, 512, false>", "tri_256": "k_tri_lds<256, 256, false>",
+    "tri_128": "k_tri_lds<128, 128, false>", "tri_wave": "k_tri_lds<64, 64, false>",
     "c4_window": "k_c4_window", "c4_med": "k_c4_filter<256, 8, 17, 15, 128, false, false>",
     "c4_hash": "k_c4_tiny<false>", "closure": "k_closure", "c4_plan": "k_c4_plan",
     "build": "(CSR builder kernels)", "tri_hubs": "k_hub_insert", "c4_desc": "k_c4_desc",

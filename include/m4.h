@@ -238,7 +238,7 @@ int m4_count_orbits4(m4_ctx* ctx, const m4_csr* g, const m4_opts* opts, uint64_t
  * context's tuning is unchanged. */
 typedef struct {
   int32_t tri_wave_max;  /* single graph: owners with out-degree <= this use one
-                            64-thread workgroup (2..64, default 32), while the
+                            64-thread workgroup (2..64, default 64), while the
                             out-lists (4 m bytes) fit in the 256 MiB Infinity
                             Cache                                              */
   int32_t c4_light_max;  /* single graph: owners with wedge bound <= this use the
@@ -252,14 +252,14 @@ typedef struct {
                             hash table of their out-list, and a triangle owner
                             probes it for its later out-neighbours instead of
                             scanning the list when that is cheaper (0 = never,
-                            else 4..65536, default 32)                        */
+                            else 4..65536, default 128)                        */
   int32_t c4_med_max;    /* single graph: owners with wedge bound in
                             (c4_light_max, c4_med_max] use the medium LDS
                             filter, heavier ones the counter windows (0 = no
                             medium bucket, else up to 12288, default 12288)   */
   int32_t probe_w;       /* single graph: a triangle row is probed in the hub
                             table when probe_w * (probes) < 3 * (elements a
-                            scan would read) (1..256, default 4), while the
+                            scan would read) (1..256, default 16), while the
                             hub tables fit in the 256 MiB Infinity Cache     */
   int32_t c4_med_win;    /* single graph: an owner with wedge bound in
                             (12288, 65536] also uses the medium filter when
@@ -283,7 +283,7 @@ typedef struct {
                             16384)                                            */
   int32_t probe_w_far;   /* single graph: probe_w when the hub tables exceed
                             the Infinity Cache, so that a probe is a line
-                            read from HBM (1..256, default 16)                */
+                            read from HBM (1..256, default 64)                */
   int32_t tri_wave_far;  /* single graph: tri_wave_max when the out-lists
                             exceed the Infinity Cache (2..64, default 64)     */
 } m4_tuning;

@@ -567,15 +567,15 @@ extern "C" int m4_count_orbits4(m4_ctx* ctx, const m4_csr* g, const m4_opts* o,
     ctx->big.ensure(bytes, s);
     return ctx->big.ptr;
   };
-  tri_run(P, ctx->scal, tu, flags, 0, at, s, ctx->num_cu, big, nullptr);
+  TriCredits credits;
+  tri_plan(P, ctx->scal, tu, flags, 0, at, s, ctx->num_cu, big, nullptr, &credits)(s);
   // statistics (8 n words) and the bitmap slices of out-degrees above the
-  // LDS bound in big2
-  const int kmax = local_dplus_max(P, ctx->scal, s);
+  // triangle stage's LDS bound in big2
   const size_t arr_bytes = align256((size_t)n * 8 * 8);
   int gblocks = 0;
   size_t g_bytes = 0;
-  if (kmax > 512) {
-    const size_t per = local_glob_stride_words(kmax) * 8;
+  if (credits.kmax > 0) {
+    const size_t per = local_glob_stride_words(credits.kmax) * 8;
     gblocks = (int)std::max<size_t>(1, std::min<size_t>((size_t(1) << 30) / per, 64));
     g_bytes = (size_t)gblocks * per;
   }
@@ -592,9 +592,9 @@ extern "C" int m4_count_orbits4(m4_ctx* ctx, const m4_csr* g, const m4_opts* o,
     ctx->tout.ensure(out_bytes, s);
     dst = reinterpret_cast<unsigned long long*>(ctx->tout.ptr);
   }
-  local_orbits(P, C, ctx->scal, arrays, cycles,
+  local_orbits(P, C, ctx->scal, arrays, cycles, credits,
                gblocks ? reinterpret_cast<unsigned long long*>(ctx->big2.ptr + arr_bytes) : nullptr,
-               gblocks, kmax, dst, ctx->num_cu, s);
+               gblocks, dst, ctx->num_cu, s);
   if (!g->on_device) M4_HIP(hipMemcpyAsync(orbits, dst, out_bytes, hipMemcpyDeviceToHost, s));
   M4_HIP(hipMemcpyAsync(ctx->scal_host, ctx->scal, kScalHead, hipMemcpyDeviceToHost, s));
   M4_HIP(hipStreamSynchronize(s));

@@ -124,21 +124,21 @@ struct Arena {
 };
 
 struct Tuning {
-  int tri_wave_max = 32;    // <= WAVE
+  int tri_wave_max = 64;    // <= WAVE
   int c4_light_max = 2048;  // wedge bound for the hash bucket
   int c4_med_max = 12288;   // wedge bound for the one-pass medium hash (0: no medium bucket)
   int grid_mult = 8;        // persistent blocks per CU for light kernels
   int batch_variant = 0;    // batched kernel: 0 = 1024 threads / 96 KiB, 1 = 512 / 40 KiB
   int batch_light = 128;    // batched kernel: wedge bound of the wavefront hash
-  int hub_min = 32;         // out-degree from which a vertex gets a hub table (0: none)
-  int probe_w = 4;          // weight of a hub-table probe against a scanned element (x 1/3)
+  int hub_min = 128;        // out-degree from which a vertex gets a hub table (0: none)
+  int probe_w = 16;         // weight of a hub-table probe against a scanned element (x 1/3)
   int c4_med_win = 64;      // ranged medium owners: 16 windows >= this per range (0: none)
   int c4_bin_win = 6;       // owners above the one-pass medium bound whose endpoints span at
                             // least this many counter windows take the large filter (0: never)
   int c4_bin_cap = 0;       // candidates one class of a large filtered owner is planned for
                             // (0: 3/4 of its table)
   int c4_bin_dense = 16384; // endpoints per window from which an owner keeps dense windows (0: never)
-  int probe_w_far = 16;     // probe_w when the hub tables do not fit in the Infinity Cache
+  int probe_w_far = 64;     // probe_w when the hub tables do not fit in the Infinity Cache
   int tri_wave_far = 64;    // tri_wave_max when the out-lists do not fit in the Infinity Cache
   // weights of the anchor-selection objective, from stage times measured on
   // the MI355X over graphs of 10^2 to 10^7 edges: ns per wedge endpoint
@@ -240,9 +240,18 @@ using Launch = std::function<void(hipStream_t)>;
 size_t tri_tmp_bytes(int64_t n, int64_t nnz, int dplus_max_bound);
 // big_scratch(bytes) returns device memory for the hub tables and for owners
 // whose bitmap does not fit in LDS (only called when those exist).
+// credits, if given, takes the launch that adds the per-vertex credits of the
+// owners with out-degree up to 512 (after the count's launch: t complete, the
+// workspace and scratch kept) and a bound of the out-degrees if any is larger
+// (else 0).
+struct TriCredits {
+  int kmax = 0;
+  std::function<void(hipStream_t, unsigned long long* n12, unsigned long long* n14)> launch;
+};
 Launch tri_plan(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags, uint32_t cache_rows,
                 Arena& tmp, hipStream_t s, int num_cu,
-                const std::function<char*(size_t)>& big_scratch, KTimer* kt);
+                const std::function<char*(size_t)>& big_scratch, KTimer* kt,
+                TriCredits* credits = nullptr);
 inline void tri_run(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags,
                     uint32_t cache_rows, Arena& tmp, hipStream_t s, int num_cu,
                     const std::function<char*(size_t)>& big_scratch, KTimer* kt) {
@@ -251,10 +260,9 @@ inline void tri_run(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags,
 
 // m4_local.hip: per-vertex orbit counts of a prepared graph (t complete)
 void local_orbits(const Prep& P, const Classes& C, Scal* scal, unsigned long long* arrays,
-                  const Launch& cycles, unsigned long long* gscr, int gblocks, int kmax,
-                  unsigned long long* out, int num_cu, hipStream_t s);
+                  const Launch& cycles, const TriCredits& credits, unsigned long long* gscr,
+                  int gblocks, unsigned long long* out, int num_cu, hipStream_t s);
 size_t local_glob_stride_words(int kmax);
-int local_dplus_max(const Prep& P, Scal* scal, hipStream_t s);
 
 // m4_edge.hip: the cycle/path anchor basis chosen by the anchor-selection
 // objective (estimates in ns; edge = adjacent pairs of A_e x B_e)

@@ -32,10 +32,10 @@
 //
 // Kernels, after the CSR builder and the triangle stage (t_e complete):
 //   k_loc_rows     per vertex, G lanes a row: t_v, S_v and the N6, N10, N13 sums
-//   k_loc_cliques  per triangle owner u (lowest vertex): the induced subgraph
-//                  on N+(u) as bitmap rows (LDS up to out-degree 512, device
-//                  scratch beyond); every triangle credits its three vertices
-//                  for N12, every 4-clique (row ANDs) its four for N14
+//   triangle stage (m4_tri.hip, with credits; k_loc_cliques for out-degrees
+//                  above 512) per owner u (lowest vertex): the induced subgraph
+//                  on N+(u) as bitmap rows; every triangle credits its three
+//                  vertices for N12, every 4-clique its four for N14
 //   4-cycle stage  (m4_c4.hip, with credits) per owner u (highest vertex) the
 //                  wedges c[w] of every endpoint w; u and w gain C(c[w], 2),
 //                  a middle vertex v the c[w] - 1 other middles of its wedge
@@ -52,8 +52,7 @@ namespace {
 
 constexpr int LOC_NT = 256;
 constexpr int LOC_NW = LOC_NT / WAVE;
-constexpr int LOC_K_LDS = 512;             // out-degree bound of the LDS bitmap
-constexpr int LOC_W_LDS = LOC_K_LDS / 64;  // its words per row
+constexpr int LOC_K_LDS = 512;             // largest out-degree the triangle stage credits
 constexpr int LOC_TRI_CHUNK = 16;          // triangle owners per grab
 constexpr int ERR_LOCAL = 8;               // an orbit inverse went negative
 
@@ -166,65 +165,34 @@ __global__ __launch_bounds__(256) void k_loc_rows(LocIn in, int64_t r_lo, int64_
   }
 }
 
-// A word of the clique kernel's bitmap or credit arrays, written by atomics of
-// other wavefronts: from LDS, or from device scratch past the CU's L1 (the
-// atomics are performed in the L2).
-template <bool GLOB>
-__device__ __forceinline__ unsigned long long ld_word(const unsigned long long* p) {
-  if (GLOB) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return *p;
+// A word of the clique kernel's bitmap, credit arrays or bit lists, written by
+// other lanes or wavefronts: the device-scope load skips the CU's L1 (atomics
+// are performed in the L2).
+template <typename T>
+__device__ __forceinline__ T ld_fresh(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-
-// A wavefront's bit list: in LDS, or in device scratch (written and read by
-// the same wavefront; the device-scope loads skip the L1).
-template <bool GLOB>
-__device__ __forceinline__ int ld_list(const int32_t* p) {
-  if (GLOB) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return *p;
-}
-template <bool GLOB>
 __device__ __forceinline__ void wave_list_sync() {
-  if (GLOB) __threadfence();
+  __threadfence();
   wave_sync();
 }
 
-// Triangle owners u (their lowest vertex) with out-degree k in [k_lo, k_hi],
-// ranks from r_start up, LOC_TRI_CHUNK per grab.  Row i of the bitmap holds
-// bit j when a[j] is in N+(a[i]), a = N+(u) (so j > i: rows are the
-// induced subgraph's out-lists).  GLOB keeps the bitmap, the credit arrays
-// and a in a per-block slice of device scratch (stride words).
-template <bool GLOB>
+// Triangle owners u (their lowest vertex) with out-degree k in (LOC_K_LDS,
+// k_hi], ranks from r_start up, LOC_TRI_CHUNK per grab (smaller out-degrees
+// are credited by the triangle stage's own kernels).  Row i of the bitmap
+// holds bit j when a[j] is in N+(a[i]), a = N+(u) (so j > i: rows are the
+// induced subgraph's out-lists); bitmap, credit arrays and a lie in a
+// per-block slice of device scratch (stride words).
 __global__ __launch_bounds__(LOC_NT) void k_loc_cliques(LocIn in, LocArrays L, int64_t r_start,
-                                                        int k_lo, int k_hi,
-                                                        unsigned long long* gscr, int64_t stride,
-                                                        unsigned int* work, Scal* scal) {
-  __shared__ unsigned long long s_bits[GLOB ? 1 : LOC_K_LDS * LOC_W_LDS];
-  __shared__ unsigned long long s_c12[GLOB ? 1 : LOC_K_LDS], s_c14[GLOB ? 1 : LOC_K_LDS];
-  __shared__ int32_t s_a[GLOB ? 1 : LOC_K_LDS];
-  __shared__ int32_t s_list[GLOB ? 1 : LOC_NW * LOC_K_LDS];
+                                                        int k_hi, unsigned long long* gscr,
+                                                        int64_t stride, unsigned int* work) {
   __shared__ int64_t s_g;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = tid / WAVE;
-  unsigned long long* bits;
-  unsigned long long *c12, *c14;
-  int32_t *a, *list;
-  int64_t list_cap;
-  if (GLOB) {
-    unsigned long long* base = gscr + (int64_t)blockIdx.x * stride;
-    const int64_t W = (k_hi + 63) / 64;
-    bits = base;
-    c12 = base + (int64_t)k_hi * W;
-    c14 = c12 + k_hi;
-    a = reinterpret_cast<int32_t*>(c14 + k_hi);
-    list = a + k_hi;
-    list_cap = k_hi;
-  } else {
-    bits = s_bits;
-    c12 = s_c12;
-    c14 = s_c14;
-    a = s_a;
-    list = s_list;
-    list_cap = LOC_K_LDS;
-  }
+  unsigned long long* bits = gscr + (int64_t)blockIdx.x * stride;
+  unsigned long long* c12 = bits + (int64_t)k_hi * ((k_hi + 63) / 64);
+  unsigned long long* c14 = c12 + k_hi;
+  int32_t* a = reinterpret_cast<int32_t*>(c14 + k_hi);
+  int32_t* lst = a + k_hi + (int64_t)wv * k_hi;  // the wavefront's bit list
   for (;;) {
     if (tid == 0) s_g = (int64_t)atomicAdd(work, 1u) * LOC_TRI_CHUNK + r_start;
     __syncthreads();
@@ -234,7 +202,7 @@ __global__ __launch_bounds__(LOC_NT) void k_loc_cliques(LocIn in, LocArrays L, i
     const int64_t u1 = u0 + LOC_TRI_CHUNK < in.n ? u0 + LOC_TRI_CHUNK : in.n;
     for (int64_t u = u0; u < u1; u++) {
       const int k = in.dplus[u];
-      if (k < 2 || k < k_lo || k > k_hi) continue;
+      if (k <= LOC_K_LDS || k > k_hi) continue;
       const int W = (k + 63) / 64;
       const int64_t ub = in.nptr[u] + in.dlo[u], oe = in.optr[u];
       for (int i = tid; i < k; i += LOC_NT) {
@@ -277,11 +245,10 @@ __global__ __launch_bounds__(LOC_NT) void k_loc_cliques(LocIn in, LocArrays L, i
       // every bit j of row i.  A wavefront lists row i's bits (each lane
       // its words' bits at its offset of a wave prefix), then its lanes
       // take the listed j's.
-      int32_t* lst = list + (int64_t)wv * list_cap;
       for (int i = wv; i < k; i += LOC_NW) {
         const unsigned long long* ri = bits + (int64_t)i * W;
         int mine = 0;
-        for (int w = lane; w < W; w += WAVE) mine += __popcll(ld_word<GLOB>(ri + w));
+        for (int w = lane; w < W; w += WAVE) mine += __popcll(ld_fresh(ri + w));
         int incl = mine;
 #pragma unroll
         for (int o = 1; o < WAVE; o <<= 1) {
@@ -291,20 +258,20 @@ __global__ __launch_bounds__(LOC_NT) void k_loc_cliques(LocIn in, LocArrays L, i
         const int total = __shfl(incl, WAVE - 1, WAVE);
         int q = incl - mine;
         for (int w = lane; w < W; w += WAVE) {
-          unsigned long long m = ld_word<GLOB>(ri + w);
+          unsigned long long m = ld_fresh(ri + w);
           while (m) {
             lst[q++] = w * 64 + __builtin_ctzll(m);
             m &= m - 1;
           }
         }
-        wave_list_sync<GLOB>();
+        wave_list_sync();
         unsigned long long ci = 0;
         for (int e = lane; e < total; e += WAVE) {
-          const int jx = ld_list<GLOB>(lst + e);
+          const int jx = ld_fresh(lst + e);
           const unsigned long long* rj = bits + (int64_t)jx * W;
           unsigned long long cj = 0;
           for (int y = jx >> 6; y < W; y++) {
-            unsigned long long andw = ld_word<GLOB>(ri + y) & ld_word<GLOB>(rj + y);
+            unsigned long long andw = ld_fresh(ri + y) & ld_fresh(rj + y);
             cj += (unsigned long long)__popcll(andw);
             while (andw) {
               const int lx = y * 64 + __builtin_ctzll(andw);
@@ -322,11 +289,11 @@ __global__ __launch_bounds__(LOC_NT) void k_loc_cliques(LocIn in, LocArrays L, i
         if (lane == 0 && ci) atomicAdd(&c14[i], ci);
         // the list is rewritten for the next row only after every lane
         // has read it
-        wave_list_sync<GLOB>();
+        wave_list_sync();
       }
       __syncthreads();
       for (int i = tid; i < k; i += LOC_NT) {
-        const unsigned long long x12 = ld_word<GLOB>(c12 + i), x14 = ld_word<GLOB>(c14 + i);
+        const unsigned long long x12 = ld_fresh(c12 + i), x14 = ld_fresh(c14 + i);
         if (x12) atomicAdd(&L.N12[a[i]], x12);
         if (x14) atomicAdd(&L.N14[a[i]], x14);
       }
@@ -393,31 +360,21 @@ __global__ __launch_bounds__(256) void k_loc_final(LocIn in, int64_t r_lo, int64
   }
 }
 
-__global__ void k_loc_dplus_max(const int32_t* __restrict__ dplus, int64_t n,
-                                unsigned int* __restrict__ out) {
-  unsigned int k = 0;
-  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
-       v += (int64_t)gridDim.x * blockDim.x)
-    k = std::max(k, (unsigned int)dplus[v]);
-  for (int o = WAVE / 2; o > 0; o >>= 1) k = std::max(k, (unsigned int)__shfl_xor((int)k, o, WAVE));
-  if ((threadIdx.x & (WAVE - 1)) == 0 && k) atomicMax(out, k);
-}
-
 }  // namespace
 
 // Orbit counts of the prepared graph P (t complete) into out (uint64[n][11],
 // device memory, caller's vertex ids).  arrays: 8 n words; cycles: the 4-cycle
-// stage, adding its credits to the words from 5 n on; gscr: the bitmap slices
-// of out-degrees above the LDS bound (kmax > LOC_K_LDS), gblocks slices.
+// stage, adding its credits to the words from 5 n on; credits: the triangle
+// stage's; gscr: gblocks bitmap slices for the out-degrees above its LDS bound
+// (credits.kmax > 0).
 void local_orbits(const Prep& P, const Classes& C, Scal* scal, unsigned long long* arrays,
-                  const Launch& cycles, unsigned long long* gscr, int gblocks, int kmax,
-                  unsigned long long* out, int num_cu, hipStream_t s) {
+                  const Launch& cycles, const TriCredits& credits, unsigned long long* gscr,
+                  int gblocks, unsigned long long* out, int num_cu, hipStream_t s) {
   const int64_t n = P.n;
   LocIn in{P.nptr, P.optr, P.ncol, P.dr, P.dlo, P.dplus, P.t, P.perm, n};
   LocArrays L{arrays,         arrays + n,     arrays + 2 * n, arrays + 3 * n,
               arrays + 4 * n, arrays + 5 * n, arrays + 6 * n, arrays + 7 * n};
   fill_u32(arrays, 0, (size_t)n * 16, s);
-  fill_u32(&scal->work[0], 0, 8, s);
   const int64_t b64 = std::min<int64_t>(C.bound[4], n);  // degree <= 64: 8 lanes a row
   const unsigned cap = (unsigned)num_cu * 64;
   auto grid_for = [&](int64_t rows, int G) {
@@ -425,31 +382,16 @@ void local_orbits(const Prep& P, const Classes& C, Scal* scal, unsigned long lon
   };
   if (b64 > 0) k_loc_rows<8><<<grid_for(b64, 8), 256, 0, s>>>(in, 0, b64, L, scal);
   if (n > b64) k_loc_rows<64><<<grid_for(n - b64, 64), 256, 0, s>>>(in, b64, n, L, scal);
-  // triangle owners have out-degree >= 2, so degree >= 2
-  const int64_t r_tri = std::min<int64_t>(C.bound[0], n);
-  k_loc_cliques<false><<<(unsigned)(num_cu * 4), LOC_NT, 0, s>>>(in, L, r_tri, 2, LOC_K_LDS,
-                                                                 nullptr, 0, &scal->work[0], scal);
-  if (kmax > LOC_K_LDS && gblocks > 0) {
-    // out-degree above 512 needs degree above 256
-    const int64_t stride = (int64_t)local_glob_stride_words(kmax);
-    k_loc_cliques<true><<<(unsigned)gblocks, LOC_NT, 0, s>>>(
-        in, L, std::min<int64_t>(C.bound[5], n), LOC_K_LDS + 1, kmax, gscr, stride,
-        &scal->work[1], scal);
+  credits.launch(s, L.N12, L.N14);
+  if (credits.kmax > LOC_K_LDS && gblocks > 0) {
+    // out-degree above 512 needs degree above 256; work[0] is no bucket's
+    const int64_t stride = (int64_t)local_glob_stride_words(credits.kmax);
+    k_loc_cliques<<<(unsigned)gblocks, LOC_NT, 0, s>>>(in, L, std::min<int64_t>(C.bound[5], n),
+                                                       credits.kmax, gscr, stride, &scal->work[0]);
   }
   cycles(s);
   if (b64 > 0) k_loc_final<8><<<grid_for(b64, 8), 256, 0, s>>>(in, 0, b64, L, out, scal);
   if (n > b64) k_loc_final<64><<<grid_for(n - b64, 64), 256, 0, s>>>(in, b64, n, L, out, scal);
-}
-
-int local_dplus_max(const Prep& P, Scal* scal, hipStream_t s) {
-  fill_u32(&scal->work[3], 0, 1, s);
-  const int64_t n = P.n;
-  k_loc_dplus_max<<<(unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 256), 4096)), 256,
-                    0, s>>>(P.dplus, n, &scal->work[3]);
-  unsigned int k = 0;
-  M4_HIP(hipMemcpyAsync(&k, &scal->work[3], 4, hipMemcpyDeviceToHost, s));
-  M4_HIP(hipStreamSynchronize(s));
-  return (int)k;
 }
 
 // per block: the bitmap (kmax rows of ceil(kmax / 64) words), the two

@@ -35,6 +35,14 @@ struct TriArgs {
   // hub tables: open-addressing tables of the out-lists of vertices with
   // out-degree >= hub_min (entry = key << 32 | position, empty = ~0)
   const int32_t* hoff;    // table offset per vertex, -1 without a table
+  // {start, first oriented edge} of the out-list of every vertex and of the
+  // one past the last (null in partitions: the separate arrays are read); its
+  // length is the next record's edge less its own
+  const int2* list;
+  // per-vertex credits (orbit counts): triangles' opposite edges less one,
+  // 4-cliques; null when counting
+  unsigned long long* n12;
+  unsigned long long* n14;
   const unsigned long long* htab;
   int hub_min;            // 0: no tables
   int probe_w;            // row i is probed when probe_w (k-1-i) < 3 |N+(a[i])|
@@ -57,6 +65,21 @@ template <typename T>
 __device__ __forceinline__ T ld(const T* p, bool fresh) {
   if (fresh) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return *p;
+}
+
+// The out-list of v: start in ncol, first oriented edge, length.  One 16-byte
+// read from the packed records instead of gathers from four arrays, which
+// fetch a line each.
+struct OutList {
+  int32_t st, oe, len;
+};
+__device__ __forceinline__ OutList out_list(const TriArgs& A, int32_t v) {
+  if (A.list) {
+    int4 r;
+    __builtin_memcpy(&r, A.list + v, sizeof(r));  // records are 8-byte aligned
+    return OutList{r.x, r.y, r.w - r.y};
+  }
+  return OutList{(int32_t)(A.nptr[v] + A.dlo[v]), (int32_t)A.optr[v], A.dplus[v]};
 }
 
 // |C(u, a[i]) & N+(a[p])| recomputed from the lists, for frontiers that are
@@ -82,8 +105,6 @@ __device__ __forceinline__ uint64_t k4_recompute(const int32_t* ncol, const int3
 
 // One owner processed by NT threads with per-owner arrays in `a..colcnt`
 // (LDS or global) and bitmap rows of W words each in `B`.
-// HASH: positions of the out-list are found through an LDS hash table
-// (hk/hv, 2H >= 2k slots) instead of a binary search over a[].
 // PROBE: a row i whose head v = a[i] has a hub table is resolved by probing
 // that table for the later entries a[i+1..k) when that is cheaper than
 // scanning N+(v): k-1-i probes, each weighted probe_w / 3 scanned elements
@@ -96,7 +117,7 @@ __device__ __forceinline__ uint64_t k4_recompute(const int32_t* ncol, const int3
 // owner's out-neighbours v, the elements a scanning intersection reads),
 // wread (4-byte words this routine reads from the out-lists and hub tables:
 // one per scanned element, two per 8-byte table slot probed).
-template <int NT, bool FRESH, bool WAVE_ONLY = false, bool HASH = false, bool PROBE = false>
+template <int NT, bool FRESH, bool WAVE_ONLY = false, bool PROBE = false>
 __device__ __forceinline__ void tri_owner(const TriArgs& A, int32_t u, const int tid, int32_t* a,
                                           int32_t* sst,
                                           int32_t* soe, int32_t* slen, int32_t* spref,
@@ -105,53 +126,30 @@ __device__ __forceinline__ void tri_owner(const TriArgs& A, int32_t u, const int
                                           unsigned long long& steps, unsigned long long& looks,
                                           unsigned long long& hits, unsigned long long& ksum,
                                           unsigned long long& wread,
-                                          unsigned long long& escan, int32_t* hk = nullptr,
-                                          int16_t* hv = nullptr) {
-  const int k = A.dplus[u];
-  const int64_t rb = A.nptr[u] + A.dlo[u];
-  const int64_t oe_u = A.optr[u];
+                                          unsigned long long& escan) {
+  const OutList lu = out_list(A, u);
+  const int k = lu.len;
+  const int64_t rb = lu.st;
+  const int64_t oe_u = lu.oe;
   const int W = (k + 63) >> 6;
   if (tid == 0) ksum += (unsigned long long)k;
   for (int i = tid; i < k; i += NT) {
     int32_t v = A.ncol[rb + i];
     a[i] = v;
-    const int L = A.dplus[v];
-    int32_t st = (int32_t)(A.nptr[v] + A.dlo[v]);
+    const OutList lv = out_list(A, v);
+    const int L = lv.len;
+    int32_t st = lv.st;
     if (PROBE && A.hub_min > 0 && L >= A.hub_min && A.probe_w * (k - 1 - i) < 3 * L) {
       const int32_t off = A.hoff[v];
       if (off >= 0) st = -1 - off;  // probe row: table offset, negated
     }
     sst[i] = st;
-    soe[i] = (int32_t)A.optr[v];
+    soe[i] = lv.oe;
     slen[i] = L;
     colcnt[i] = 0;
   }
   for (int i = tid; i < k * W; i += NT) B[i] = 0;
-  int H = 16, hshift = 28;
-  if (HASH) {
-    while (H < 2 * k) {
-      H <<= 1;
-      hshift--;
-    }
-    for (int i = tid; i < H; i += NT) hk[i] = -1;
-  }
   TRI_SYNC();
-  if (HASH) {
-    // k distinct keys in H >= 2k slots: a free slot is met within H probes
-    for (int i = tid; i < k; i += NT) {
-      const int32_t key = a[i];
-      uint32_t h = ((uint32_t)key * 0x9E3779B1u) >> hshift;
-      int probes = 0;
-      while (atomicCAS(&hk[h], -1, key) != -1) {
-        h = (h + 1) & (uint32_t)(H - 1);
-        if (++probes >= H) {
-          atomicOr(A.err, ERR_PROBE);
-          break;
-        }
-      }
-      if (probes < H) hv[h] = (int16_t)i;
-    }
-  }
   // exclusive prefix of the row work of a[0..k) into spref[0..k]: |N+(a[i])|
   // elements for a scanned row, k-1-i probes for a probed row
   {
@@ -248,25 +246,6 @@ __device__ __forceinline__ void tri_owner(const TriArgs& A, int32_t u, const int
           wread += 2;
         }
         if (pos < 0) p = -1;
-      } else if (HASH) {
-        // x > a[ir], so a hit is always a position after ir
-        pos = cj[r];
-        wread++;
-        uint32_t h = ((uint32_t)x * 0x9E3779B1u) >> hshift;
-        p = -1;
-        for (int probes = 0;; probes++) {
-          const int32_t key = hk[h];
-          if (key == x) {
-            p = hv[h];
-            break;
-          }
-          if (key == -1) break;
-          if (probes >= H) {
-            atomicOr(A.err, ERR_PROBE);
-            break;
-          }
-          h = (h + 1) & (uint32_t)(H - 1);
-        }
       } else {
         pos = cj[r];
         wread++;
@@ -315,8 +294,8 @@ __device__ __forceinline__ void tri_owner(const TriArgs& A, int32_t u, const int
           k4acc += c;
         } else {
           // probed rows keep a table offset in sst[]: take the list start again
-          const int64_t si = (PROBE && sst[i] < 0) ? A.nptr[a[i]] + A.dlo[a[i]] : sst[i];
-          const int64_t sp = (PROBE && sst[p] < 0) ? A.nptr[a[p]] + A.dlo[a[p]] : sst[p];
+          const int64_t si = (PROBE && sst[i] < 0) ? out_list(A, a[i]).st : sst[i];
+          const int64_t sp = (PROBE && sst[p] < 0) ? out_list(A, a[p]).st : sst[p];
           k4acc += k4_recompute(A.ncol, a, k, p, si, slen[i], sp, slen[p]);
         }
       }
