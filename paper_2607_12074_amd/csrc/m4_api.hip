@@ -301,7 +301,7 @@ void run_resident(m4_ctx* c, const int64_t* rp, const int32_t* col, int64_t n, i
   build_prep(rp, col, n, nnz, (flags & M4_VALIDATE) != 0, P, C, c->scal, c->scal_host, a, s);
   if (kt) kt->end(M4_K_BUILD, s);
   // the cycle/path anchor basis (Section III-A): wedges or edge anchors
-  c->basis = choose_basis(P, tu, flags, o && o->device_budget_bytes > 0, c->scal, c->cost_pair, s);
+  c->basis = choose_basis(P, tu, flags, o && o->device_budget_bytes > 0, c->scal, c->cost_in, s);
   if (want_timing) M4_HIP(hipEventRecord(c->ev[1], s));
   auto big = [c, s](size_t bytes) -> char* {
     c->big.ensure(bytes, s);
@@ -446,6 +446,9 @@ extern "C" int m4_count_motifs4_ex(m4_ctx* ctx, const m4_csr* g, const m4_opts* 
   if (h.status != 0) return set_error(ctx, M4_EINTERNAL, "closure consistency check failed");
   for (int i = 0; i < 6; i++) out[i] = h.out[i];
   if (st) {
+    const bool budgeted = o && o->device_budget_bytes > 0;
+    if (ctx->basis.pending)
+      basis_costs(ctx->basis, tuning_for(ctx, o), g->n, budgeted, &h.stat[ST_COST]);
     fill_stats(ctx, h, st, timing);
     st->k_elems[M4_K_BUILD] = (uint64_t)g->nnz;
     st->k_rows[M4_K_BUILD] = (uint64_t)g->n;

@@ -88,7 +88,7 @@ struct m4_ctx {
   m4::BatchState* batch = nullptr;
   m4::PartState* part = nullptr;
   m4::BasisChoice basis;                  // cycle/path basis of the last resident count
-  unsigned long long cost_pair[2] = {0, 0};  // its objective's inputs, read back
+  unsigned long long cost_in[3] = {0, 0, 0};  // its objective's inputs, read back
   bool no_alloc = false;  // inside the allocation-free entry point
   // device bytes the context holds now (workspaces, batch buffers, Scal)
   size_t held_bytes() const;

@@ -42,12 +42,13 @@ __device__ __forceinline__ int64_t find_sorted(const int32_t* __restrict__ a, in
 // d(a) (each edge owned by its lower end scans the rows of the lower end's
 // neighbours).  The first pass reads degrees only and gives the wedge term
 // and a lower bound of the edge term (every neighbour has degree >= 1 and u
-// itself is in each neighbour's row: sum over u of d+(u) d(u)); the second
-// reads the rows and is run only when that bound does not settle the
+// itself is in each neighbour's row: sum over u of d+(u) d(u)) and the longest
+// row; the second reads the rows and is run only when those do not settle the
 // choice.
 __global__ void k_edge_cost(const int32_t* __restrict__ dr, const int32_t* __restrict__ dplus,
                             int64_t n, unsigned long long* __restrict__ out) {
   unsigned long long wedge = 0, lower = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) out[2] = (unsigned long long)dr[n - 1];
   for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n;
        u += (int64_t)gridDim.x * blockDim.x) {
     const int64_t d = dr[u];
@@ -125,35 +126,53 @@ __global__ __launch_bounds__(256) void k_edge_pairs(const int64_t* __restrict__ 
 
 }  // namespace
 
+// Eq. (1) over the two cycle/path bases: the triangle anchor, the recoverable
+// counts (closure yield: all six for both) and the reuse (none for either) are
+// shared and drop out; enumeration plus intersection work, each element
+// weighted by its measured cost on this device, plus a fixed stage cost
+// (launches and the host read-backs of the wedge plan) or the two serial
+// parts of the edge stage, and the halo term: the edge basis reads 2-hop
+// rows, which the halo partitions do not hold, so it is infinite under a
+// budget.  Edge / wedge stage, us of a whole call: 200 vertices and 800 edges
+// 352 / 367, 1000 and 8000 381 / 383, 2000 and 20000 475 / 402, a power law of
+// 512 and 2200 edges (longest row 170) 928 / 442, 10^5 and 2 10^5 edges
+// 1552 / 518.
+void basis_costs(BasisChoice& b, const Tuning& tu, int64_t n, bool budgeted,
+                 const unsigned long long* in) {
+  b.cost_wedge = tu.cost_wedge_ns * (double)in[0] + tu.cost_wedge_fixed_us * 1e3;
+  b.cost_edge = budgeted ? INFINITY
+                         : tu.cost_edge_ns * (double)in[1] + tu.cost_edge_owner_ns * (double)n +
+                               tu.cost_edge_row_ns * (double)in[2];
+}
+
 BasisChoice choose_basis(const Prep& P, const Tuning& tu, uint32_t flags, bool budgeted,
-                         Scal* scal, unsigned long long* host_pair, hipStream_t s) {
+                         Scal* scal, unsigned long long* in, hipStream_t s) {
   BasisChoice b;
-  host_pair[0] = host_pair[1] = 0;
+  in[0] = in[1] = in[2] = 0;
   const bool forced = (flags & (M4_BASIS_WEDGE | M4_BASIS_EDGE)) != 0;
   const unsigned grid = (unsigned)std::min<int64_t>(ceil_div(std::max<int64_t>(P.n, 1), 256), 4096);
   if (P.n > 0) {
     k_edge_cost<<<grid, 256, 0, s>>>(P.dr, P.dplus, P.n, &scal->stat[ST_COST]);
-    M4_HIP(hipMemcpyAsync(host_pair, &scal->stat[ST_COST], 16, hipMemcpyDeviceToHost, s));
+    // its owners alone cost the edge stage more than the fixed part of the
+    // wedge stage, and it scans at least an entry per wedge endpoint at the
+    // higher price: settled without waiting for the inputs (a read-back takes
+    // some 10 us of a call)
+    if (!forced && (budgeted || (tu.cost_edge_owner_ns * (double)P.n >= tu.cost_wedge_fixed_us * 1e3 &&
+                                 tu.cost_edge_ns >= tu.cost_wedge_ns))) {
+      b.pending = true;
+      return b;
+    }
+    M4_HIP(hipMemcpyAsync(in, &scal->stat[ST_COST], 24, hipMemcpyDeviceToHost, s));
     M4_HIP(hipStreamSynchronize(s));
   }
-  // Eq. (1) over the two cycle/path bases: the triangle anchor, the
-  // recoverable counts (closure yield: all six for both) and the reuse
-  // (none for either) are shared and drop out; enumeration plus
-  // intersection work, each element weighted by its measured cost on this
-  // device, plus a fixed stage cost (launches and the host read-backs of the
-  // wedge plan), and the halo term: the edge basis reads 2-hop rows, which
-  // the halo partitions do not hold, so it is infinite under a budget.
-  b.cost_wedge = tu.cost_wedge_ns * (double)host_pair[0] + tu.cost_wedge_fixed_us * 1e3;
-  b.cost_edge = tu.cost_edge_ns * (double)host_pair[1];  // a lower bound so far
-  if (budgeted) {
-    b.cost_edge = INFINITY;
-  } else if (P.n > 0 && (b.cost_edge < b.cost_wedge || forced)) {
+  basis_costs(b, tu, P.n, budgeted, in);  // for the edge basis a lower bound so far
+  if (!budgeted && P.n > 0 && (b.cost_edge < b.cost_wedge || forced)) {
     fill_u32(&scal->stat[ST_COST + 1], 0, 2, s);
     k_edge_scan_cost<<<grid, 256, 0, s>>>(P.nptr, P.ncol, P.dr, P.dplus, P.n,
                                           &scal->stat[ST_COST + 1]);
-    M4_HIP(hipMemcpyAsync(host_pair + 1, &scal->stat[ST_COST + 1], 8, hipMemcpyDeviceToHost, s));
+    M4_HIP(hipMemcpyAsync(in + 1, &scal->stat[ST_COST + 1], 8, hipMemcpyDeviceToHost, s));
     M4_HIP(hipStreamSynchronize(s));
-    b.cost_edge = tu.cost_edge_ns * (double)host_pair[1];
+    basis_costs(b, tu, P.n, budgeted, in);
   }
   if (flags & M4_BASIS_EDGE) b.edge = !budgeted;
   else if (flags & M4_BASIS_WEDGE) b.edge = false;

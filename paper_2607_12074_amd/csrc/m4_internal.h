@@ -29,8 +29,8 @@ enum Acc { ACC_K4 = 0, ACC_C4, ACC_S, ACC_P, ACC_PAW2, ACC_D, ACC_SUMT, ACC_N };
 // adjacent pairs of A_e x B_e over all edges (edge-anchor basis), in the
 // spare accumulator
 constexpr int ACC_Z = ACC_N;
-// ST_COST, ST_COST + 1: the anchor-selection inputs (wedge endpoints bound,
-// edge-basis row entries)
+// ST_COST to ST_COST + 2: the anchor-selection inputs (wedge endpoints bound,
+// edge-basis row entries, longest row)
 enum Stat { ST_STEPS = 0, ST_WEDGES, ST_LOOKUPS, ST_HITS, ST_COST, ST_N = 8 };
 
 // Triangle-owner buckets by out-degree k = d+(u).
@@ -142,9 +142,12 @@ struct Tuning {
   int tri_wave_far = 64;    // tri_wave_max when the out-lists do not fit in the Infinity Cache
   // weights of the anchor-selection objective, from stage times measured on
   // the MI355X over graphs of 10^2 to 10^7 edges: ns per wedge endpoint
-  // bound, fixed us of the wedge stage (its plan kernels and host
-  // read-backs), ns per row entry the edge basis scans
-  double cost_wedge_ns = 0.005, cost_wedge_fixed_us = 300.0, cost_edge_ns = 0.03;
+  // bound, fixed us of the wedge stage (what its plan kernels and host
+  // read-backs take beyond the edge stage's); ns per row entry the edge basis
+  // scans, per owner (the work counter they are taken from serves one in
+  // 12 ns) and per entry of the longest row (one thread scans it alone)
+  double cost_wedge_ns = 0.005, cost_wedge_fixed_us = 50.0, cost_edge_ns = 0.03;
+  double cost_edge_owner_ns = 12.0, cost_edge_row_ns = 1000.0;
 };
 
 // Optional per-launch HIP event pairs (M4_TIMING).
@@ -268,10 +271,14 @@ size_t local_glob_stride_words(int kmax);
 // objective (estimates in ns; edge = adjacent pairs of A_e x B_e)
 struct BasisChoice {
   bool edge = false;
+  bool pending = false;  // settled without the estimates: basis_costs() fills them in
   double cost_wedge = 0, cost_edge = 0;
 };
+// in[3]: the objective's inputs, read back where the choice needs them
 BasisChoice choose_basis(const Prep& P, const Tuning& tu, uint32_t flags, bool budgeted,
-                         Scal* scal, unsigned long long* host_pair, hipStream_t s);
+                         Scal* scal, unsigned long long* in, hipStream_t s);
+void basis_costs(BasisChoice& b, const Tuning& tu, int64_t n, bool budgeted,
+                 const unsigned long long* in);
 Launch edge_plan(const Prep& P, Scal* scal, uint32_t flags, int num_cu, KTimer* kt);
 
 // m4_c4.hip (binned, if given, is set when owners go to the large filter,
