@@ -274,6 +274,45 @@ Tuning tuning_for(const m4_ctx* c, const m4_opts* o) {
   return tu;
 }
 
+// The prepared graph and the two anchor stages' workspaces, side by side in
+// c->tmp; si: the host's copy of a small graph's plan, else null.
+struct StageWork {
+  TriWork tri;
+  C4Work c4;
+  const SmallInfo* si = nullptr;
+};
+
+// Clears the counters, and prepares the graph in P (whose arrays are carved):
+// graphs of up to SMALL_N vertices by the fused path, which plans both stages
+// too, others by build_prep, whose workspace overlaps the stages'.
+void prepare(m4_ctx* c, const int64_t* rp, const int32_t* col, int64_t n, int64_t nnz,
+             uint32_t flags, uint32_t cache_rows, const Tuning& tu, bool credit, hipStream_t s,
+             Prep& P, Classes& C, StageWork& w) {
+  P.n = n;
+  P.nnz = nnz;
+  P.m = nnz / 2;
+  const size_t c4_bytes = c4_tmp_bytes(n);
+  Arena at, ac;
+  at.base = c->tmp.ptr;
+  at.cap = c->tmp.cap - c4_bytes;
+  ac.base = c->tmp.ptr + at.cap;
+  ac.cap = c4_bytes;
+  w.tri = tri_work(P, tu, at);
+  w.c4 = c4_work(P, ac);
+  if (n <= SMALL_N) {
+    small_prep(rp, col, n, nnz, P, C, tu, flags, cache_rows, credit, w.tri, w.c4, c->scal,
+               c->scal_host, s);
+    w.si = &c->scal_host->small;
+    return;
+  }
+  fill_u32(c->scal, 0, sizeof(Scal) / 4, s);
+  fill_u32(P.t, 0, (size_t)P.m, s);
+  Arena a;
+  a.base = c->tmp.ptr;
+  a.cap = c->tmp.cap;
+  build_prep(rp, col, n, nnz, (flags & M4_VALIDATE) != 0, P, C, c->scal, c->scal_host, a, s);
+}
+
 // The resident single-graph pipeline.  Leaves the prepared graph in c->prep
 // (P) and the results in c->scal; the caller reads them back.
 void run_resident(m4_ctx* c, const int64_t* rp, const int32_t* col, int64_t n, int64_t nnz,
@@ -289,19 +328,15 @@ void run_resident(m4_ctx* c, const int64_t* rp, const int32_t* col, int64_t n, i
   const Tuning tu = tuning_for(c, o);
   c->prep.ensure(prep_bytes(n, nnz), s);
   P = carve_prep(c->prep.ptr, n, nnz);
-  fill_u32(c->scal, 0, sizeof(Scal) / 4, s);
-  if (nnz / 2) fill_u32(P.t, 0, (size_t)(nnz / 2), s);
-  if (want_timing) M4_HIP(hipEventRecord(c->ev[0], s));
   c->tmp.ensure(stage_tmp_bytes(n, nnz, 1, c->num_cu), s);
-  Arena a;
-  a.base = c->tmp.ptr;
-  a.cap = c->tmp.cap;
+  if (want_timing) M4_HIP(hipEventRecord(c->ev[0], s));
   Classes C{};
+  StageWork w;
   if (kt) kt->begin(M4_K_BUILD, s);
-  build_prep(rp, col, n, nnz, (flags & M4_VALIDATE) != 0, P, C, c->scal, c->scal_host, a, s);
+  prepare(c, rp, col, n, nnz, flags, cache_rows, tu, false, s, P, C, w);
   if (kt) kt->end(M4_K_BUILD, s);
   // the cycle/path anchor basis (Section III-A): wedges or edge anchors
-  c->basis = choose_basis(P, tu, flags, o && o->device_budget_bytes > 0, c->scal, c->cost_in, s);
+  c->basis = choose_basis(P, tu, flags, o && o->device_budget_bytes > 0, c->scal, c->cost_in, s, w.si);
   if (want_timing) M4_HIP(hipEventRecord(c->ev[1], s));
   auto big = [c, s](size_t bytes) -> char* {
     c->big.ensure(bytes, s);
@@ -319,17 +354,15 @@ void run_resident(m4_ctx* c, const int64_t* rp, const int32_t* col, int64_t n, i
   // 4-cycle owners take the large filter the stages run in order: its
   // workgroup holds all of the LDS of its CU, and sharing the CUs with the
   // triangle kernels measured slower.
-  const size_t c4_bytes = c4_tmp_bytes(n);
-  Arena at, ac;
-  at.base = c->tmp.ptr;
-  at.cap = c->tmp.cap - c4_bytes;
-  ac.base = c->tmp.ptr + at.cap;
-  ac.cap = c4_bytes;
-  Launch tri = tri_plan(P, c->scal, tu, flags, cache_rows, at, s, c->num_cu, big, kt);
+  // Small graphs run them in order too: the events cost more than the overlap
+  // gives.
+  Launch tri =
+      tri_plan(P, c->scal, tu, flags, cache_rows, w.tri, s, c->num_cu, big, kt, nullptr, w.si);
   bool binned = false;
   Launch c4 = c->basis.edge ? edge_plan(P, c->scal, flags, c->num_cu, kt)
-                            : c4_plan(P, C, c->scal, tu, flags, ac, s, c->num_cu, kt, big2, &binned);
-  if ((flags & M4_SERIAL) || binned) {
+                            : c4_plan(P, C, c->scal, tu, flags, w.c4, s, c->num_cu, kt, big2,
+                                      &binned, nullptr, w.si);
+  if ((flags & M4_SERIAL) || binned || w.si) {
     tri(s);
     if (want_timing) M4_HIP(hipEventRecord(c->ev[2], s));
     c4(s);
@@ -425,16 +458,11 @@ extern "C" int m4_count_motifs4_ex(m4_ctx* ctx, const m4_csr* g, const m4_opts* 
   if (needs_partition(ctx, g, o)) return count_partitioned(ctx, g, o, out, st);
   double h2d = 0;
   if (timing) M4_HIP(hipEventRecord(ctx->ev[5], s));
+  if (!g->on_device && g->row_ptr[g->n] != g->nnz)
+    return set_error(ctx, M4_ERANGE, "row_ptr[n] != nnz");
   const int64_t* rp;
   const int32_t* col;
   stage_input(ctx, g, s, &rp, &col, &h2d);
-  if (!g->on_device) {
-    // row_ptr[n] must equal nnz
-    int64_t last = 0;
-    M4_HIP(hipMemcpyAsync(&last, rp + g->n, 8, hipMemcpyDeviceToHost, s));
-    M4_HIP(hipStreamSynchronize(s));
-    if (last != g->nnz) return set_error(ctx, M4_ERANGE, "row_ptr[n] != nnz");
-  }
   if (timing) M4_HIP(hipEventRecord(ctx->ev[6], s));
   Prep P;
   run_resident(ctx, rp, col, g->n, g->nnz, o, s, P, timing);
@@ -485,21 +513,17 @@ extern "C" int m4_edge_triangles(m4_ctx* ctx, const m4_csr* g, const m4_opts* o,
   const Tuning tu = tuning_for(ctx, o);
   ctx->prep.ensure(prep_bytes(g->n, g->nnz), s);
   P = carve_prep(ctx->prep.ptr, g->n, g->nnz);
-  fill_u32(ctx->scal, 0, sizeof(Scal) / 4, s);
-  fill_u32(P.t, 0, (size_t)(g->nnz / 2), s);
   ctx->tmp.ensure(stage_tmp_bytes(g->n, g->nnz, 1, ctx->num_cu), s);
-  Arena a;
-  a.base = ctx->tmp.ptr;
-  a.cap = ctx->tmp.cap;
   Classes C{};
-  build_prep(rp, col, g->n, g->nnz, (flags & M4_VALIDATE) != 0, P, C, ctx->scal, ctx->scal_host,
-             a, s);
-  a.used = 0;
+  StageWork w;
+  const uint32_t cache_rows = o ? o->cache_rows : 0;
+  prepare(ctx, rp, col, g->n, g->nnz, flags, cache_rows, tu, false, s, P, C, w);
   auto big = [ctx, s](size_t bytes) -> char* {
     ctx->big.ensure(bytes, s);
     return ctx->big.ptr;
   };
-  tri_run(P, ctx->scal, tu, flags, o ? o->cache_rows : 0, a, s, ctx->num_cu, big, nullptr);
+  tri_plan(P, ctx->scal, tu, flags, cache_rows, w.tri, s, ctx->num_cu, big, nullptr, nullptr,
+           w.si)(s);
   uint32_t* dst = t_out;
   if (!g->on_device) {
     ctx->tout.ensure((size_t)g->nnz * 4, s);
@@ -537,41 +561,25 @@ extern "C" int m4_count_orbits4(m4_ctx* ctx, const m4_csr* g, const m4_opts* o,
     }
     return M4_OK;
   }
+  if (!g->on_device && g->row_ptr[n] != g->nnz)
+    return set_error(ctx, M4_ERANGE, "row_ptr[n] != nnz");
   const int64_t* rp;
   const int32_t* col;
   stage_input(ctx, g, s, &rp, &col, nullptr);
-  if (!g->on_device) {
-    int64_t last = 0;
-    M4_HIP(hipMemcpyAsync(&last, rp + n, 8, hipMemcpyDeviceToHost, s));
-    M4_HIP(hipStreamSynchronize(s));
-    if (last != g->nnz) return set_error(ctx, M4_ERANGE, "row_ptr[n] != nnz");
-  }
   const uint32_t flags = o ? (o->flags & M4_VALIDATE) : 0;
   const Tuning tu = tuning_for(ctx, o);
   ctx->prep.ensure(prep_bytes(n, g->nnz), s);
   Prep P = carve_prep(ctx->prep.ptr, n, g->nnz);
-  fill_u32(ctx->scal, 0, sizeof(Scal) / 4, s);
-  fill_u32(P.t, 0, (size_t)(g->nnz / 2), s);
   ctx->tmp.ensure(stage_tmp_bytes(n, g->nnz, 1, ctx->num_cu), s);
-  Arena a;
-  a.base = ctx->tmp.ptr;
-  a.cap = ctx->tmp.cap;
   Classes C{};
-  build_prep(rp, col, n, g->nnz, (flags & M4_VALIDATE) != 0, P, C, ctx->scal, ctx->scal_host, a,
-             s);
-  // the triangle and 4-cycle stages keep their workspaces side by side
-  const size_t c4_bytes = c4_tmp_bytes(n);
-  Arena at, ac;
-  at.base = ctx->tmp.ptr;
-  at.cap = ctx->tmp.cap - c4_bytes;
-  ac.base = ctx->tmp.ptr + at.cap;
-  ac.cap = c4_bytes;
+  StageWork w;
+  prepare(ctx, rp, col, n, g->nnz, flags, 0, tu, true, s, P, C, w);
   auto big = [ctx, s](size_t bytes) -> char* {
     ctx->big.ensure(bytes, s);
     return ctx->big.ptr;
   };
   TriCredits credits;
-  tri_plan(P, ctx->scal, tu, flags, 0, at, s, ctx->num_cu, big, nullptr, &credits)(s);
+  tri_plan(P, ctx->scal, tu, flags, 0, w.tri, s, ctx->num_cu, big, nullptr, &credits, w.si)(s);
   // statistics (8 n words) and the bitmap slices of out-degrees above the
   // triangle stage's LDS bound in big2
   const size_t arr_bytes = align256((size_t)n * 8 * 8);
@@ -588,8 +596,8 @@ extern "C" int m4_count_orbits4(m4_ctx* ctx, const m4_csr* g, const m4_opts* o,
     ctx->big3.ensure(bytes, s);
     return ctx->big3.ptr;
   };
-  const Launch cycles = c4_plan(P, C, ctx->scal, tu, flags, ac, s, ctx->num_cu, nullptr, big3,
-                                nullptr, arrays + 5 * n);
+  const Launch cycles = c4_plan(P, C, ctx->scal, tu, flags, w.c4, s, ctx->num_cu, nullptr, big3,
+                                nullptr, arrays + 5 * n, w.si);
   unsigned long long* dst = reinterpret_cast<unsigned long long*>(orbits);
   if (!g->on_device) {
     ctx->tout.ensure(out_bytes, s);

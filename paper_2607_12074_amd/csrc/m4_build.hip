@@ -348,16 +348,19 @@ void sort_rows(const int64_t* rp, const int32_t* col, const int32_t* perm, const
 int row_class_count() { return kNThr; }
 const int* row_class_thresholds() { return kThr; }
 
+void validate_csr(const int64_t* rp, const int32_t* col, int64_t n, int64_t nnz, Scal* scal,
+                  hipStream_t s) {
+  k_validate_rows<<<blocks_for(n + 1, 256), 256, 0, s>>>(rp, n, nnz, scal);
+  if (nnz > 0) k_validate_entries<<<blocks_for(nnz, 256), 256, 0, s>>>(rp, col, n, nnz, scal);
+}
+
 void degree_order(const int64_t* rp, const int32_t* col, int64_t n, int64_t nnz, bool validate,
                   Prep& P, Classes& C, Scal* scal, Scal* scal_host, Arena& tmp, hipStream_t s) {
   P.n = n;
   P.nnz = nnz;
   P.m = nnz / 2;
   const int NT = 256;
-  if (validate) {
-    k_validate_rows<<<blocks_for(n + 1, NT), NT, 0, s>>>(rp, n, nnz, scal);
-    if (nnz > 0) k_validate_entries<<<blocks_for(nnz, NT), NT, 0, s>>>(rp, col, n, nnz, scal);
-  }
+  if (validate) validate_csr(rp, col, n, nnz, scal, s);
   // degrees and the stable sort by degree
   uint32_t* kA = tmp.take<uint32_t>(n);
   uint32_t* kB = tmp.take<uint32_t>(n);

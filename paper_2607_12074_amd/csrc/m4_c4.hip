@@ -29,11 +29,13 @@
 // A filter costs per wedge; a window costs per rank of the owner's range, so
 // owners whose endpoints are sparse over many windows belong in a filter.
 #include <limits.h>
+#include <string.h>
 
 #include <algorithm>
 #include <array>
 #include <type_traits>
 
+#include "m4_plan_dev.h"
 #include "m4_walk_dev.h"
 
 namespace m4 {
@@ -87,86 +89,14 @@ __global__ void k_zone_bounds(const int32_t* __restrict__ dr, int64_t n, int64_t
   out[i] = lo;
 }
 
-// Owners with wedge bounds in (12288, C4_MED_MAX] join the medium bucket when
-// their endpoints are thin over many windows; the rule counts ranges of
-// C4_MED_CAP endpoints against windows.
-constexpr int64_t C4_MED_CAP = 3 * C4_MED_SLOTS / 4;
-
-// Filtered owners: log2 of the bits of the first and second LDS bitmap of
-// each bucket (the first holds 2^(bits - 5) table slots afterwards).
-constexpr int C4_LIGHT_AB = 15, C4_LIGHT_BB = 13;
-constexpr int C4_MED_AB = 17, C4_MED_BB = 15;
-constexpr int C4_BIN_AB = 20, C4_BIN_BB = 17;
-constexpr int C4_DISP_BITS = 6;                  // distance of a slot from its home slot
 constexpr uint32_t C4_MAX_CLASSES = 1u << 16;
 constexpr uint32_t C4_KEY_MUL = 0x9E3779B1u, C4_KEY_INV = 0x0E8B2F51u;  // MUL x INV = 1 mod 2^32
-// Direct counters: graphs of at most C4_DIRECT_N vertices, and parts of large
-// filtered owners over at most C4_DIRECT_SPAN ranks.
-constexpr int C4_DIRECT_N = 8192;
+// Direct counters: small graphs, and parts of large filtered owners over at
+// most C4_DIRECT_SPAN ranks.
 constexpr int32_t C4_DIRECT_SPAN = 262144;
 // endpoints of one part of a large filtered owner; most parts
 constexpr int64_t C4_BIN_RANGE = 131072;
 constexpr int C4_MAX_PARTS = 4096;
-
-// Bits of a permuted rank for tables of 2^hb slots, and the first number of
-// lower neighbours whose counts do not fit beside the key in a slot.
-inline int c4_key_bits(int64_t n, int hb) {
-  int b = hb;
-  while ((int64_t(1) << b) < n) b++;
-  return b;
-}
-inline int32_t c4_count_limit(int64_t n, int hb) {
-  const int bits = 32 - C4_DISP_BITS - (c4_key_bits(n, hb) - hb);
-  return bits >= 31 ? INT_MAX : (bits <= 0 ? 0 : 1 << bits);
-}
-
-// Windows of dense counters owner u needs over ranks [r1, u); zb holds the
-// first ranks of degree > 15 and > 255 (the zone bounds).
-__device__ __forceinline__ int64_t c4_windows(const int64_t* zb, int64_t r1, int64_t u) {
-  const int64_t z1 = zb[0] > r1 ? zb[0] : r1, z2 = zb[1] > z1 ? zb[1] : z1;
-  const int64_t aw = (z1 - r1 + 7) >> 3, bw = (z2 - z1 + 3) >> 2;
-  int64_t words;
-  if (u <= r1) words = 0;
-  else if (u <= z1) words = (u - r1 + 7) >> 3;
-  else if (u <= z2) words = aw + ((u - z1 + 3) >> 2);
-  else words = aw + bw + (u - z2);
-  return (words + C4_WIN_WORDS - 1) / C4_WIN_WORDS;
-}
-
-// Bucket of owner u with wedge bound w > 0 and nl lower neighbours.  Owners up
-// to C4_TINY_MAX wedges take one wavefront and a table, the ones above a
-// bitmap filter sized to their bound.  Beyond the one-pass medium bound a
-// dense window costs a pass over the owner's lower neighbours, so an owner
-// goes to the filter of the ranged medium bucket only when its endpoints are
-// thin over many windows (16 windows >= med_win ranges; med_win 0: never), to
-// the large filter when they span at least bin_win windows and average fewer
-// than bin_dense endpoints per window, and else keeps the dense windows.  A
-// filter needs its counts to fit beside the key (lower neighbours below its
-// limit); with credits (orbit counts) there are no dense windows and the
-// large filter takes the rest, or its variant with 64-bit slots.
-struct C4Plan {
-  int light_max, med_max, med_win, bin_win, bin_dense;
-  const int64_t* zb;
-  int64_t r1;
-  int32_t lim_light, lim_med, lim_bin;
-  int credit;
-};
-__device__ __forceinline__ uint32_t c4_bucket(const C4Plan& pl, int64_t w, int64_t u, int nl) {
-  if (w <= pl.light_max) {
-    if (w <= C4_TINY_MAX) return CB_TINY;
-    if (nl < pl.lim_light) return CB_HASH;
-  }
-  if (pl.med_max > 0 && w <= pl.med_max && w <= C4_MED_CAP && nl < pl.lim_med) return CB_MED;
-  const int64_t nwin = c4_windows(pl.zb, pl.r1, u);
-  if (pl.bin_win > 0 && nwin >= pl.bin_win && nl < pl.lim_bin &&
-      (pl.bin_dense <= 0 || w < (int64_t)pl.bin_dense * nwin))
-    return CB_BIN;
-  if (pl.med_max > 0 && pl.med_win > 0 && w <= C4_MED_MAX && nl < pl.lim_med &&
-      16 * nwin >= (int64_t)pl.med_win * ((w + C4_MED_CAP - 1) / C4_MED_CAP))
-    return CB_MED;
-  if (pl.credit) return nl < pl.lim_bin ? CB_BIN : CB_WIDE;
-  return CB_WIN;
-}
 
 // wedge bound of every owner: G lanes cooperate on one row, 4 loads in flight
 template <int G>
@@ -486,13 +416,13 @@ __device__ __forceinline__ void count_direct(const C4Args& A, uint4* cnt4, int2*
   }
 }
 
-// Graphs of at most C4_DIRECT_N vertices: every owner above the tiny bound,
+// Graphs of at most SMALL_N vertices: every owner above the tiny bound,
 // whatever its bucket (one window, no cursors, no bitmaps, and no bucket size
 // that the host has to wait for).
 template <bool CRED>
 __global__ __launch_bounds__(256) void k_c4_direct(C4Args A) {
   constexpr int NT = 256, SEGS = 256;
-  __shared__ uint4 cnt4[C4_DIRECT_N / 4];
+  __shared__ uint4 cnt4[SMALL_N / 4];
   __shared__ int2 sg[SEGS + 1];
   __shared__ int32_t sv[CRED ? SEGS : 1];
   __shared__ int s_next;
@@ -504,7 +434,7 @@ __global__ __launch_bounds__(256) void k_c4_direct(C4Args A) {
     const int32_t u = __builtin_amdgcn_readfirstlane(A.order[at]);
     const int nl = __builtin_amdgcn_readfirstlane(A.dlo[u]);
     unsigned long long own = 0, wedges = 0;
-    count_direct<NT, C4_DIRECT_N, SEGS, CRED>(A, cnt4, sg, sv, &s_next, A.nptr[u], nl, A.zr1, u,
+    count_direct<NT, SMALL_N, SEGS, CRED>(A, cnt4, sg, sv, &s_next, A.nptr[u], nl, A.zr1, u,
                                               acc, wedges, own);
     if (CRED) {
       own = lane_group_sum<WAVE>(own);
@@ -1285,57 +1215,69 @@ inline unsigned blocks_for(int64_t n, int nt) { return (unsigned)ceil_div(n > 0 
 
 }  // namespace
 
+C4Work c4_work(const Prep& P, Arena& tmp) {
+  const int64_t n = P.n;
+  C4Work w{};
+  w.wub = tmp.take<int64_t>(n);
+  w.key = tmp.take<uint32_t>(n);
+  w.order = tmp.take<int32_t>(n);
+  w.rtmp = tmp.take<int64_t>(radix_tmp_elems(n, C4_KEY_BITS));
+  w.start = tmp.take<int64_t>(C4_START_SLOTS + 2);
+  w.hlen = tmp.take<int32_t>(n);
+  w.hoff = tmp.take<int64_t>(n + 2);
+  w.stmp = tmp.take<int64_t>(scan_tmp_elems(n));
+  if (!P.row_len) w.vmeta = tmp.take<int4>(n);
+  if (!w.wub || !w.key || !w.order || !w.rtmp || !w.start || !w.hlen || !w.hoff || !w.stmp ||
+      (!P.row_len && !w.vmeta))
+    throw Fail(M4_EINTERNAL, "workspace too small (c4)");
+  return w;
+}
+
 Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, uint32_t flags,
-               Arena& tmp, hipStream_t s, int num_cu, KTimer* kt,
+               const C4Work& w, hipStream_t s, int num_cu, KTimer* kt,
                const std::function<char*(size_t)>& big_scratch, bool* binned,
-               unsigned long long* n8) {
+               unsigned long long* n8, const SmallInfo* si) {
   const int64_t n = P.n;
   if (n == 0 || P.m == 0) return [](hipStream_t) {};
-  int64_t* wub = tmp.take<int64_t>(n);
-  uint32_t* key = tmp.take<uint32_t>(n);
-  int32_t* order = tmp.take<int32_t>(n);
-  int64_t* rtmp = tmp.take<int64_t>(radix_tmp_elems(n, C4_KEY_BITS));
-  // bucket starts (C4_START_SLOTS), then the two zone bounds
-  int64_t* start = tmp.take<int64_t>(C4_START_SLOTS + 2);
-  int32_t* hlen = tmp.take<int32_t>(n);
-  int64_t* hoff = tmp.take<int64_t>(n + 2);
-  int64_t* stmp = tmp.take<int64_t>(scan_tmp_elems(n));
-  // per-row records of full rows (a partition stores row prefixes instead)
-  int4* vmeta = P.row_len ? nullptr : tmp.take<int4>(n);
-  if (!wub || !key || !order || !rtmp || !start || !hlen || !hoff || !stmp ||
-      (!P.row_len && !vmeta))
-    throw Fail(M4_EINTERNAL, "workspace too small (c4)");
-  fill_u32(&scal->work_c4[0], 0, 8, s);
+  int64_t* wub = w.wub;
+  int32_t* order = w.order;
+  const int64_t* start = si ? scal->small.c4_start : w.start;
+  int32_t* hlen = w.hlen;
+  int64_t* hoff = w.hoff;
+  int64_t* stmp = w.stmp;
+  int4* vmeta = w.vmeta;
+  const bool small = si != nullptr;  // direct counters above the tiny bound
   // W_u <= d (d - 1) of the largest degree d: where that leaves only the light
   // buckets the host does not wait for the bucket sizes; the kernels read them
   // on the device, and their grids are bounded by n
   const int64_t wmost = (int64_t)C.dmax * (C.dmax - 1);
-  const bool small = n <= C4_DIRECT_N && !P.row_len;  // direct counters above the tiny bound
-  const bool light_only = small || (wmost <= tu.c4_light_max &&
-                                    (wmost <= C4_TINY_MAX ||
-                                     C.dmax < c4_count_limit(n, C4_LIGHT_AB - 5)));
-  // zone bounds first: the planner needs every heavy owner's window count
-  int64_t* zbounds = start + C4_START_SLOTS;
-  if (!light_only || small) k_zone_bounds<<<1, 64, 0, s>>>(P.dr, n, zbounds);
-  C4Plan pl{tu.c4_light_max, tu.c4_med_max, tu.c4_med_win, tu.c4_bin_win, tu.c4_bin_dense,
-            zbounds, C.r1, c4_count_limit(n, C4_LIGHT_AB - 5), c4_count_limit(n, C4_MED_AB - 5),
-            c4_count_limit(n, C4_BIN_AB - 5), n8 ? 1 : 0};
-  // rows by degree: <= 64 with 8 lanes, <= 4096 with a wavefront, longer
-  // rows with a workgroup
-  const int64_t b64 = C.bound[4], b4096 = C.bound[7];
+  const bool light_only = wmost <= tu.c4_light_max &&
+                          (wmost <= C4_TINY_MAX || C.dmax < c4_count_limit(n, C4_LIGHT_AB - 5));
   if (kt) kt->begin(M4_K_C4_PLAN, s);
-  if (b64 > 0)
-    k_c4_plan<8><<<blocks_for(b64 * 8, 256), 256, 0, s>>>(P.nptr, P.ncol, P.dr, P.dlo, 0, b64,
-                                                          C.r1, pl, wub, key, P.own_lo, P.hi());
-  if (b4096 > b64)
-    k_c4_plan<64><<<blocks_for((b4096 - b64) * 64, 256), 256, 0, s>>>(
-        P.nptr, P.ncol, P.dr, P.dlo, b64, b4096, C.r1, pl, wub, key, P.own_lo, P.hi());
-  if (n > b4096)
-    k_c4_plan_big<<<(unsigned)(n - b4096), 1024, 0, s>>>(P.nptr, P.ncol, P.dr, P.dlo, b4096, C.r1,
-                                                         pl, wub, key, P.own_lo, P.hi());
-  radix_pass(key, nullptr, n, 0, C4_KEY_BITS, nullptr, order, rtmp, start, s);
+  if (!small) {
+    fill_u32(&scal->work_c4[0], 0, 8, s);
+    // zone bounds first: the planner needs every heavy owner's window count
+    int64_t* zbounds = w.start + C4_START_SLOTS;
+    if (!light_only) k_zone_bounds<<<1, 64, 0, s>>>(P.dr, n, zbounds);
+    const C4Plan pl = c4_plan_rule(n, tu, zbounds, C.r1, n8 != nullptr);
+    // rows by degree: <= 64 with 8 lanes, <= 4096 with a wavefront, longer
+    // rows with a workgroup
+    const int64_t b64 = C.bound[4], b4096 = C.bound[7];
+    if (b64 > 0)
+      k_c4_plan<8><<<blocks_for(b64 * 8, 256), 256, 0, s>>>(
+          P.nptr, P.ncol, P.dr, P.dlo, 0, b64, C.r1, pl, wub, w.key, P.own_lo, P.hi());
+    if (b4096 > b64)
+      k_c4_plan<64><<<blocks_for((b4096 - b64) * 64, 256), 256, 0, s>>>(
+          P.nptr, P.ncol, P.dr, P.dlo, b64, b4096, C.r1, pl, wub, w.key, P.own_lo, P.hi());
+    if (n > b4096)
+      k_c4_plan_big<<<(unsigned)(n - b4096), 1024, 0, s>>>(P.nptr, P.ncol, P.dr, P.dlo, b4096,
+                                                           C.r1, pl, wub, w.key, P.own_lo, P.hi());
+    radix_pass(w.key, nullptr, n, 0, C4_KEY_BITS, nullptr, order, w.rtmp, w.start, s);
+  }
   std::array<int64_t, C4_START_SLOTS + 2> hstart;
-  if (light_only) {
+  if (small) {
+    memcpy(hstart.data(), si->c4_start, sizeof(int64_t) * hstart.size());
+  } else if (light_only) {
     // at most n owners in each light bucket, none elsewhere
     hstart.fill(wmost > C4_TINY_MAX ? 2 * n : n);
     hstart[CB_TINY] = 0;
@@ -1350,10 +1292,10 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
   const int64_t z2 = std::max<int64_t>(hstart[C4_START_SLOTS + 1], z1);
   const int64_t aw = (z1 - C.r1 + 7) >> 3, bw = (z2 - z1 + 3) >> 2;
   auto owners = [&hstart](int b) { return hstart[b + 1] - hstart[b]; };
-  const int64_t HW = owners(CB_WIN);
+  const int64_t HW = small ? 0 : owners(CB_WIN);
   // a partition takes whole owners: it does not hold the degrees' prefix sums
-  const int64_t HB = P.row_len ? 0 : hstart[CB_WIDE + 1] - hstart[CB_BIN];
-  if (binned) *binned = hstart[CB_WIDE + 1] > hstart[CB_BIN];
+  const int64_t HB = small || P.row_len ? 0 : hstart[CB_WIDE + 1] - hstart[CB_BIN];
+  if (binned) *binned = !small && hstart[CB_WIDE + 1] > hstart[CB_BIN];
   int4* desc = nullptr;
   int32_t* seg_cnt = nullptr;
   int4* parts = nullptr;
@@ -1415,7 +1357,7 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
     if (hstart[CB_N] == hstart[CB_TINY]) return;  // no owner at all
     // with stored prefixes only the partition's rows are valid: no full pass
     if (kt) kt->begin(M4_K_C4_DESC, ls);
-    if (!P.row_len)
+    if (!P.row_len && !small)
       k_vmeta<<<blocks_for(n, 256), 256, 0, ls>>>(P.nptr, P.ncol, P.dr, P.dlo, n, C.r1, vmeta);
     if (HW > 0)
       k_c4_desc<<<(unsigned)HW, 256, 0, ls>>>(order, start, hoff, P.nptr, P.dlo, P.ncol, vmeta,
@@ -1446,10 +1388,8 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
     const int64_t waves = (int64_t)num_cu * 32;
     if (small) {
       // the owners of every bucket above the tiny one: a kernel for all
-      if (wmost > C4_TINY_MAX) {
-        hstart[CB_HASH + 1] = 2 * n;
-        filter(CB_HASH, M4_K_C4_HASH, 1, k_c4_direct<false>, k_c4_direct<true>, 256, 4);
-      }
+      hstart[CB_HASH + 1] = hstart[CB_N];
+      filter(CB_HASH, M4_K_C4_HASH, 1, k_c4_direct<false>, k_c4_direct<true>, 256, 4);
       run(CB_TINY, M4_K_C4_HASH, 1, n8 ? k_c4_tiny<true> : k_c4_tiny<false>, WAVE, waves, 1);
       return;
     }

@@ -146,15 +146,17 @@ void basis_costs(BasisChoice& b, const Tuning& tu, int64_t n, bool budgeted,
 }
 
 BasisChoice choose_basis(const Prep& P, const Tuning& tu, uint32_t flags, bool budgeted,
-                         Scal* scal, unsigned long long* in, hipStream_t s) {
+                         Scal* scal, unsigned long long* in, hipStream_t s, const SmallInfo* si) {
   BasisChoice b;
   in[0] = in[1] = in[2] = 0;
   const bool forced = (flags & (M4_BASIS_WEDGE | M4_BASIS_EDGE)) != 0;
   const unsigned grid = (unsigned)std::min<int64_t>(ceil_div(std::max<int64_t>(P.n, 1), 256), 4096);
-  if (P.n > 0) {
+  if (si) {
+    for (int i = 0; i < 3; i++) in[i] = si->cost[i];
+  } else if (P.n > 0) {
     k_edge_cost<<<grid, 256, 0, s>>>(P.dr, P.dplus, P.n, &scal->stat[ST_COST]);
-    // its owners alone cost the edge stage more than the fixed part of the
-    // wedge stage, and it scans at least an entry per wedge endpoint at the
+    // beyond SMALL_N vertices the owners alone cost the edge stage more than the
+    // fixed part of the wedge stage (4167 are enough), and it scans at least an entry per wedge endpoint at the
     // higher price: settled without waiting for the inputs (a read-back takes
     // some 10 us of a call)
     if (!forced && (budgeted || (tu.cost_edge_owner_ns * (double)P.n >= tu.cost_wedge_fixed_us * 1e3 &&
@@ -167,11 +169,15 @@ BasisChoice choose_basis(const Prep& P, const Tuning& tu, uint32_t flags, bool b
   }
   basis_costs(b, tu, P.n, budgeted, in);  // for the edge basis a lower bound so far
   if (!budgeted && P.n > 0 && (b.cost_edge < b.cost_wedge || forced)) {
-    fill_u32(&scal->stat[ST_COST + 1], 0, 2, s);
-    k_edge_scan_cost<<<grid, 256, 0, s>>>(P.nptr, P.ncol, P.dr, P.dplus, P.n,
-                                          &scal->stat[ST_COST + 1]);
-    M4_HIP(hipMemcpyAsync(in + 1, &scal->stat[ST_COST + 1], 8, hipMemcpyDeviceToHost, s));
-    M4_HIP(hipStreamSynchronize(s));
+    if (si) {
+      in[1] = si->cost[3];
+    } else {
+      fill_u32(&scal->stat[ST_COST + 1], 0, 2, s);
+      k_edge_scan_cost<<<grid, 256, 0, s>>>(P.nptr, P.ncol, P.dr, P.dplus, P.n,
+                                            &scal->stat[ST_COST + 1]);
+      M4_HIP(hipMemcpyAsync(in + 1, &scal->stat[ST_COST + 1], 8, hipMemcpyDeviceToHost, s));
+      M4_HIP(hipStreamSynchronize(s));
+    }
     basis_costs(b, tu, P.n, budgeted, in);
   }
   if (flags & M4_BASIS_EDGE) b.edge = !budgeted;

@@ -64,6 +64,20 @@ constexpr int ERR_PROBE = 4;    // an open-addressing probe ran past its table s
 // are summed at the end.
 constexpr int ACC_STRIPES = 32;
 
+// Graphs of at most this many vertices are prepared and planned by three
+// kernels and one read-back (m4_small.hip).
+constexpr int SMALL_N = 8192;
+struct SmallInfo {
+  int64_t tri_start[17];
+  int64_t c4_start[C4_START_SLOTS + 2];  // bucket starts, then the two zone bounds
+  int64_t bound[16];                     // Classes::bound
+  unsigned long long cost[4];  // wedge endpoints, bound of the row entries the edge basis
+                               // scans, longest row, those row entries
+  int64_t hub_slots;
+  unsigned int kmax;  // largest out-degree beyond TRI_LDS_MAX, 0 if none
+  int dmax;
+};
+
 struct Scal {
   unsigned long long stat[ST_N];
   unsigned int dmax;
@@ -79,6 +93,7 @@ struct Scal {
   unsigned long long kstat[M4_NK][4];  // per kernel slot: elems, rows, aux, aux2
   int status;
   int pad;
+  SmallInfo small;
   alignas(128) U128 acc[ACC_STRIPES][ACC_N + 1];  // not read back to the host
 };
 constexpr size_t kScalHead = offsetof(Scal, acc);
@@ -217,6 +232,9 @@ void fill_u32(void* p, uint32_t v, size_t count32, hipStream_t s);
 size_t build_tmp_bytes(int64_t n, int64_t nnz);
 void build_prep(const int64_t* rp, const int32_t* col, int64_t n, int64_t nnz, bool validate,
                 Prep& P, Classes& C, Scal* scal, Scal* scal_host, Arena& tmp, hipStream_t s);
+// Checks a CSR (simple, symmetric, sorted); errors go to scal->err.
+void validate_csr(const int64_t* rp, const int32_t* col, int64_t n, int64_t nnz, Scal* scal,
+                  hipStream_t s);
 // First half of build_prep: degrees, degree order (perm, dr, rank), row
 // offsets nptr and the rank boundaries of the degree classes.
 void degree_order(const int64_t* rp, const int32_t* col, int64_t n, int64_t nnz, bool validate,
@@ -251,14 +269,30 @@ struct TriCredits {
   int kmax = 0;
   std::function<void(hipStream_t, unsigned long long* n12, unsigned long long* n14)> launch;
 };
+// Workspace of a plan; with SmallInfo (the host's copy) its contents are there
+// already and nothing is planned or read back.
+struct TriWork {
+  uint32_t* key;
+  int32_t* order;
+  int64_t* rtmp;
+  int64_t* start;
+  int64_t* hoff64;  // resident runs: hub table offsets, then the out-list records
+  int32_t* hoff;    // hub tables (null: none)
+  int32_t* hub_list;
+  int64_t* hst;
+};
+TriWork tri_work(const Prep& P, const Tuning& tu, Arena& tmp);
+// out-degree bounds of the register kernel (0: unused) and the wavefront kernel
+void tri_bounds(const Prep& P, const Tuning& tu, uint32_t flags, uint32_t cache_rows,
+                int* small_max, int* wave_max);
 Launch tri_plan(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags, uint32_t cache_rows,
-                Arena& tmp, hipStream_t s, int num_cu,
+                const TriWork& w, hipStream_t s, int num_cu,
                 const std::function<char*(size_t)>& big_scratch, KTimer* kt,
-                TriCredits* credits = nullptr);
+                TriCredits* credits = nullptr, const SmallInfo* si = nullptr);
 inline void tri_run(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags,
                     uint32_t cache_rows, Arena& tmp, hipStream_t s, int num_cu,
                     const std::function<char*(size_t)>& big_scratch, KTimer* kt) {
-  tri_plan(P, scal, tu, flags, cache_rows, tmp, s, num_cu, big_scratch, kt)(s);
+  tri_plan(P, scal, tu, flags, cache_rows, tri_work(P, tu, tmp), s, num_cu, big_scratch, kt)(s);
 }
 
 // m4_local.hip: per-vertex orbit counts of a prepared graph (t complete)
@@ -276,23 +310,43 @@ struct BasisChoice {
 };
 // in[3]: the objective's inputs, read back where the choice needs them
 BasisChoice choose_basis(const Prep& P, const Tuning& tu, uint32_t flags, bool budgeted,
-                         Scal* scal, unsigned long long* in, hipStream_t s);
+                         Scal* scal, unsigned long long* in, hipStream_t s, const SmallInfo* si);
 void basis_costs(BasisChoice& b, const Tuning& tu, int64_t n, bool budgeted,
                  const unsigned long long* in);
 Launch edge_plan(const Prep& P, Scal* scal, uint32_t flags, int num_cu, KTimer* kt);
 
 // m4_c4.hip (binned, if given, is set when owners go to the large filter,
 // which holds every CU with a persistent workgroup and all of its LDS; n8, if
-// given, receives the per-vertex 4-cycle credits of every rank)
+// given, receives the per-vertex 4-cycle credits of every rank; si as in
+// tri_plan)
+struct C4Work {
+  int64_t* wub;
+  uint32_t* key;
+  int32_t* order;
+  int64_t* rtmp;
+  int64_t* start;  // bucket starts (C4_START_SLOTS), then the two zone bounds
+  int32_t* hlen;
+  int64_t* hoff;
+  int64_t* stmp;
+  int4* vmeta;  // per-row records of full rows (a partition stores row prefixes instead)
+};
+C4Work c4_work(const Prep& P, Arena& tmp);
 Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, uint32_t flags,
-               Arena& tmp, hipStream_t s, int num_cu, KTimer* kt,
+               const C4Work& w, hipStream_t s, int num_cu, KTimer* kt,
                const std::function<char*(size_t)>& big_scratch, bool* binned = nullptr,
-               unsigned long long* n8 = nullptr);
+               unsigned long long* n8 = nullptr, const SmallInfo* si = nullptr);
 inline void c4_run(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, uint32_t flags,
                    Arena& tmp, hipStream_t s, int num_cu, KTimer* kt,
                    const std::function<char*(size_t)>& big_scratch) {
-  c4_plan(P, C, scal, tu, flags, tmp, s, num_cu, kt, big_scratch)(s);
+  c4_plan(P, C, scal, tu, flags, c4_work(P, tmp), s, num_cu, kt, big_scratch)(s);
 }
+
+// m4_small.hip: build_prep, the anchor objective's inputs and the plans of both
+// anchor stages for a graph of at most SMALL_N vertices; clears scal and t.
+// The host's copy of SmallInfo is scal_host->small afterwards.
+void small_prep(const int64_t* rp, const int32_t* col, int64_t n, int64_t nnz, Prep& P, Classes& C,
+                const Tuning& tu, uint32_t flags, uint32_t cache_rows, bool credit,
+                const TriWork& tw, const C4Work& cw, Scal* scal, Scal* scal_host, hipStream_t s);
 
 // m4_closure.hip
 void closure_run(const Prep& P, Scal* scal, uint32_t flags, hipStream_t s);

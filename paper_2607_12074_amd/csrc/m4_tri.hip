@@ -17,11 +17,13 @@
 // one workgroup with the bitmap in global scratch (larger k).  Block-local sums
 // are folded into one 128-bit atomic per workgroup (block-local aggregation).
 #include <limits.h>
+#include <string.h>
 
 #include <algorithm>
 #include <array>
 #include <type_traits>
 
+#include "m4_plan_dev.h"
 #include "m4_tri_dev.h"
 #include "m4_walk_dev.h"
 
@@ -661,7 +663,6 @@ __global__ __launch_bounds__(NT) void k_tri_global(TriArgs A) {
 }
 
 // bucket of every owner by its out-degree k
-enum { TK_NONE = 0, TK_WAVE, TK_128, TK_256, TK_512, TK_1024, TK_GLOBAL, TK_SMALL, TK_N };
 
 __global__ void k_tri_keys(const int32_t* __restrict__ dplus, int64_t n, int64_t own_lo,
                            int64_t own_hi, int small_max, int wave_max, uint32_t* __restrict__ key,
@@ -669,18 +670,8 @@ __global__ void k_tri_keys(const int32_t* __restrict__ dplus, int64_t n, int64_t
   int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (u >= n) return;
   int k = (u >= own_lo && u < own_hi) ? dplus[u] : 0;
-  uint32_t b;
-  if (k < 2) b = TK_NONE;
-  else if (k <= small_max) b = TK_SMALL;
-  else if (k <= wave_max) b = TK_WAVE;
-  else if (k <= 128) b = TK_128;
-  else if (k <= 256) b = TK_256;
-  else if (k <= 512) b = TK_512;
-  else if (k <= TRI_LDS_MAX) b = TK_1024;
-  else {
-    b = TK_GLOBAL;
-    atomicMax((unsigned int*)&scal->work[7], (unsigned int)k);
-  }
+  const uint32_t b = tri_bucket(k, small_max, wave_max);
+  if (b == TK_GLOBAL) atomicMax((unsigned int*)&scal->work[7], (unsigned int)k);
   key[u] = b;
 }
 
@@ -766,59 +757,86 @@ size_t tri_tmp_bytes(int64_t n, int64_t nnz, int kmax_global) {
              ((size_t)kmax_global * ((kmax_global + 63) / 64) * 8 + (7 * (size_t)kmax_global + 2) * 4);
 }
 
-Launch tri_plan(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags, uint32_t cache_rows,
-                Arena& tmp, hipStream_t s, int num_cu,
-                const std::function<char*(size_t)>& big_scratch, KTimer* kt, TriCredits* credits) {
+namespace {
+// out-list records and hub tables: resident runs only (a partition holds only
+// its halo rows)
+inline bool full_rows(const Prep& P) { return P.own_hi < 0 && !P.row_len; }
+}  // namespace
+
+TriWork tri_work(const Prep& P, const Tuning& tu, Arena& tmp) {
   const int64_t n = P.n;
-  if (n == 0 || P.m == 0) return [](hipStream_t) {};
-  uint32_t* key = tmp.take<uint32_t>(n);
-  int32_t* order = tmp.take<int32_t>(n);
-  int64_t* rtmp = tmp.take<int64_t>(radix_tmp_elems(n, 4));
-  int64_t* start = tmp.take<int64_t>(17);
-  if (!key || !order || !rtmp || !start) throw Fail(M4_EINTERNAL, "workspace too small (tri)");
-  fill_u32(&scal->work[0], 0, 8, s);
+  TriWork w{};
+  w.key = tmp.take<uint32_t>(n);
+  w.order = tmp.take<int32_t>(n);
+  w.rtmp = tmp.take<int64_t>(radix_tmp_elems(n, 4));
+  w.start = tmp.take<int64_t>(17);
+  if (!w.key || !w.order || !w.rtmp || !w.start) throw Fail(M4_EINTERNAL, "workspace too small (tri)");
+  if (full_rows(P)) {
+    w.hoff64 = tmp.take<int64_t>(n + 1);
+    if (!w.hoff64) throw Fail(M4_EINTERNAL, "workspace too small (out-lists)");
+    if (tu.hub_min > 0) {
+      w.hoff = tmp.take<int32_t>(n);
+      w.hub_list = tmp.take<int32_t>(n);
+      w.hst = tmp.take<int64_t>(scan_tmp_elems(n));
+      if (!w.hoff || !w.hub_list || !w.hst) throw Fail(M4_EINTERNAL, "workspace too small (hubs)");
+    }
+  }
+  return w;
+}
+
+void tri_bounds(const Prep& P, const Tuning& tu, uint32_t flags, uint32_t cache_rows,
+                int* small_max, int* wave_max) {
   // the bound of the owners of one wavefront has one value for out-lists that
   // stream from HBM and one for those in the Infinity Cache (both 64 now)
-  const int wave_req = (size_t)P.m * 4 > kInfinityCacheBytes ? tu.tri_wave_far : tu.tri_wave_max;
-  int wave_max = wave_req < 2 ? 2 : (wave_req > 64 ? 64 : wave_req);
-  // out-list records and hub tables: resident runs only (a partition holds
-  // only its halo rows); the register kernel needs the records and holds every
-  // frontier, so it is left out where the cache is off or capped below it
-  const bool full = P.own_hi < 0 && !P.row_len;
-  const bool small = full && !(flags & M4_NO_CACHE) &&
+  const int req = (size_t)P.m * 4 > kInfinityCacheBytes ? tu.tri_wave_far : tu.tri_wave_max;
+  *wave_max = req < 2 ? 2 : (req > 64 ? 64 : req);
+  // the register kernel needs the out-list records and holds every frontier,
+  // so it is left out where the cache is off or capped below it
+  const bool small = full_rows(P) && !(flags & M4_NO_CACHE) &&
                      (cache_rows == 0 || cache_rows >= (uint32_t)TRI_SMALL);
-  k_tri_keys<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(
-      P.dplus, n, P.own_lo, P.hi(), small ? std::min(wave_max, TRI_SMALL) : 0, wave_max, key, scal);
-  radix_pass(key, nullptr, n, 0, 4, nullptr, order, rtmp, start, s);
-  const bool hubs = full && tu.hub_min > 0;
-  int32_t* hsz = reinterpret_cast<int32_t*>(key);  // the keys are in order[] now
-  int32_t* hoff = nullptr;
-  int32_t* hub_list = nullptr;
-  int64_t* hoff64 = nullptr;
-  int2* list = nullptr;  // takes the place of hoff64 once hoff is made of it
-  if (full) {
-    hoff64 = tmp.take<int64_t>(n + 1);
-    if (!hoff64) throw Fail(M4_EINTERNAL, "workspace too small (out-lists)");
-    list = reinterpret_cast<int2*>(hoff64);
-  }
-  if (hubs) {
-    hoff = tmp.take<int32_t>(n);
-    hub_list = tmp.take<int32_t>(n);
-    int64_t* hst = tmp.take<int64_t>(scan_tmp_elems(n));
-    if (!hoff || !hub_list || !hst) throw Fail(M4_EINTERNAL, "workspace too small (hubs)");
-    fill_u32(&scal->nhub, 0, 1, s);
-    k_hub_size<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(P.dplus, n, tu.hub_min, hsz, hub_list,
-                                                          &scal->nhub);
-    scan_i32(hsz, n, hoff64, hst, s);
-  }
+  *small_max = small ? std::min(*wave_max, TRI_SMALL) : 0;
+}
+
+Launch tri_plan(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags, uint32_t cache_rows,
+                const TriWork& w, hipStream_t s, int num_cu,
+                const std::function<char*(size_t)>& big_scratch, KTimer* kt, TriCredits* credits,
+                const SmallInfo* si) {
+  const int64_t n = P.n;
+  if (n == 0 || P.m == 0) return [](hipStream_t) {};
+  int32_t* order = w.order;
+  const int64_t* start = si ? scal->small.tri_start : w.start;
+  int32_t* hoff = w.hoff;
+  int32_t* hub_list = w.hub_list;
+  int64_t* hoff64 = w.hoff64;
+  int2* list = reinterpret_cast<int2*>(hoff64);  // takes its place once hoff is made of it
+  int32_t* hsz = reinterpret_cast<int32_t*>(w.key);  // the keys are in order[] then
+  const bool hubs = hoff != nullptr;
   // largest out-degree of the global bucket decides its scratch size
   unsigned int kmax_g = 0;
   int64_t hstart[17];
   int64_t hub_slots = 0;
-  M4_HIP(hipMemcpyAsync(&kmax_g, &scal->work[7], sizeof(kmax_g), hipMemcpyDeviceToHost, s));
-  M4_HIP(hipMemcpyAsync(hstart, start, sizeof(hstart), hipMemcpyDeviceToHost, s));
-  if (hubs) M4_HIP(hipMemcpyAsync(&hub_slots, hoff64 + n, 8, hipMemcpyDeviceToHost, s));
-  M4_HIP(hipStreamSynchronize(s));
+  if (si) {
+    kmax_g = si->kmax;
+    memcpy(hstart, si->tri_start, sizeof(hstart));
+    hub_slots = si->hub_slots;
+  } else {
+    int small_max, wave_max;
+    tri_bounds(P, tu, flags, cache_rows, &small_max, &wave_max);
+    fill_u32(&scal->work[0], 0, 8, s);
+    k_tri_keys<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(P.dplus, n, P.own_lo, P.hi(), small_max,
+                                                          wave_max, w.key, scal);
+    radix_pass(w.key, nullptr, n, 0, 4, nullptr, order, w.rtmp, w.start, s);
+    if (hubs) {
+      fill_u32(&scal->nhub, 0, 1, s);
+      k_hub_size<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(P.dplus, n, tu.hub_min, hsz, hub_list,
+                                                            &scal->nhub);
+      scan_i32(hsz, n, hoff64, w.hst, s);
+    }
+    M4_HIP(hipMemcpyAsync(&kmax_g, &scal->work[7], sizeof(kmax_g), hipMemcpyDeviceToHost, s));
+    M4_HIP(hipMemcpyAsync(hstart, start, sizeof(hstart), hipMemcpyDeviceToHost, s));
+    if (hubs) M4_HIP(hipMemcpyAsync(&hub_slots, hoff64 + n, 8, hipMemcpyDeviceToHost, s));
+    M4_HIP(hipStreamSynchronize(s));
+  }
   // scratch: hub tables, then the dense-owner bitmaps
   size_t hub_bytes = 0, dense_bytes = 0, dense_bits = 0, dense_blocks = 0;
   const bool use_hubs = hubs && hub_slots > 0 && hub_slots < (int64_t(1) << 31);
@@ -909,12 +927,13 @@ Launch tri_plan(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags, uin
       run_small(B, true_type{}, ls);
     };
   }
+  const bool planned = si != nullptr;
   // everything below runs on the launch stream, after the plan above
   return [=](hipStream_t ls) mutable {
     if (kt) kt->begin(M4_K_TRI_HUBS, ls);
-    if (use_hubs)
+    if (use_hubs && !planned)
       k_hub_off<<<(unsigned)ceil_div(n, 256), 256, 0, ls>>>(hsz, hoff64, n, hoff);
-    if (list)
+    if (list && !planned)
       k_tri_list<<<(unsigned)ceil_div(n + 1, 256), 256, 0, ls>>>(P.nptr, P.dlo, P.optr, n, list);
     if (use_hubs) {
       unsigned long long* htab = reinterpret_cast<unsigned long long*>(scratch);

@@ -1,6 +1,6 @@
-"""The anchor-selection objective around the sizes where it is settled without
-its inputs (4167 vertices: their work counter alone costs the edge stage more
-than the wedge stage's fixed part), and where one long row decides."""
+"""The anchor-selection objective: the serial parts of the edge stage (its owner
+counter, its longest row) against the fixed part of the wedge stage, and graphs
+beyond 8192 vertices, where the choice is settled without its inputs."""
 import pytest
 
 import graphgen as gg
@@ -11,10 +11,11 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     ("short rows, few owners", G.cycle(300), 1),
-    ("short rows, below the settled size", G.cycle(4000), 0),
-    ("one vertex below", G.cycle(4166), 0),
-    ("settled", G.cycle(4167), 0),
-    ("settled, hubs", gg.ba(5000, 3, 6), 0),
+    ("short rows, few enough owners", G.cycle(1000), 1),
+    ("short rows, too many owners", G.cycle(4000), 0),
+    ("one vertex below settled", G.cycle(8192), 0),
+    ("settled", G.cycle(8193), 0),
+    ("settled, hubs", gg.ba(9000, 3, 6), 0),
     ("a long row among few owners", G.wheel(60), 0),
     ("empty rows", G.disjoint_union(G.csr(100, []), G.complete(5)), 1),
 ]
