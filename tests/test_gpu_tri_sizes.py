@@ -62,3 +62,17 @@ def test_random_graphs(ctx, n, m, hubs):
         assert np.array_equal(ctx.edge_triangles(*g), (A @ A)[src, g[1]])
     finally:
         ctx.set_tuning(**base)
+
+
+# owners of one wavefront dealt in turn, and in runs from the work counter (from
+# 262144 owners on); without the cache none of them takes the register kernel
+@pytest.mark.parametrize("n", [150000, 300001])
+def test_dealing(ctx, n):
+    import paper_2607_12074_amd as m4
+    g = gg.gnm(n, 4 * n, 5)
+    ref = oracle.closure(*g)
+    assert ctx.count(*g, flags=m4.M4_NO_CACHE) == ref
+    assert ctx.count(*g) == ref
+    # halo partitions: the register kernel on the separate arrays
+    got, st = ctx.count(*g, flags=m4.M4_FORCE_PARTITION, budget=96 * n + 40 * n, stats=True)
+    assert got == ref and st["partitions"] > 1
