@@ -72,7 +72,7 @@ size_t m4_ctx::held_bytes() const {
 
 void m4_ctx::release_resident() {
   (void)hipStreamSynchronize(stream);
-  (void)hipStreamSynchronize(stream2);
+  if (stream2) (void)hipStreamSynchronize(stream2);
   prep.release();
   tmp.release();
   big.release();
@@ -144,6 +144,10 @@ int scal_error(m4_ctx* ctx, int err) {
 }  // namespace m4
 
 extern "C" int m4_ctx_create(int device, m4_ctx** out) {
+  return m4::ctx_create(device, true, out);
+}
+
+int m4::ctx_create(int device, bool overlap, m4_ctx** out) {
   if (!out) return M4_EINVAL;
   *out = nullptr;
   int ndev = 0;
@@ -161,7 +165,7 @@ extern "C" int m4_ctx_create(int device, m4_ctx** out) {
     c->num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     c->arch = std::string(prop.gcnArchName) + " " + std::to_string(c->num_cu) + " CU";
     M4_HIP(hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking));
-    M4_HIP(hipStreamCreateWithFlags(&c->stream2, hipStreamNonBlocking));
+    if (overlap) M4_HIP(hipStreamCreateWithFlags(&c->stream2, hipStreamNonBlocking));
     M4_HIP(hipEventCreateWithFlags(&c->fork_ev, hipEventDisableTiming));
     M4_HIP(hipEventCreateWithFlags(&c->join_ev, hipEventDisableTiming));
     M4_HIP(hipMalloc((void**)&c->scal, sizeof(Scal)));
@@ -275,7 +279,7 @@ Tuning tuning_for(const m4_ctx* c, const m4_opts* o) {
 }
 
 // The prepared graph and the two anchor stages' workspaces, side by side in
-// c->tmp; si: the host's copy of a small graph's plan, else null.
+// c->tmp; si: the host's copy of the plans (null before they are made).
 struct StageWork {
   TriWork tri;
   C4Work c4;
@@ -313,10 +317,23 @@ void prepare(m4_ctx* c, const int64_t* rp, const int32_t* col, int64_t n, int64_
   build_prep(rp, col, n, nnz, (flags & M4_VALIDATE) != 0, P, C, c->scal, c->scal_host, a, s);
 }
 
+// The plans of the triangle stage and, with c4, the 4-cycle stage; one
+// read-back for both.
+void plan_stages(m4_ctx* c, const Prep& P, const Classes& C, uint32_t flags, uint32_t cache_rows,
+                 const Tuning& tu, bool c4, bool credit, hipStream_t s, KTimer* kt, StageWork& w) {
+  if (w.si) return;
+  tri_enqueue(P, c->scal, tu, flags, cache_rows, w.tri, s);
+  if (c4) c4_enqueue(P, C, c->scal, tu, w.c4, s, credit, kt);
+  M4_HIP(hipMemcpyAsync(c->scal_host, c->scal, kScalHead, hipMemcpyDeviceToHost, s));
+  M4_HIP(hipStreamSynchronize(s));
+  w.si = &c->scal_host->small;
+}
+
 // The resident single-graph pipeline.  Leaves the prepared graph in c->prep
 // (P) and the results in c->scal; the caller reads them back.
 void run_resident(m4_ctx* c, const int64_t* rp, const int32_t* col, int64_t n, int64_t nnz,
-                  const m4_opts* o, hipStream_t s, Prep& P, bool want_timing) {
+                  const m4_opts* o, hipStream_t s, Prep& P, bool want_timing,
+                  bool costs) {
   KTimer* kt = nullptr;
   if (o && (o->flags & M4_TIMING)) {
     kt = &c->ktimer;
@@ -336,7 +353,8 @@ void run_resident(m4_ctx* c, const int64_t* rp, const int32_t* col, int64_t n, i
   prepare(c, rp, col, n, nnz, flags, cache_rows, tu, false, s, P, C, w);
   if (kt) kt->end(M4_K_BUILD, s);
   // the cycle/path anchor basis (Section III-A): wedges or edge anchors
-  c->basis = choose_basis(P, tu, flags, o && o->device_budget_bytes > 0, c->scal, c->cost_in, s, w.si);
+  c->basis = choose_basis(P, tu, flags, o && o->device_budget_bytes > 0, costs, c->scal,
+                          c->cost_in, s, w.si);
   if (want_timing) M4_HIP(hipEventRecord(c->ev[1], s));
   auto big = [c, s](size_t bytes) -> char* {
     c->big.ensure(bytes, s);
@@ -356,17 +374,18 @@ void run_resident(m4_ctx* c, const int64_t* rp, const int32_t* col, int64_t n, i
   // triangle kernels measured slower.
   // Small graphs run them in order too: the events cost more than the overlap
   // gives.
-  Launch tri =
-      tri_plan(P, c->scal, tu, flags, cache_rows, w.tri, s, c->num_cu, big, kt, nullptr, w.si);
+  plan_stages(c, P, C, flags, cache_rows, tu, !c->basis.edge, false, s, kt, w);
+  Launch tri = tri_plan(P, c->scal, tu, flags, cache_rows, w.tri, c->num_cu, big, kt, *w.si);
   bool binned = false;
   Launch c4 = c->basis.edge ? edge_plan(P, c->scal, flags, c->num_cu, kt)
                             : c4_plan(P, C, c->scal, tu, flags, w.c4, s, c->num_cu, kt, big2,
-                                      &binned, nullptr, w.si);
-  if ((flags & M4_SERIAL) || binned || w.si) {
+                                      *w.si, &binned);
+  if ((flags & M4_SERIAL) || binned || n <= SMALL_N) {
     tri(s);
     if (want_timing) M4_HIP(hipEventRecord(c->ev[2], s));
     c4(s);
   } else {
+    if (!c->stream2) M4_HIP(hipStreamCreateWithFlags(&c->stream2, hipStreamNonBlocking));
     M4_HIP(hipEventRecord(c->fork_ev, s));
     M4_HIP(hipStreamWaitEvent(c->stream2, c->fork_ev, 0));
     tri(s);
@@ -465,7 +484,7 @@ extern "C" int m4_count_motifs4_ex(m4_ctx* ctx, const m4_csr* g, const m4_opts* 
   stage_input(ctx, g, s, &rp, &col, &h2d);
   if (timing) M4_HIP(hipEventRecord(ctx->ev[6], s));
   Prep P;
-  run_resident(ctx, rp, col, g->n, g->nnz, o, s, P, timing);
+  run_resident(ctx, rp, col, g->n, g->nnz, o, s, P, timing, st != nullptr);
   M4_HIP(hipMemcpyAsync(ctx->scal_host, ctx->scal, kScalHead, hipMemcpyDeviceToHost, s));
   M4_HIP(hipStreamSynchronize(s));
   const Scal& h = *ctx->scal_host;
@@ -522,8 +541,8 @@ extern "C" int m4_edge_triangles(m4_ctx* ctx, const m4_csr* g, const m4_opts* o,
     ctx->big.ensure(bytes, s);
     return ctx->big.ptr;
   };
-  tri_plan(P, ctx->scal, tu, flags, cache_rows, w.tri, s, ctx->num_cu, big, nullptr, nullptr,
-           w.si)(s);
+  plan_stages(ctx, P, C, flags, cache_rows, tu, false, false, s, nullptr, w);
+  tri_plan(P, ctx->scal, tu, flags, cache_rows, w.tri, ctx->num_cu, big, nullptr, *w.si)(s);
   uint32_t* dst = t_out;
   if (!g->on_device) {
     ctx->tout.ensure((size_t)g->nnz * 4, s);
@@ -579,7 +598,8 @@ extern "C" int m4_count_orbits4(m4_ctx* ctx, const m4_csr* g, const m4_opts* o,
     return ctx->big.ptr;
   };
   TriCredits credits;
-  tri_plan(P, ctx->scal, tu, flags, 0, w.tri, s, ctx->num_cu, big, nullptr, &credits, w.si)(s);
+  plan_stages(ctx, P, C, flags, 0, tu, true, true, s, nullptr, w);
+  tri_plan(P, ctx->scal, tu, flags, 0, w.tri, ctx->num_cu, big, nullptr, *w.si, &credits)(s);
   // statistics (8 n words) and the bitmap slices of out-degrees above the
   // triangle stage's LDS bound in big2
   const size_t arr_bytes = align256((size_t)n * 8 * 8);
@@ -597,7 +617,7 @@ extern "C" int m4_count_orbits4(m4_ctx* ctx, const m4_csr* g, const m4_opts* o,
     return ctx->big3.ptr;
   };
   const Launch cycles = c4_plan(P, C, ctx->scal, tu, flags, w.c4, s, ctx->num_cu, nullptr, big3,
-                                nullptr, arrays + 5 * n, w.si);
+                                *w.si, nullptr, arrays + 5 * n);
   unsigned long long* dst = reinterpret_cast<unsigned long long*>(orbits);
   if (!g->on_device) {
     ctx->tout.ensure(out_bytes, s);

@@ -81,31 +81,35 @@ __global__ void k_validate_entries(const int64_t* __restrict__ rp, const int32_t
   if (bad) atomicOr(&scal->err, ERR_INVALID);
 }
 
-__global__ void k_identity(int32_t* __restrict__ p, uint32_t* __restrict__ k, int64_t n) {
+// the degree order of a graph without edges
+__global__ void k_identity(int32_t* __restrict__ p, int32_t* __restrict__ r,
+                           int32_t* __restrict__ d, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) {
-    p[i] = (int32_t)i;
-    k[i] = 0;
+    p[i] = r[i] = (int32_t)i;
+    d[i] = 0;
   }
 }
 
-__global__ void k_rank(const int32_t* __restrict__ perm, int64_t n, int32_t* __restrict__ rank) {
-  int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < n) rank[perm[r]] = (int32_t)r;
-}
-
-// First rank whose degree exceeds each threshold (degrees are sorted).
-__global__ void k_classes(const int32_t* __restrict__ dr, int64_t n, const int* thr, int nthr,
-                          int64_t* __restrict__ out) {
-  int i = threadIdx.x;
-  if (i >= nthr) return;
+// First rank whose degree exceeds each threshold (degrees are sorted), and the
+// two of the 4-cycle counter zones.
+struct ClassThr {
+  int thr[16];
+  int n;
+};
+__global__ void k_classes(const int32_t* __restrict__ dr, int64_t n, ClassThr T,
+                          SmallInfo* __restrict__ out) {
+  const int i = threadIdx.x;
+  if (i >= T.n + 2) return;
+  const int thr = i < T.n ? T.thr[i] : (i == T.n ? 15 : 255);
   int64_t lo = 0, hi = n;
   while (lo < hi) {
     int64_t mid = (lo + hi) >> 1;
-    if (dr[mid] <= thr[i]) lo = mid + 1;
+    if (dr[mid] <= thr) lo = mid + 1;
     else hi = mid;
   }
-  out[i] = lo;
+  if (i < T.n) out->bound[i] = lo;
+  else out->c4_start[C4_START_SLOTS + i - T.n] = lo;
 }
 
 // Rows of degree <= G: G lanes per row; each lane maps one neighbour to its
@@ -375,39 +379,30 @@ void degree_order(const int64_t* rp, const int32_t* col, int64_t n, int64_t nnz,
   C.dmax = (int)dmax;
   int passes = 0;
   while (passes < 4 && (dmax >> (8 * passes)) != 0) passes++;
+  // the last pass leaves the sorted degrees, the permutation and its inverse
+  // in place
   uint32_t* kin = kA;
   int32_t* vin = nullptr;  // identity on the first pass
-  uint32_t* kout = kB;
-  int32_t* vout = P.perm;
-  int32_t* vother = vB;
   for (int p = 0; p < passes; p++) {
-    radix_pass(kin, vin, n, 8 * p, 8, kout, vout, rtmp, nullptr, s);
-    std::swap(kin, kout);
+    const bool last = p + 1 == passes;
+    uint32_t* kout = last ? reinterpret_cast<uint32_t*>(P.dr) : (p & 1 ? kA : kB);
+    int32_t* vout = (passes - 1 - p) & 1 ? vB : P.perm;
+    radix_pass(kin, vin, n, 8 * p, 8, kout, vout, rtmp, nullptr, s, last ? P.rank : nullptr);
+    kin = kout;
     vin = vout;
-    std::swap(vout, vother);
   }
-  // sorted degrees are in kin, the permutation in vin
-  if (passes == 0) {
-    k_identity<<<blocks_for(n, NT), NT, 0, s>>>(P.perm, kB, n);
-    kin = kB;
-    vin = P.perm;
-  }
-  if (vin != P.perm)
-    M4_HIP(hipMemcpyAsync(P.perm, vin, n * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-  M4_HIP(hipMemcpyAsync(P.dr, kin, n * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-  k_rank<<<blocks_for(n, NT), NT, 0, s>>>(P.perm, n, P.rank);
+  if (passes == 0) k_identity<<<blocks_for(n, NT), NT, 0, s>>>(P.perm, P.rank, P.dr, n);
   int64_t* stmp = tmp.take<int64_t>(scan_tmp_elems(n));
-  int* thr_d = tmp.take<int>(kNThr);
-  int64_t* bounds_d = tmp.take<int64_t>(kNThr);
-  if (!stmp || !thr_d || !bounds_d) throw Fail(M4_EINTERNAL, "workspace too small (build)");
+  if (!stmp) throw Fail(M4_EINTERNAL, "workspace too small (build)");
   scan_i32(P.dr, n, P.nptr, stmp, s);
-  M4_HIP(hipMemcpyAsync(thr_d, kThr, sizeof(kThr), hipMemcpyHostToDevice, s));
-  k_classes<<<1, 64, 0, s>>>(P.dr, n, thr_d, kNThr, bounds_d);
-  int64_t b[kNThr];
-  M4_HIP(hipMemcpyAsync(b, bounds_d, sizeof(b), hipMemcpyDeviceToHost, s));
+  ClassThr T{};
+  T.n = kNThr;
+  for (int i = 0; i < kNThr; i++) T.thr[i] = kThr[i];
+  k_classes<<<1, 64, 0, s>>>(P.dr, n, T, &scal->small);
+  M4_HIP(hipMemcpyAsync(scal_host, scal, kScalHead, hipMemcpyDeviceToHost, s));
   M4_HIP(hipStreamSynchronize(s));
-  C.r1 = b[0];
-  for (int i = 0; i < kNThr; i++) C.bound[i] = b[i];
+  for (int i = 0; i < kNThr; i++) C.bound[i] = scal_host->small.bound[i];
+  C.r1 = C.bound[0];
 }
 
 void build_prep(const int64_t* rp, const int32_t* col, int64_t n, int64_t nnz, bool validate,

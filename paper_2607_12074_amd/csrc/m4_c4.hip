@@ -75,20 +75,6 @@ struct C4Args {
   int32_t z1, z2, aw, bw, zr1;  // zr1: r1 as a 32-bit rank
 };
 
-// first ranks with degree > 15 and > 255 (degrees are sorted by rank)
-__global__ void k_zone_bounds(const int32_t* __restrict__ dr, int64_t n, int64_t* __restrict__ out) {
-  const int i = threadIdx.x;
-  if (i >= 2) return;
-  const int thr = i == 0 ? 15 : 255;
-  int64_t lo = 0, hi = n;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (dr[mid] <= thr) lo = mid + 1;
-    else hi = mid;
-  }
-  out[i] = lo;
-}
-
 constexpr uint32_t C4_MAX_CLASSES = 1u << 16;
 constexpr uint32_t C4_KEY_MUL = 0x9E3779B1u, C4_KEY_INV = 0x0E8B2F51u;  // MUL x INV = 1 mod 2^32
 // Direct counters: small graphs, and parts of large filtered owners over at
@@ -1222,71 +1208,56 @@ C4Work c4_work(const Prep& P, Arena& tmp) {
   w.key = tmp.take<uint32_t>(n);
   w.order = tmp.take<int32_t>(n);
   w.rtmp = tmp.take<int64_t>(radix_tmp_elems(n, C4_KEY_BITS));
-  w.start = tmp.take<int64_t>(C4_START_SLOTS + 2);
   w.hlen = tmp.take<int32_t>(n);
   w.hoff = tmp.take<int64_t>(n + 2);
   w.stmp = tmp.take<int64_t>(scan_tmp_elems(n));
   if (!P.row_len) w.vmeta = tmp.take<int4>(n);
-  if (!w.wub || !w.key || !w.order || !w.rtmp || !w.start || !w.hlen || !w.hoff || !w.stmp ||
+  if (!w.wub || !w.key || !w.order || !w.rtmp || !w.hlen || !w.hoff || !w.stmp ||
       (!P.row_len && !w.vmeta))
     throw Fail(M4_EINTERNAL, "workspace too small (c4)");
   return w;
 }
 
+void c4_enqueue(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, const C4Work& w,
+                hipStream_t s, bool credit, KTimer* kt) {
+  const int64_t n = P.n;
+  if (n == 0 || P.m == 0) return;
+  if (kt) kt->begin(M4_K_C4_PLAN, s);
+  if (P.row_len) fill_u32(&scal->work_c4[0], 0, 8, s);  // one of several plans
+  const C4Plan pl =
+      c4_plan_rule(n, tu, scal->small.c4_start + C4_START_SLOTS, C.r1, credit);
+  // rows by degree: <= 64 with 8 lanes, <= 4096 with a wavefront, longer
+  // rows with a workgroup
+  const int64_t b64 = C.bound[4], b4096 = C.bound[7];
+  if (b64 > 0)
+    k_c4_plan<8><<<blocks_for(b64 * 8, 256), 256, 0, s>>>(
+        P.nptr, P.ncol, P.dr, P.dlo, 0, b64, C.r1, pl, w.wub, w.key, P.own_lo, P.hi());
+  if (b4096 > b64)
+    k_c4_plan<64><<<blocks_for((b4096 - b64) * 64, 256), 256, 0, s>>>(
+        P.nptr, P.ncol, P.dr, P.dlo, b64, b4096, C.r1, pl, w.wub, w.key, P.own_lo, P.hi());
+  if (n > b4096)
+    k_c4_plan_big<<<(unsigned)(n - b4096), 1024, 0, s>>>(
+        P.nptr, P.ncol, P.dr, P.dlo, b4096, C.r1, pl, w.wub, w.key, P.own_lo, P.hi());
+  radix_pass(w.key, nullptr, n, 0, C4_KEY_BITS, nullptr, w.order, w.rtmp, scal->small.c4_start, s);
+}
+
 Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, uint32_t flags,
                const C4Work& w, hipStream_t s, int num_cu, KTimer* kt,
-               const std::function<char*(size_t)>& big_scratch, bool* binned,
-               unsigned long long* n8, const SmallInfo* si) {
+               const std::function<char*(size_t)>& big_scratch, const SmallInfo& si, bool* binned,
+               unsigned long long* n8) {
   const int64_t n = P.n;
   if (n == 0 || P.m == 0) return [](hipStream_t) {};
   int64_t* wub = w.wub;
   int32_t* order = w.order;
-  const int64_t* start = si ? scal->small.c4_start : w.start;
+  const int64_t* start = scal->small.c4_start;
   int32_t* hlen = w.hlen;
   int64_t* hoff = w.hoff;
   int64_t* stmp = w.stmp;
   int4* vmeta = w.vmeta;
-  const bool small = si != nullptr;  // direct counters above the tiny bound
-  // W_u <= d (d - 1) of the largest degree d: where that leaves only the light
-  // buckets the host does not wait for the bucket sizes; the kernels read them
-  // on the device, and their grids are bounded by n
-  const int64_t wmost = (int64_t)C.dmax * (C.dmax - 1);
-  const bool light_only = wmost <= tu.c4_light_max &&
-                          (wmost <= C4_TINY_MAX || C.dmax < c4_count_limit(n, C4_LIGHT_AB - 5));
-  if (kt) kt->begin(M4_K_C4_PLAN, s);
-  if (!small) {
-    fill_u32(&scal->work_c4[0], 0, 8, s);
-    // zone bounds first: the planner needs every heavy owner's window count
-    int64_t* zbounds = w.start + C4_START_SLOTS;
-    if (!light_only) k_zone_bounds<<<1, 64, 0, s>>>(P.dr, n, zbounds);
-    const C4Plan pl = c4_plan_rule(n, tu, zbounds, C.r1, n8 != nullptr);
-    // rows by degree: <= 64 with 8 lanes, <= 4096 with a wavefront, longer
-    // rows with a workgroup
-    const int64_t b64 = C.bound[4], b4096 = C.bound[7];
-    if (b64 > 0)
-      k_c4_plan<8><<<blocks_for(b64 * 8, 256), 256, 0, s>>>(
-          P.nptr, P.ncol, P.dr, P.dlo, 0, b64, C.r1, pl, wub, w.key, P.own_lo, P.hi());
-    if (b4096 > b64)
-      k_c4_plan<64><<<blocks_for((b4096 - b64) * 64, 256), 256, 0, s>>>(
-          P.nptr, P.ncol, P.dr, P.dlo, b64, b4096, C.r1, pl, wub, w.key, P.own_lo, P.hi());
-    if (n > b4096)
-      k_c4_plan_big<<<(unsigned)(n - b4096), 1024, 0, s>>>(P.nptr, P.ncol, P.dr, P.dlo, b4096,
-                                                           C.r1, pl, wub, w.key, P.own_lo, P.hi());
-    radix_pass(w.key, nullptr, n, 0, C4_KEY_BITS, nullptr, order, w.rtmp, w.start, s);
-  }
+  const bool small = n <= SMALL_N && !P.row_len;  // direct counters above the tiny bound
+  if (kt && small) kt->begin(M4_K_C4_PLAN, s);
   std::array<int64_t, C4_START_SLOTS + 2> hstart;
-  if (small) {
-    memcpy(hstart.data(), si->c4_start, sizeof(int64_t) * hstart.size());
-  } else if (light_only) {
-    // at most n owners in each light bucket, none elsewhere
-    hstart.fill(wmost > C4_TINY_MAX ? 2 * n : n);
-    hstart[CB_TINY] = 0;
-    hstart[CB_HASH] = n;
-  } else {
-    M4_HIP(hipMemcpyAsync(hstart.data(), start, sizeof(int64_t) * hstart.size(),
-                          hipMemcpyDeviceToHost, s));
-    M4_HIP(hipStreamSynchronize(s));
-  }
+  memcpy(hstart.data(), si.c4_start, sizeof(int64_t) * hstart.size());
   // counter zones of the window owners
   const int64_t z1 = std::max<int64_t>(hstart[C4_START_SLOTS], C.r1);
   const int64_t z2 = std::max<int64_t>(hstart[C4_START_SLOTS + 1], z1);

@@ -42,9 +42,13 @@ int set_error(m4_ctx* ctx, int code, const std::string& msg);
 // status and message of the error bits a call left in Scal::err
 int scal_error(m4_ctx* ctx, int err);
 int check_csr_args(const m4_csr* g);
+// overlap: with the stream of the 4-cycle stage, else that one is made by the
+// first call that overlaps the stages (a stream holds 1-2 MB of device memory)
+int ctx_create(int device, bool overlap, m4_ctx** out);
 Tuning tuning_for(const m4_ctx* c, const m4_opts* o);
 void run_resident(m4_ctx* c, const int64_t* rp, const int32_t* col, int64_t n, int64_t nnz,
-                  const m4_opts* o, hipStream_t s, Prep& P, bool want_timing);
+                  const m4_opts* o, hipStream_t s, Prep& P, bool want_timing,
+                  bool costs);
 // m4_noalloc.hip: the fixed scratch of the allocation-free entry point;
 // noalloc_setup() looks up its address on the current device (once per
 // device, from m4_ctx_create; a failed lookup leaves that entry point

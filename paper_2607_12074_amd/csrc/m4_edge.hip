@@ -146,7 +146,7 @@ void basis_costs(BasisChoice& b, const Tuning& tu, int64_t n, bool budgeted,
 }
 
 BasisChoice choose_basis(const Prep& P, const Tuning& tu, uint32_t flags, bool budgeted,
-                         Scal* scal, unsigned long long* in, hipStream_t s, const SmallInfo* si) {
+                         bool costs, Scal* scal, unsigned long long* in, hipStream_t s, const SmallInfo* si) {
   BasisChoice b;
   in[0] = in[1] = in[2] = 0;
   const bool forced = (flags & (M4_BASIS_WEDGE | M4_BASIS_EDGE)) != 0;
@@ -154,16 +154,16 @@ BasisChoice choose_basis(const Prep& P, const Tuning& tu, uint32_t flags, bool b
   if (si) {
     for (int i = 0; i < 3; i++) in[i] = si->cost[i];
   } else if (P.n > 0) {
-    k_edge_cost<<<grid, 256, 0, s>>>(P.dr, P.dplus, P.n, &scal->stat[ST_COST]);
     // beyond SMALL_N vertices the owners alone cost the edge stage more than the
-    // fixed part of the wedge stage (4167 are enough), and it scans at least an entry per wedge endpoint at the
-    // higher price: settled without waiting for the inputs (a read-back takes
-    // some 10 us of a call)
-    if (!forced && (budgeted || (tu.cost_edge_owner_ns * (double)P.n >= tu.cost_wedge_fixed_us * 1e3 &&
-                                 tu.cost_edge_ns >= tu.cost_wedge_ns))) {
-      b.pending = true;
-      return b;
-    }
+    // fixed part of the wedge stage (4167 are enough), and it scans at least an
+    // entry per wedge endpoint at the higher price: settled without waiting for
+    // the inputs (a read-back takes some 10 us of a call)
+    b.pending =
+        !forced && (budgeted || (tu.cost_edge_owner_ns * (double)P.n >= tu.cost_wedge_fixed_us * 1e3 &&
+                                 tu.cost_edge_ns >= tu.cost_wedge_ns));
+    if (costs || !b.pending)
+      k_edge_cost<<<grid, 256, 0, s>>>(P.dr, P.dplus, P.n, &scal->stat[ST_COST]);
+    if (b.pending) return b;
     M4_HIP(hipMemcpyAsync(in, &scal->stat[ST_COST], 24, hipMemcpyDeviceToHost, s));
     M4_HIP(hipStreamSynchronize(s));
   }

@@ -33,8 +33,6 @@ constexpr int ACC_Z = ACC_N;
 // edge-basis row entries, longest row)
 enum Stat { ST_STEPS = 0, ST_WEDGES, ST_LOOKUPS, ST_HITS, ST_COST, ST_N = 8 };
 
-// Triangle-owner buckets by out-degree k = d+(u).
-enum TriBucket { TB_NONE = 0, TB_WAVE, TB_LDS, TB_GLOBAL, TB_N = 4 };
 // 4-cycle-owner buckets by wedge bound.
 enum C4Bucket { CB_NONE = 0, CB_TINY, CB_HASH, CB_MED, CB_WIN, CB_BIN, CB_WIDE, CB_N };
 // radix digits of the 4-cycle bucket keys and slots of their bucket starts
@@ -86,8 +84,6 @@ struct Scal {
   unsigned int work_c4[8];  // ... of the 4-cycle stage (the stages may overlap)
   unsigned int nhub;  // vertices with a hub table (triangle stage)
   unsigned int pad2;
-  int64_t tri_start[TB_N + 1];
-  int64_t c4_start[CB_N + 1];
   unsigned long long out[6];
   unsigned long long basis[8];  // T, K4, C4_ni, S, P_ni, Paw_ni, D_ni, sum_t
   unsigned long long kstat[M4_NK][4];  // per kernel slot: elems, rows, aux, aux2
@@ -223,7 +219,8 @@ void scan_i64(const int64_t* in, int64_t count, int64_t* out, int64_t* tmp, hipS
 size_t radix_tmp_elems(int64_t count, int bits);
 void radix_pass(const uint32_t* keys_in, const int32_t* vals_in, int64_t count, int shift,
                 int bits, uint32_t* keys_out, int32_t* vals_out, int64_t* tmp,
-                int64_t* bucket_start /* nullable, [2^bits + 1] */, hipStream_t s);
+                int64_t* bucket_start /* nullable, [2^bits + 1] */, hipStream_t s,
+                int32_t* place = nullptr /* position of every value */);
 
 void fill_u32(void* p, uint32_t v, size_t count32, hipStream_t s);
 
@@ -269,13 +266,14 @@ struct TriCredits {
   int kmax = 0;
   std::function<void(hipStream_t, unsigned long long* n12, unsigned long long* n14)> launch;
 };
-// Workspace of a plan; with SmallInfo (the host's copy) its contents are there
-// already and nothing is planned or read back.
+// A stage's plan: its enqueue() buckets the owners (its workspace) and counts
+// them (scal->small); once the host has that back, its plan() makes the
+// launches.  Both stages share the read-back; graphs of up to SMALL_N vertices
+// are planned by small_prep() instead of the enqueues.
 struct TriWork {
   uint32_t* key;
   int32_t* order;
   int64_t* rtmp;
-  int64_t* start;
   int64_t* hoff64;  // resident runs: hub table offsets, then the out-list records
   int32_t* hoff;    // hub tables (null: none)
   int32_t* hub_list;
@@ -285,14 +283,24 @@ TriWork tri_work(const Prep& P, const Tuning& tu, Arena& tmp);
 // out-degree bounds of the register kernel (0: unused) and the wavefront kernel
 void tri_bounds(const Prep& P, const Tuning& tu, uint32_t flags, uint32_t cache_rows,
                 int* small_max, int* wave_max);
+void tri_enqueue(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags, uint32_t cache_rows,
+                 const TriWork& w, hipStream_t s);
 Launch tri_plan(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags, uint32_t cache_rows,
-                const TriWork& w, hipStream_t s, int num_cu,
-                const std::function<char*(size_t)>& big_scratch, KTimer* kt,
-                TriCredits* credits = nullptr, const SmallInfo* si = nullptr);
+                const TriWork& w, int num_cu, const std::function<char*(size_t)>& big_scratch,
+                KTimer* kt, const SmallInfo& si, TriCredits* credits = nullptr);
+// the counters of the enqueued plans
+inline SmallInfo read_plan(const Scal* scal, hipStream_t s) {
+  SmallInfo si;
+  M4_HIP(hipMemcpyAsync(&si, &scal->small, sizeof(si), hipMemcpyDeviceToHost, s));
+  M4_HIP(hipStreamSynchronize(s));
+  return si;
+}
 inline void tri_run(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags,
                     uint32_t cache_rows, Arena& tmp, hipStream_t s, int num_cu,
-                    const std::function<char*(size_t)>& big_scratch, KTimer* kt) {
-  tri_plan(P, scal, tu, flags, cache_rows, tri_work(P, tu, tmp), s, num_cu, big_scratch, kt)(s);
+                    const std::function<char*(size_t)>& big_scratch) {
+  const TriWork w = tri_work(P, tu, tmp);
+  tri_enqueue(P, scal, tu, flags, cache_rows, w, s);
+  tri_plan(P, scal, tu, flags, cache_rows, w, num_cu, big_scratch, nullptr, read_plan(scal, s))(s);
 }
 
 // m4_local.hip: per-vertex orbit counts of a prepared graph (t complete)
@@ -308,37 +316,41 @@ struct BasisChoice {
   bool pending = false;  // settled without the estimates: basis_costs() fills them in
   double cost_wedge = 0, cost_edge = 0;
 };
-// in[3]: the objective's inputs, read back where the choice needs them
+// in[3]: the objective's inputs, read back where the choice needs them; costs:
+// the estimates are wanted (in scal's stat[], if pending)
 BasisChoice choose_basis(const Prep& P, const Tuning& tu, uint32_t flags, bool budgeted,
-                         Scal* scal, unsigned long long* in, hipStream_t s, const SmallInfo* si);
+                         bool costs, Scal* scal, unsigned long long* in, hipStream_t s, const SmallInfo* si);
 void basis_costs(BasisChoice& b, const Tuning& tu, int64_t n, bool budgeted,
                  const unsigned long long* in);
 Launch edge_plan(const Prep& P, Scal* scal, uint32_t flags, int num_cu, KTimer* kt);
 
 // m4_c4.hip (binned, if given, is set when owners go to the large filter,
 // which holds every CU with a persistent workgroup and all of its LDS; n8, if
-// given, receives the per-vertex 4-cycle credits of every rank; si as in
-// tri_plan)
+// given, receives the per-vertex 4-cycle credits of every rank, which the
+// enqueue has to know of: credit)
 struct C4Work {
   int64_t* wub;
   uint32_t* key;
   int32_t* order;
   int64_t* rtmp;
-  int64_t* start;  // bucket starts (C4_START_SLOTS), then the two zone bounds
   int32_t* hlen;
   int64_t* hoff;
   int64_t* stmp;
   int4* vmeta;  // per-row records of full rows (a partition stores row prefixes instead)
 };
 C4Work c4_work(const Prep& P, Arena& tmp);
+void c4_enqueue(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, const C4Work& w,
+                hipStream_t s, bool credit, KTimer* kt);
 Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, uint32_t flags,
                const C4Work& w, hipStream_t s, int num_cu, KTimer* kt,
-               const std::function<char*(size_t)>& big_scratch, bool* binned = nullptr,
-               unsigned long long* n8 = nullptr, const SmallInfo* si = nullptr);
+               const std::function<char*(size_t)>& big_scratch, const SmallInfo& si,
+               bool* binned = nullptr, unsigned long long* n8 = nullptr);
 inline void c4_run(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, uint32_t flags,
-                   Arena& tmp, hipStream_t s, int num_cu, KTimer* kt,
+                   Arena& tmp, hipStream_t s, int num_cu,
                    const std::function<char*(size_t)>& big_scratch) {
-  c4_plan(P, C, scal, tu, flags, c4_work(P, tmp), s, num_cu, kt, big_scratch)(s);
+  const C4Work w = c4_work(P, tmp);
+  c4_enqueue(P, C, scal, tu, w, s, false, nullptr);
+  c4_plan(P, C, scal, tu, flags, w, s, num_cu, nullptr, big_scratch, read_plan(scal, s))(s);
 }
 
 // m4_small.hip: build_prep, the anchor objective's inputs and the plans of both

@@ -101,7 +101,7 @@ extern "C" int m4_count_motifs4_noalloc(m4_ctx* ctx, const m4_csr* g, const m4_o
     if (o) oo = *o;
     oo.flags &= ~(uint32_t)(M4_TIMING | M4_FORCE_PARTITION);
     Prep P;
-    run_resident(ctx, g->row_ptr, g->col, g->n, g->nnz, &oo, s, P, false);
+    run_resident(ctx, g->row_ptr, g->col, g->n, g->nnz, &oo, s, P, false, false);
     M4_HIP(hipMemcpyAsync(ctx->scal_host, ctx->scal, kScalHead, hipMemcpyDeviceToHost, s));
     M4_HIP(hipStreamSynchronize(s));
     const Scal& h = *ctx->scal_host;
@@ -117,7 +117,7 @@ extern "C" int m4_count_motifs4_noalloc(m4_ctx* ctx, const m4_csr* g, const m4_o
     // a workspace that did not fit: the launches queued before it finish
     // before the scratch can be handed to another call
     (void)hipStreamSynchronize(s);
-    (void)hipStreamSynchronize(ctx->stream2);
+    if (ctx->stream2) (void)hipStreamSynchronize(ctx->stream2);
     return set_error(ctx, f.code, f.msg);
   } catch (...) {
     return set_error(ctx, M4_EINTERNAL, "unexpected exception");

@@ -690,7 +690,7 @@ int count_partitioned(m4_ctx* c, const m4_csr* g, const m4_opts* o, uint64_t out
           P.own_lo = lo;
           P.own_hi = hi;
           Arena a = tmp_arena(tri_tmp);
-          tri_run(P, c->scal, tu, flags, o ? o->cache_rows : 0, a, s, c->num_cu, big, nullptr);
+          tri_run(P, c->scal, tu, flags, o ? o->cache_rows : 0, a, s, c->num_cu, big);
           M4_HIP(hipStreamSynchronize(s));
         });
   }
@@ -718,7 +718,7 @@ int count_partitioned(m4_ctx* c, const m4_csr* g, const m4_opts* o, uint64_t out
           P.own_lo = lo;
           P.own_hi = hi;
           Arena a = tmp_arena(c4_tmp);
-          c4_run(P, C, c->scal, tu, flags, a, s, c->num_cu, nullptr, big);
+          c4_run(P, C, c->scal, tu, flags, a, s, c->num_cu, big);
           M4_HIP(hipStreamSynchronize(s));
           P.row_len = nullptr;
         });

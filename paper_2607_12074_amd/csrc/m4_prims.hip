@@ -5,7 +5,7 @@ namespace m4 {
 
 namespace {
 
-constexpr int SCAN_T = 256, SCAN_I = 8, SCAN_TILE = SCAN_T * SCAN_I;
+constexpr int SCAN_T = 256, SCAN_I = 8, SCAN_TILE = SCAN_T * SCAN_I, SCAN_FLAT = 4096;
 constexpr int RAD_T = 256, RAD_ROUNDS = 16, RAD_TILE = RAD_T * RAD_ROUNDS;
 
 __device__ __forceinline__ int64_t wave_incl_scan(int64_t v, int lane) {
@@ -53,8 +53,16 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_tile_sums(const T* __restrict__
 template <typename T>
 __global__ __launch_bounds__(SCAN_T) void k_scan_tiles(const T* __restrict__ in, int64_t count,
                                                        const int64_t* __restrict__ offs,
+                                                       const int64_t* __restrict__ sums,
                                                        int64_t* __restrict__ out) {
   int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_I;
+  // the tile's offset: given, or the sum of the tiles before it
+  int64_t before = offs ? offs[blockIdx.x] : 0;
+  if (sums) {
+    int64_t part = 0;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += SCAN_T) part += sums[i];
+    block_excl_scan(part, &before);
+  }
   int64_t v[SCAN_I];
   int64_t sum = 0;
 #pragma unroll
@@ -63,7 +71,7 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_tiles(const T* __restrict__ in,
     v[k] = i < count ? (int64_t)in[i] : 0;
     sum += v[k];
   }
-  int64_t run = block_excl_scan(sum, nullptr) + (offs ? offs[blockIdx.x] : 0);
+  int64_t run = block_excl_scan(sum, nullptr) + before;
 #pragma unroll
   for (int k = 0; k < SCAN_I; k++) {
     int64_t i = base + k;
@@ -83,15 +91,23 @@ void scan_impl(const T* in, int64_t count, int64_t* out, int64_t* tmp, hipStream
   }
   int64_t nb = ceil_div(count, SCAN_TILE);
   if (nb == 1) {
-    k_scan_tiles<T><<<1, SCAN_T, 0, s>>>(in, count, nullptr, out);
+    k_scan_tiles<T><<<1, SCAN_T, 0, s>>>(in, count, nullptr, nullptr, out);
     return;
   }
   int64_t* sums = tmp;
+  // up to SCAN_FLAT tiles each adds the sums before its own (32 KB from L2 at
+  // most), which takes a launch less than a scan of the sums: a launch is
+  // 4-5 us of host time, the sums 1-2 us of the device's
+  if (nb <= SCAN_FLAT) {
+    k_scan_tile_sums<T><<<(unsigned)nb, SCAN_T, 0, s>>>(in, count, sums);
+    k_scan_tiles<T><<<(unsigned)nb, SCAN_T, 0, s>>>(in, count, nullptr, sums, out);
+    return;
+  }
   int64_t* offs = tmp + nb;
   int64_t* rest = tmp + 2 * nb + 1;
   k_scan_tile_sums<T><<<(unsigned)nb, SCAN_T, 0, s>>>(in, count, sums);
   scan_impl<int64_t>(sums, nb, offs, rest, s);
-  k_scan_tiles<T><<<(unsigned)nb, SCAN_T, 0, s>>>(in, count, offs, out);
+  k_scan_tiles<T><<<(unsigned)nb, SCAN_T, 0, s>>>(in, count, offs, nullptr, out);
 }
 
 // ------------------------------------------------------------- radix pass
@@ -124,7 +140,9 @@ __global__ __launch_bounds__(RAD_T) void k_radix_scatter(const uint32_t* __restr
                                                          int64_t count, int shift,
                                                          const int64_t* __restrict__ offs,
                                                          uint32_t* __restrict__ keys_out,
-                                                         int32_t* __restrict__ vals_out) {
+                                                         int32_t* __restrict__ vals_out,
+                                                         int32_t* __restrict__ place,
+                                                         int64_t* __restrict__ bucket_start) {
   constexpr int NB = 1 << BITS;
   constexpr int NW = RAD_T / WAVE;
   __shared__ unsigned int run[NB];
@@ -134,6 +152,10 @@ __global__ __launch_bounds__(RAD_T) void k_radix_scatter(const uint32_t* __restr
     run[d] = 0;
 #pragma unroll
     for (int k = 0; k < NW; k++) wcnt[k][d] = 0;
+    if (bucket_start && blockIdx.x == 0) {
+      bucket_start[d] = offs[(int64_t)d * gridDim.x];
+      if (d == 0) bucket_start[NB] = count;
+    }
   }
   __syncthreads();
   const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (WAVE - lane));
@@ -157,7 +179,9 @@ __global__ __launch_bounds__(RAD_T) void k_radix_scatter(const uint32_t* __restr
       for (int k = 0; k < w; k++) pre += wcnt[k][dig];
       int64_t pos = offs[(int64_t)dig * gridDim.x + blockIdx.x] + pre + rk;
       if (keys_out) keys_out[pos] = key;
-      vals_out[pos] = vals_in ? vals_in[i] : (int32_t)i;
+      const int32_t v = vals_in ? vals_in[i] : (int32_t)i;
+      vals_out[pos] = v;
+      if (place) place[v] = (int32_t)pos;
     }
     __syncthreads();
     for (int d = tid; d < NB; d += RAD_T) {
@@ -173,13 +197,6 @@ __global__ __launch_bounds__(RAD_T) void k_radix_scatter(const uint32_t* __restr
   }
 }
 
-__global__ void k_bucket_starts(const int64_t* offs, int64_t nb, int NB, int64_t count,
-                                int64_t* bucket_start) {
-  int d = threadIdx.x;
-  if (d < NB) bucket_start[d] = offs[(int64_t)d * nb];
-  if (d == NB) bucket_start[NB] = count;
-}
-
 __global__ void k_zero_starts(int64_t* bucket_start, int NB) {
   int d = threadIdx.x;
   if (d <= NB) bucket_start[d] = 0;
@@ -188,7 +205,7 @@ __global__ void k_zero_starts(int64_t* bucket_start, int NB) {
 template <int BITS>
 void radix_pass_t(const uint32_t* keys_in, const int32_t* vals_in, int64_t count, int shift,
                   uint32_t* keys_out, int32_t* vals_out, int64_t* tmp, int64_t* bucket_start,
-                  hipStream_t s) {
+                  int32_t* place, hipStream_t s) {
   constexpr int NB = 1 << BITS;
   if (count <= 0) {
     if (bucket_start) k_zero_starts<<<1, NB + 1, 0, s>>>(bucket_start, NB);
@@ -201,8 +218,7 @@ void radix_pass_t(const uint32_t* keys_in, const int32_t* vals_in, int64_t count
   k_radix_hist<BITS><<<(unsigned)nb, RAD_T, 0, s>>>(keys_in, count, shift, hist);
   scan_impl<int64_t>(hist, NB * nb, offs, stmp, s);
   k_radix_scatter<BITS><<<(unsigned)nb, RAD_T, 0, s>>>(keys_in, vals_in, count, shift, offs,
-                                                        keys_out, vals_out);
-  if (bucket_start) k_bucket_starts<<<1, NB + 1, 0, s>>>(offs, nb, NB, count, bucket_start);
+                                                        keys_out, vals_out, place, bucket_start);
 }
 
 __global__ void k_fill_u32(uint32_t* p, uint32_t v, size_t n) {
@@ -238,11 +254,11 @@ size_t radix_tmp_elems(int64_t count, int bits) {
 
 void radix_pass(const uint32_t* keys_in, const int32_t* vals_in, int64_t count, int shift, int bits,
                 uint32_t* keys_out, int32_t* vals_out, int64_t* tmp, int64_t* bucket_start,
-                hipStream_t s) {
+                hipStream_t s, int32_t* place) {
   switch (bits) {
-    case 2: radix_pass_t<2>(keys_in, vals_in, count, shift, keys_out, vals_out, tmp, bucket_start, s); break;
-    case 4: radix_pass_t<4>(keys_in, vals_in, count, shift, keys_out, vals_out, tmp, bucket_start, s); break;
-    case 8: radix_pass_t<8>(keys_in, vals_in, count, shift, keys_out, vals_out, tmp, bucket_start, s); break;
+    case 2: radix_pass_t<2>(keys_in, vals_in, count, shift, keys_out, vals_out, tmp, bucket_start, place, s); break;
+    case 4: radix_pass_t<4>(keys_in, vals_in, count, shift, keys_out, vals_out, tmp, bucket_start, place, s); break;
+    case 8: radix_pass_t<8>(keys_in, vals_in, count, shift, keys_out, vals_out, tmp, bucket_start, place, s); break;
     default: throw Fail(M4_EINTERNAL, "radix_pass: unsupported digit width");
   }
 }

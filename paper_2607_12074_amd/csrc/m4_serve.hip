@@ -149,8 +149,8 @@ extern "C" int m4_server_create(m4_ctx* ctx, uint64_t budget, int max_queue, m4_
   *out = nullptr;
   m4_server* s = new (std::nothrow) m4_server();
   if (!s) return M4_ENOMEM;
-  int rc = m4_ctx_create(ctx->device, &s->dev.ctx);
-  if (rc == M4_OK) rc = m4_ctx_create(ctx->device, &s->dev.big_ctx);
+  int rc = m4::ctx_create(ctx->device, false, &s->dev.ctx);
+  if (rc == M4_OK) rc = m4::ctx_create(ctx->device, false, &s->dev.big_ctx);
   if (rc != M4_OK) {
     m4_ctx_destroy(s->dev.ctx);
     delete s;

@@ -17,7 +17,6 @@
 // one workgroup with the bitmap in global scratch (larger k).  Block-local sums
 // are folded into one 128-bit atomic per workgroup (block-local aggregation).
 #include <limits.h>
-#include <string.h>
 
 #include <algorithm>
 #include <array>
@@ -678,21 +677,23 @@ __global__ void k_tri_keys(const int32_t* __restrict__ dplus, int64_t n, int64_t
   if (u >= n) return;
   int k = (u >= own_lo && u < own_hi) ? dplus[u] : 0;
   const uint32_t b = tri_bucket(k, small_max, wave_max);
-  if (b == TK_GLOBAL) atomicMax((unsigned int*)&scal->work[7], (unsigned int)k);
+  if (b == TK_GLOBAL) atomicMax(&scal->small.kmax, (unsigned int)k);
   key[u] = b;
 }
 
 // Hub tables (a vertex with out-degree >= hub_min gets an open-addressing
 // table of its out-list, mapping a rank to its position in N+(v)).
-__global__ void k_hub_size(const int32_t* __restrict__ dplus, int64_t n, int hub_min,
-                           int32_t* __restrict__ hsz, int32_t* __restrict__ hubs,
-                           unsigned int* __restrict__ nhub) {
+__global__ __launch_bounds__(256) void k_hub_size(const int32_t* __restrict__ dplus, int64_t n,
+                                                  int hub_min, int32_t* __restrict__ hsz,
+                                                  int32_t* __restrict__ hubs, Scal* scal) {
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n) return;
-  const int L = dplus[v];
-  const bool hub = L >= hub_min;
-  hsz[v] = hub ? (1 << hub_bits(L)) : 0;
-  if (hub) hubs[atomicAdd(nhub, 1u)] = (int32_t)v;
+  const int L = v < n ? dplus[v] : 0;
+  const bool hub = v < n && L >= hub_min;
+  const int slots = hub ? (1 << hub_bits(L)) : 0;
+  if (v < n) hsz[v] = slots;
+  if (hub) hubs[atomicAdd(&scal->nhub, 1u)] = (int32_t)v;
+  block_add_u64<256>(reinterpret_cast<unsigned long long*>(&scal->small.hub_slots),
+                     (unsigned long long)slots);
 }
 
 __global__ void k_hub_off(const int32_t* __restrict__ hsz, const int64_t* __restrict__ off64,
@@ -776,8 +777,7 @@ TriWork tri_work(const Prep& P, const Tuning& tu, Arena& tmp) {
   w.key = tmp.take<uint32_t>(n);
   w.order = tmp.take<int32_t>(n);
   w.rtmp = tmp.take<int64_t>(radix_tmp_elems(n, 4));
-  w.start = tmp.take<int64_t>(17);
-  if (!w.key || !w.order || !w.rtmp || !w.start) throw Fail(M4_EINTERNAL, "workspace too small (tri)");
+  if (!w.key || !w.order || !w.rtmp) throw Fail(M4_EINTERNAL, "workspace too small (tri)");
   if (full_rows(P)) {
     w.hoff64 = tmp.take<int64_t>(n + 1);
     if (!w.hoff64) throw Fail(M4_EINTERNAL, "workspace too small (out-lists)");
@@ -804,46 +804,44 @@ void tri_bounds(const Prep& P, const Tuning& tu, uint32_t flags, uint32_t cache_
   *small_max = small ? std::min(*wave_max, TRI_SMALL) : 0;
 }
 
+void tri_enqueue(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags, uint32_t cache_rows,
+                 const TriWork& w, hipStream_t s) {
+  const int64_t n = P.n;
+  if (n == 0 || P.m == 0) return;
+  if (!full_rows(P)) {  // one of several plans on these counters
+    fill_u32(&scal->work[0], 0, 8, s);
+    fill_u32(&scal->small.kmax, 0, 1, s);
+  }
+  int small_max, wave_max;
+  tri_bounds(P, tu, flags, cache_rows, &small_max, &wave_max);
+  k_tri_keys<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(P.dplus, n, P.own_lo, P.hi(), small_max,
+                                                        wave_max, w.key, scal);
+  radix_pass(w.key, nullptr, n, 0, 4, nullptr, w.order, w.rtmp, scal->small.tri_start, s);
+  if (w.hoff) {
+    int32_t* hsz = reinterpret_cast<int32_t*>(w.key);  // the keys are in order[] now
+    k_hub_size<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(P.dplus, n, tu.hub_min, hsz, w.hub_list,
+                                                          scal);
+    scan_i32(hsz, n, w.hoff64, w.hst, s);
+  }
+}
+
 Launch tri_plan(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags, uint32_t cache_rows,
-                const TriWork& w, hipStream_t s, int num_cu,
-                const std::function<char*(size_t)>& big_scratch, KTimer* kt, TriCredits* credits,
-                const SmallInfo* si) {
+                const TriWork& w, int num_cu, const std::function<char*(size_t)>& big_scratch,
+                KTimer* kt, const SmallInfo& si, TriCredits* credits) {
   const int64_t n = P.n;
   if (n == 0 || P.m == 0) return [](hipStream_t) {};
   int32_t* order = w.order;
-  const int64_t* start = si ? scal->small.tri_start : w.start;
+  const int64_t* start = scal->small.tri_start;
   int32_t* hoff = w.hoff;
   int32_t* hub_list = w.hub_list;
   int64_t* hoff64 = w.hoff64;
   int2* list = reinterpret_cast<int2*>(hoff64);  // takes its place once hoff is made of it
-  int32_t* hsz = reinterpret_cast<int32_t*>(w.key);  // the keys are in order[] then
+  int32_t* hsz = reinterpret_cast<int32_t*>(w.key);
   const bool hubs = hoff != nullptr;
   // largest out-degree of the global bucket decides its scratch size
-  unsigned int kmax_g = 0;
-  int64_t hstart[17];
-  int64_t hub_slots = 0;
-  if (si) {
-    kmax_g = si->kmax;
-    memcpy(hstart, si->tri_start, sizeof(hstart));
-    hub_slots = si->hub_slots;
-  } else {
-    int small_max, wave_max;
-    tri_bounds(P, tu, flags, cache_rows, &small_max, &wave_max);
-    fill_u32(&scal->work[0], 0, 8, s);
-    k_tri_keys<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(P.dplus, n, P.own_lo, P.hi(), small_max,
-                                                          wave_max, w.key, scal);
-    radix_pass(w.key, nullptr, n, 0, 4, nullptr, order, w.rtmp, w.start, s);
-    if (hubs) {
-      fill_u32(&scal->nhub, 0, 1, s);
-      k_hub_size<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(P.dplus, n, tu.hub_min, hsz, hub_list,
-                                                            &scal->nhub);
-      scan_i32(hsz, n, hoff64, w.hst, s);
-    }
-    M4_HIP(hipMemcpyAsync(&kmax_g, &scal->work[7], sizeof(kmax_g), hipMemcpyDeviceToHost, s));
-    M4_HIP(hipMemcpyAsync(hstart, start, sizeof(hstart), hipMemcpyDeviceToHost, s));
-    if (hubs) M4_HIP(hipMemcpyAsync(&hub_slots, hoff64 + n, 8, hipMemcpyDeviceToHost, s));
-    M4_HIP(hipStreamSynchronize(s));
-  }
+  const unsigned int kmax_g = si.kmax;
+  const int64_t* hstart = si.tri_start;
+  const int64_t hub_slots = si.hub_slots;
   // scratch: hub tables, then the dense-owner bitmaps
   size_t hub_bytes = 0, dense_bytes = 0, dense_bits = 0, dense_blocks = 0;
   const bool use_hubs = hubs && hub_slots > 0 && hub_slots < (int64_t(1) << 31);
@@ -937,7 +935,7 @@ Launch tri_plan(const Prep& P, Scal* scal, const Tuning& tu, uint32_t flags, uin
       run_small(B, true_type{}, ls);
     };
   }
-  const bool planned = si != nullptr;
+  const bool planned = full_rows(P) && n <= SMALL_N;  // offsets and records are there
   // everything below runs on the launch stream, after the plan above
   return [=](hipStream_t ls) mutable {
     if (kt) kt->begin(M4_K_TRI_HUBS, ls);
