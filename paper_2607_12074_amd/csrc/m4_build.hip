@@ -11,7 +11,7 @@
 #include <type_traits>
 #include <utility>
 
-#include "m4_internal.h"
+#include "m4_device.h"
 
 namespace m4 {
 
@@ -155,7 +155,12 @@ __global__ __launch_bounds__(256) void k_row_small(const int64_t* __restrict__ r
   }
 }
 
-// Rows of degree in (64, CAP]: one workgroup, bitonic sort in LDS.
+// Rows of degree in (64, CAP]: one workgroup, bitonic sort in LDS.  The whole
+// build of the scale-24 web graph took 17.2 ms with an entry to a thread (every
+// other one idle) and a barrier after each stage, 16.1 with pairs, 14.0 with a
+// wavefront for rows up to 256, two up to 1024 and four up to 2048 (two, four
+// and eight before); 512 threads up to 8192 are as fast there, and slower
+// (0.27 for 0.25 ms) where few rows are that long.
 template <int CAP, int NT>
 __global__ __launch_bounds__(NT) void k_row_bitonic(const int64_t* __restrict__ rp,
                                                     const int32_t* __restrict__ col,
@@ -186,22 +191,25 @@ __global__ __launch_bounds__(NT) void k_row_bitonic(const int64_t* __restrict__ 
   }
   if (mybelow) atomicAdd(&below, mybelow);
   __syncthreads();
+  // thread p takes pair p of a stage; pairs 64 apart or less stay within the 128
+  // entries of 64 consecutive p, that is within a wavefront, so only the stages
+  // that are wider, or come before one, end with a barrier
   for (int k = 2; k <= P; k <<= 1) {
     for (int jj = k >> 1; jj > 0; jj >>= 1) {
-      for (int i = threadIdx.x; i < P; i += NT) {
-        int ixj = i ^ jj;
-        if (ixj > i) {
-          int32_t a = s[i], b = s[ixj];
-          bool up = (i & k) == 0;
-          if ((a > b) == up) {
-            s[i] = b;
-            s[ixj] = a;
-          }
+      for (int p = threadIdx.x; p < P / 2; p += NT) {
+        const int i = ((p & ~(jj - 1)) << 1) | (p & (jj - 1)), ixj = i | jj;
+        const int32_t a = s[i], b = s[ixj];
+        const bool up = (i & k) == 0;
+        if ((a > b) == up) {
+          s[i] = b;
+          s[ixj] = a;
         }
       }
-      __syncthreads();
+      if (jj > WAVE || (jj == 1 && k > WAVE)) __syncthreads();
+      else wave_sync();
     }
   }
+  __syncthreads();
   int32_t* out = ncol + nptr[li];
   for (int i = threadIdx.x; i < d; i += NT) out[i] = s[i];
   if (threadIdx.x == 0) {
@@ -330,13 +338,13 @@ void sort_rows(const int64_t* rp, const int32_t* col, const int32_t* perm, const
   small(std::integral_constant<int, 32>{}, b[2], b[3]);
   small(std::integral_constant<int, 64>{}, b[3], b[4]);
   if (b[5] > b[4])
-    k_row_bitonic<256, 128><<<(unsigned)(b[5] - b[4]), 128, 0, s>>>(
+    k_row_bitonic<256, 64><<<(unsigned)(b[5] - b[4]), 64, 0, s>>>(
         rp, col, perm, rank, nptr, dr, b[4], ncol, dlo, dplus, r_base);
   if (b[6] > b[5])
-    k_row_bitonic<1024, 256><<<(unsigned)(b[6] - b[5]), 256, 0, s>>>(
+    k_row_bitonic<1024, 128><<<(unsigned)(b[6] - b[5]), 128, 0, s>>>(
         rp, col, perm, rank, nptr, dr, b[5], ncol, dlo, dplus, r_base);
   if (b[7] > b[6])
-    k_row_bitonic<2048, 512><<<(unsigned)(b[7] - b[6]), 512, 0, s>>>(
+    k_row_bitonic<2048, 256><<<(unsigned)(b[7] - b[6]), 256, 0, s>>>(
         rp, col, perm, rank, nptr, dr, b[6], ncol, dlo, dplus, r_base);
   // up to 16384 entries a row is one bitonic sort in LDS (gathering each
   // entry's rank once); longer rows take the bitmap windows
