@@ -403,8 +403,7 @@ __device__ __forceinline__ void count_direct(const C4Args& A, uint4* cnt4, int2*
 }
 
 // Graphs of at most SMALL_N vertices: every owner above the tiny bound,
-// whatever its bucket (one window, no cursors, no bitmaps, and no bucket size
-// that the host has to wait for).
+// whatever its bucket (one window, no cursors, no bitmaps, one launch).
 template <bool CRED>
 __global__ __launch_bounds__(256) void k_c4_direct(C4Args A) {
   constexpr int NT = 256, SEGS = 256;
