@@ -79,6 +79,12 @@ __global__ __launch_bounds__(NT) void k_batch(BatchArgs A) {
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid / WAVE;
 
   for (;;) {
+    // Every way round the loop meets here.  Without this barrier the compiler
+    // joins the "thread 0 writes a status" branch of a graph that is passed
+    // over with the "thread 0 takes an item" branch below: the other threads
+    // then return straight to the second barrier, an inner loop that runs
+    // before thread 0's way round, and read the old item for ever.
+    __syncthreads();
     if (tid == 0) s_item = (int)atomicAdd(A.work, 1u);
     __syncthreads();
     const int64_t item = s_item;
