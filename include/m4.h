@@ -125,8 +125,9 @@ enum {
  *                   words the kernel read from out-lists and hub tables (one
  *                   per scanned element, two per 8-byte table slot probed)
  *   4-cycle slots:  k_elems = wedge endpoints counted, k_rows = owners,
- *                   k_aux = lower neighbours (segments), k_aux2 = segment
- *                   visits (window slot) or walks over an owner's rows
+ *                   k_aux = lower neighbours read (segments; the filters
+ *                   and the table read those of degree above 1), k_aux2 =
+ *                   segment visits (window slot) or walks over an owner's rows
  *                   (filters; a tiny owner's endpoints for the table)
  *   edge basis:     k_elems = row entries scanned, k_rows = owners with an
  *                   out-neighbour, k_aux = (out-neighbour, neighbour) pairs

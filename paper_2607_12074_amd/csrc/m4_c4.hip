@@ -49,7 +49,7 @@ struct C4Args {
   const int32_t* ncol;
   const int32_t* dr;
   const int32_t* dlo;
-  const int64_t* wub;
+  const int2* wub;         // {wedge bound, lower neighbours of degree above 1}
   const int32_t* row_len;  // stored prefix of every row (null: full rows)
   int64_t r1;
   int bucket;
@@ -84,14 +84,19 @@ constexpr int32_t C4_DIRECT_SPAN = 262144;
 constexpr int64_t C4_BIN_RANGE = 131072;
 constexpr int C4_MAX_PARTS = 4096;
 
-// wedge bound of every owner: G lanes cooperate on one row, 4 loads in flight
+// Wedge bound of every owner and its lower neighbours of degree above 1, the
+// last of its lower entries (an entry of degree 1 is below r1 and holds no
+// endpoint): the kernels read only those.  The bound stays below 2^31, since
+// every CSR entry is an endpoint of an owner once at most.  A hub of 10^6 leaves
+// with 180 wedges took its one wavefront 52 ms with the leaves.
+// G lanes cooperate on one row, 4 loads in flight.
 template <int G>
 __global__ __launch_bounds__(256) void k_c4_plan(const int64_t* __restrict__ nptr,
                                                  const int32_t* __restrict__ ncol,
                                                  const int32_t* __restrict__ dr,
                                                  const int32_t* __restrict__ dlo, int64_t r_lo,
                                                  int64_t r_hi, int64_t r1, C4Plan pl,
-                                                 int64_t* __restrict__ wub,
+                                                 int2* __restrict__ wub,
                                                  uint32_t* __restrict__ key, int64_t own_lo,
                                                  int64_t own_hi) {
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -105,18 +110,27 @@ __global__ __launch_bounds__(256) void k_c4_plan(const int64_t* __restrict__ npt
   int nl = ok ? dlo[u] : 0;
   int64_t b = ok ? nptr[u] : 0;
   int64_t s = 0;
+  int nw = 0;
   int i = j;
   for (; i + 3 * G < nl; i += 4 * G) {
     int32_t v0 = ncol[b + i], v1 = ncol[b + i + G], v2 = ncol[b + i + 2 * G], v3 = ncol[b + i + 3 * G];
     s += (int64_t)dr[v0] + dr[v1] + dr[v2] + dr[v3] - 4;
+    nw += (v0 >= r1) + (v1 >= r1) + (v2 >= r1) + (v3 >= r1);
   }
-  for (; i < nl; i += G) s += dr[ncol[b + i]] - 1;
+  for (; i < nl; i += G) {
+    const int32_t v = ncol[b + i];
+    s += dr[v] - 1;
+    nw += v >= r1;
+  }
 #pragma unroll
-  for (int o = G / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, WAVE);
+  for (int o = G / 2; o > 0; o >>= 1) {
+    s += __shfl_xor(s, o, WAVE);
+    nw += __shfl_xor(nw, o, WAVE);
+  }
   if (ok && j == 0) {
-    wub[u] = s;
+    wub[u] = make_int2((int)s, nw);
     uint32_t k = CB_NONE;
-    if (u >= r1 && nl >= 2 && s > 0) k = c4_bucket(pl, s, u, nl);
+    if (u >= r1 && nl >= 2 && s > 0) k = c4_bucket(pl, s, u, nw);
     key[u] = k;
   }
 }
@@ -127,7 +141,7 @@ __global__ __launch_bounds__(1024) void k_c4_plan_big(const int64_t* __restrict_
                                                       const int32_t* __restrict__ dr,
                                                       const int32_t* __restrict__ dlo, int64_t r_lo,
                                                       int64_t r1, C4Plan pl,
-                                                      int64_t* __restrict__ wub,
+                                                      int2* __restrict__ wub,
                                                       uint32_t* __restrict__ key, int64_t own_lo,
                                                       int64_t own_hi) {
   int64_t u = r_lo + blockIdx.x;
@@ -138,13 +152,19 @@ __global__ __launch_bounds__(1024) void k_c4_plan_big(const int64_t* __restrict_
   int nl = dlo[u];
   int64_t b = nptr[u];
   int64_t s = 0;
-  for (int i = threadIdx.x; i < nl; i += 1024) s += dr[ncol[b + i]] - 1;
-  int64_t tot;
-  block_excl_scan64<1024>(s, &tot);
+  // both sums stay below 2^31: one scan of the pair
+  for (int i = threadIdx.x; i < nl; i += 1024) {
+    const int32_t v = ncol[b + i];
+    s += dr[v] - 1 + ((int64_t)(v >= r1) << 32);
+  }
+  int64_t both;
+  block_excl_scan64<1024>(s, &both);
   if (threadIdx.x == 0) {
-    wub[u] = tot;
+    const int64_t tot = (uint32_t)both;
+    const int nw = (int)(both >> 32);
+    wub[u] = make_int2((int)tot, nw);
     uint32_t k = CB_NONE;
-    if (u >= r1 && nl >= 2 && tot > 0) k = c4_bucket(pl, tot, u, nl);
+    if (u >= r1 && nl >= 2 && tot > 0) k = c4_bucket(pl, tot, u, nw);
     key[u] = k;
   }
 }
@@ -224,9 +244,9 @@ __global__ __launch_bounds__(WAVE) void k_c4_tiny(C4Args A) {
     const int64_t mine = first + lane;
     const bool have = lane < A.grab && mine < cnt;
     const int32_t mu = have ? A.order[b0 + mine] : 0;
-    const int32_t mnl = have ? A.dlo[mu] : 0;
-    const int64_t mbase = have ? A.nptr[mu] : 0;
-    const int32_t mwb = have ? (int32_t)A.wub[mu] : 0;
+    const int2 mw = have ? A.wub[mu] : make_int2(0, 0);
+    const int32_t mwb = mw.x, mnl = mw.y;
+    const int64_t mbase = have ? A.nptr[mu] + A.dlo[mu] - mnl : 0;
     const int nown = (int)std::min<int64_t>(A.grab, cnt - first);
     for (int o = 0; o < nown; o++) {
       const int32_t u = __builtin_amdgcn_readlane(mu, o);
@@ -417,10 +437,10 @@ __global__ __launch_bounds__(256) void k_c4_direct(C4Args A) {
   for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
     const int64_t at = b0 + items - 1 - item;  // heaviest owners (highest ranks) first
     const int32_t u = __builtin_amdgcn_readfirstlane(A.order[at]);
-    const int nl = __builtin_amdgcn_readfirstlane(A.dlo[u]);
+    const int nl = __builtin_amdgcn_readfirstlane(A.wub[u].y);
     unsigned long long own = 0, wedges = 0;
-    count_direct<NT, SMALL_N, SEGS, CRED>(A, cnt4, sg, sv, &s_next, A.nptr[u], nl, A.zr1, u,
-                                              acc, wedges, own);
+    count_direct<NT, SMALL_N, SEGS, CRED>(A, cnt4, sg, sv, &s_next, A.nptr[u] + A.dlo[u] - nl, nl,
+                                          A.zr1, u, acc, wedges, own);
     if (CRED) {
       own = lane_group_sum<WAVE>(own);
       if (lane == 0 && own) atomicAdd(&A.n8[u], own);
@@ -565,12 +585,13 @@ __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
     if (A.parts) part = A.parts[pos];
     else part.x = A.order[b0 + pos];
     const int32_t u = __builtin_amdgcn_readfirstlane(part.x);
-    const int nl = __builtin_amdgcn_readfirstlane(A.dlo[u]);
-    const int64_t base = A.nptr[u];
+    const int2 bound = A.wub[u];
+    const int nl = __builtin_amdgcn_readfirstlane(bound.y);
+    const int64_t base = A.nptr[u] + A.dlo[u] - nl;
     const int32_t lo = A.parts ? __builtin_amdgcn_readfirstlane(part.y) : A.zr1;
     const int32_t hi = A.parts ? __builtin_amdgcn_readfirstlane(part.z) : u;
     const unsigned long long wb =
-        A.parts ? (unsigned long long)part.w : (unsigned long long)A.wub[u];
+        A.parts ? (unsigned long long)part.w : (unsigned long long)bound.x;
     owners += lo == A.zr1;
     segs += (unsigned long long)nl;
     unsigned long long own = 0;
@@ -804,7 +825,7 @@ __global__ void k_vmeta(const int64_t* __restrict__ nptr, const int32_t* __restr
 // Lengths of the heavy owners' lists: segment descriptors of a window owner,
 // parts of a large filtered one (the two are adjacent in the bucket order).
 __global__ void k_c4_heavy_len(const int32_t* __restrict__ order, const int64_t* __restrict__ start,
-                               const int32_t* __restrict__ dlo, const int64_t* __restrict__ wub,
+                               const int32_t* __restrict__ dlo, const int2* __restrict__ wub,
                                int64_t H, int32_t* __restrict__ len) {
   const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (h >= H) return;
@@ -812,7 +833,7 @@ __global__ void k_c4_heavy_len(const int32_t* __restrict__ order, const int64_t*
   if (h < start[CB_WIN + 1] - start[CB_WIN]) {
     len[h] = dlo[u];
   } else {
-    const int64_t k = (wub[u] + C4_BIN_RANGE - 1) / C4_BIN_RANGE;
+    const int64_t k = (wub[u].x + C4_BIN_RANGE - 1) / C4_BIN_RANGE;
     len[h] = (int32_t)(k < C4_MAX_PARTS ? k : C4_MAX_PARTS);
   }
 }
@@ -821,7 +842,7 @@ __global__ void k_c4_heavy_len(const int32_t* __restrict__ order, const int64_t*
 // of endpoints (an endpoint's chance to be rank x is about proportional to the
 // degree of x, and the row offsets are the degrees' prefix sums).  One thread
 // per part; off holds the first part of each owner.
-__global__ void k_c4_parts(const int32_t* __restrict__ owner, const int64_t* __restrict__ wub,
+__global__ void k_c4_parts(const int32_t* __restrict__ owner, const int2* __restrict__ wub,
                            const int64_t* __restrict__ nptr, const int64_t* __restrict__ off,
                            int64_t H, int64_t total, int64_t r1, int4* __restrict__ parts) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -836,7 +857,7 @@ __global__ void k_c4_parts(const int32_t* __restrict__ owner, const int64_t* __r
     return (int32_t)lower_index(nptr, r1, (int64_t)u,
                                 d0 + (int64_t)((double)(d1 - d0) * (double)q / (double)k));
   };
-  const int64_t w = (wub[u] + k - 1) / k;
+  const int64_t w = (wub[u].x + k - 1) / k;
   parts[i] = make_int4(u, cut(p), cut(p + 1), (int)(w < INT_MAX ? w : INT_MAX));
 }
 
@@ -1203,7 +1224,7 @@ inline unsigned blocks_for(int64_t n, int nt) { return (unsigned)ceil_div(n > 0 
 C4Work c4_work(const Prep& P, Arena& tmp) {
   const int64_t n = P.n;
   C4Work w{};
-  w.wub = tmp.take<int64_t>(n);
+  w.wub = tmp.take<int2>(n);
   w.key = tmp.take<uint32_t>(n);
   w.order = tmp.take<int32_t>(n);
   w.rtmp = tmp.take<int64_t>(radix_tmp_elems(n, C4_KEY_BITS));
@@ -1246,7 +1267,7 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
                unsigned long long* n8) {
   const int64_t n = P.n;
   if (n == 0 || P.m == 0) return [](hipStream_t) {};
-  int64_t* wub = w.wub;
+  int2* wub = w.wub;
   int32_t* order = w.order;
   const int64_t* start = scal->small.c4_start;
   int32_t* hlen = w.hlen;

@@ -329,7 +329,7 @@ Launch edge_plan(const Prep& P, Scal* scal, uint32_t flags, int num_cu, KTimer* 
 // given, receives the per-vertex 4-cycle credits of every rank, which the
 // enqueue has to know of: credit)
 struct C4Work {
-  int64_t* wub;
+  int2* wub;  // {wedge bound, lower neighbours of degree above 1}
   uint32_t* key;
   int32_t* order;
   int64_t* rtmp;

@@ -57,7 +57,8 @@ __device__ __forceinline__ int64_t c4_windows(const int64_t* zb, int64_t r1, int
   return (words + C4_WIN_WORDS - 1) / C4_WIN_WORDS;
 }
 
-// Bucket of owner u with wedge bound w > 0 and nl lower neighbours.  Owners up
+// Bucket of owner u with wedge bound w > 0 and nl lower neighbours of degree
+// above 1.  Owners up
 // to C4_TINY_MAX wedges take one wavefront and a table, the ones above a
 // bitmap filter sized to their bound.  Beyond the one-pass medium bound a
 // dense window costs a pass over the owner's lower neighbours, so an owner

@@ -173,7 +173,8 @@ struct SmallRow {
   int32_t* ncol;
   int32_t* dlo;
   int32_t* dplus;
-  int64_t* wub;    // wedge bound: sum of (degree - 1) over the lower neighbours
+  int2* wub;       // {wedge bound, lower neighbours of degree above 1}; the bound is the
+                   // sum of (degree - 1) over the lower neighbours
   int4* vmeta;     // {row offset, degree, lower neighbours, entries below r1}
   int64_t* dsum;   // sum of the neighbours' degrees
   uint32_t* t;
@@ -254,7 +255,7 @@ __global__ __launch_bounds__(SM_ROW_NT) void k_small_rows(SmallRow A) {
     if (lane == 0) {
       A.dlo[r] = below;
       A.dplus[r] = d - below;
-      A.wub[r] = wb;
+      A.wub[r] = make_int2(wb, below - min(cut, below));
       A.dsum[r] = ds;
       A.vmeta[r] = make_int4((int)out0, d, below, cut);
     }
@@ -290,7 +291,7 @@ __global__ __launch_bounds__(SM_ROW_NT) void k_small_rows(SmallRow A) {
       const int below = (int)(uint32_t)ntot, cut = (int)(ntot >> 32);
       A.dlo[r] = below;
       A.dplus[r] = d - below;
-      A.wub[r] = stot >> 32;
+      A.wub[r] = make_int2((int)(stot >> 32), below - min(cut, below));
       A.dsum[r] = (uint32_t)stot;
       A.vmeta[r] = make_int4((int)out0, d, below, cut);
     }
@@ -310,7 +311,7 @@ struct SmallPlan {
   int32_t* hoff;
   int32_t* hub_list;
   C4Plan pl;  // r1 is read on the device
-  const int64_t* wub;
+  const int2* wub;
   const int64_t* dsum;
   int32_t* c4_order;
 };
@@ -415,9 +416,9 @@ __global__ __launch_bounds__(PL_NT) void k_small_plan(SmallPlan A, Scal* scal) {
   int64_t wedge = 0, lower = 0, scan = 0;
 #pragma unroll 2
   for (int i = tid; i < n; i += PL_NT) {
-    const int64_t wb = A.wub[i];
-    const int nl = A.dlo[i];
-    val[i] = i >= pl.r1 && nl >= 2 && wb > 0 ? (int)c4_bucket(pl, wb, i, nl) : (int)CB_NONE;
+    const int2 wb = A.wub[i];
+    val[i] = i >= pl.r1 && A.dlo[i] >= 2 && wb.x > 0 ? (int)c4_bucket(pl, wb.x, i, wb.y)
+                                                     : (int)CB_NONE;
     const int64_t dg = A.dr[i], k = A.dplus[i];
     if (dg >= 2) wedge += (dg - 1) * k;
     lower += dg * k;
