@@ -1,0 +1,102 @@
+"""The bitmap filters themselves, with and without per-vertex credits: owners
+whose endpoints are thin over many ranks, so that no part of them is counted
+directly.
+
+m vertices stand at chosen places among T of degree 2 (the rest a ring), each
+joined to two middles; a hub is joined to the middles and has pendants enough to
+rank highest.  The hub's endpoints are the m vertices, each met twice: wedge
+bound 2 m, m candidates.  Without pendants and ring the graph is K_{2, m+1}."""
+from math import comb
+
+import numpy as np
+import pytest
+
+import graphgen as gg
+
+pytestmark = pytest.mark.gpu
+DIRECT_SPAN = 262144  # ranks of a part that is counted directly
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import paper_2607_12074_amd as m4
+    c = m4.Context(0)
+    yield c
+    c.close()
+
+
+def thin(places, total):
+    """(graph, middles, hub): ids 0 .. total - 1 have degree 2, in rank order."""
+    m = len(places)
+    ring = np.setdiff1d(np.arange(total), places)
+    mid, hub = total + np.arange(2), total + 2
+    pend = hub + 1 + np.arange(m + 2)
+    src = np.concatenate([np.tile(places, 2), mid, np.full(m + 2, hub), ring])
+    dst = np.concatenate([np.repeat(mid, m), np.full(2, hub), pend, np.roll(ring, 1)])
+    return gg.from_edges(hub + m + 3, src.astype(np.int32), dst.astype(np.int32)), mid, hub
+
+
+def spread(m, total, seed=1):
+    return np.sort(np.random.default_rng(seed).choice(total, m, replace=False))
+
+
+def check(ctx, places, total, walks=None, **tuning):
+    import paper_2607_12074_amd as m4
+    m = len(places)
+    g, mid, hub = thin(places, total)
+    n = len(g[0]) - 1
+    base = ctx.get_tuning()
+    slots = [m4.KERNELS.index(k) for k in ("c4_hash", "c4_med", "c4_bin")]
+    try:
+        ctx.set_tuning(**tuning)
+        got, st = ctx.count(*g, flags=m4.M4_BASIS_WEDGE, stats=True)
+        orb = ctx.orbits(*g)[:, 4]
+    finally:
+        ctx.set_tuning(**base)
+    assert got[3] == comb(m + 1, 2)
+    want = np.zeros(n, np.uint64)
+    want[places] = want[hub] = m
+    want[mid] = comb(m + 1, 2)
+    assert (orb == want).all()
+    return {k: (st["k_rows"][i], st["k_elems"][i], st["k_aux2"][i])
+            for k, i in zip(("hash", "med", "bin"), slots)}
+
+
+# the hub's wedge bound is above 12288, its range above DIRECT_SPAN ranks; the
+# parts of the last two (131072 endpoints each) are still above it
+@pytest.mark.parametrize("m,total", [(6145, 300000), (12000, 300000), (24000, 500000),
+                                     (30000, 500000), (65000, 300000), (100001, 900000),
+                                     (140001, 1400000)])
+def test_large_filter(ctx, m, total):
+    parts = -(-2 * m // 131072)
+    assert total // parts > DIRECT_SPAN
+    rows, elems, walks = check(ctx, spread(m, total), total, c4_bin_win=1, c4_bin_dense=0)["bin"]
+    assert rows >= 1 and elems >= 2 * m
+    assert walks >= 2 * parts  # a bitmap walk and a counting walk
+
+
+# one class, a class for every 64 candidates, and the classes between
+@pytest.mark.parametrize("m,total", [(12000, 300000), (30000, 500000), (140001, 1400000)])
+def test_classes(ctx, m, total):
+    seen = {}
+    for cap in (64, 1000, 24576):
+        seen[cap] = check(ctx, spread(m, total, 2), total, c4_bin_win=1, c4_bin_dense=0,
+                          c4_bin_cap=cap)["bin"][2]
+    assert seen[64] > m // 64 and seen[1000] > m // 1000 and seen[64] > seen[1000] > seen[24576]
+
+
+# the smaller filters beyond the small graphs' kernels: wedge bounds around
+# theirs, tables of 768 and 3072 planned candidates
+@pytest.mark.parametrize("m", [129, 700, 769, 1024, 1025, 3000, 3073, 6144])
+def test_light_and_medium_filters(ctx, m):
+    got = check(ctx, spread(m, 20000), 20000)
+    rows, elems, walks = got["hash" if m <= 1024 else "med"]
+    assert rows >= 1 and elems >= 2 * m and walks >= 2
+
+
+# the ranged medium bucket (up to 65536 wedges, thin over many windows)
+@pytest.mark.parametrize("m", [6145, 20000, 32768])
+def test_ranged_medium_filter(ctx, m):
+    total = 1500000
+    rows, elems, walks = check(ctx, spread(m, total), total, c4_bin_win=0, c4_med_win=1)["med"]
+    assert rows >= 1 and elems >= 2 * m and walks >= 2
