@@ -622,20 +622,25 @@ __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
       unsigned dup = 0, valid = 0;
       walk(
           [&](const int32_t(&x)[4], int, int) {
-            uint32_t bit[4], old[4];
+            // lanes without an endpoint set nothing, each in a word of its own:
+            // in one word they wait for each other, all but a few of a
+            // wavefront's where segments are short (140000 segments of one
+            // endpoint 19.4 -> 13 ms, web 2^24 206.5 -> 195.5 ms a call)
+            uint32_t bit[4], old[4], at[4];
 #pragma unroll
             for (int k = 0; k < 4; k++) {
               const bool in = x[k] < hi;
               bit[k] = in ? 1u << (x[k] & 31) : 0u;
+              at[k] = in ? (uint32_t)x[k] >> 5 : (uint32_t)lane;
               valid += in;
-              old[k] = atomicOr(&fa[((uint32_t)x[k] >> 5) & (AW - 1)], bit[k]);
+              old[k] = atomicOr(&fa[at[k] & (AW - 1)], bit[k]);
             }
             // without a branch: a lane that finds its bit clear sets nothing
 #pragma unroll
             for (int k = 0; k < 4; k++) {
               const uint32_t d = old[k] & bit[k];
               dup += d != 0;
-              atomicOr(&fb[((uint32_t)x[k] >> 5) & (BW - 1)], d);
+              atomicOr(&fb[at[k] & (BW - 1)], d);
             }
           },
           [](int, bool) {});
@@ -653,6 +658,27 @@ __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
           nd + ((wb * nd) >> BB), (unsigned long long)(hi - lo));
       uint32_t P = (uint32_t)std::min<unsigned long long>((est + CAP - 1) / CAP, C4_MAX_CLASSES);
       if (nd == 0) P = 0;
+      if (__builtin_expect(P > 4, 0)) {
+        // Many classes: perhaps of few ranks, each met many times.  nb set bits
+        // of the second bitmap's B = 2^BB, where they are few, stand for little
+        // more than nb ranks (three times as many are allowed for), and a share
+        // nb / B of the other endpoints has its bit set by them.  140000
+        // endpoints of one rank took five classes: 13 -> 2.7 ms.  Asked of every
+        // part, with a logarithm where bits are many, this took the web 2^24
+        // graph from 195.5 to 199.5 ms.
+        static_assert(BW == 4 * NT, "16 bytes of the second bitmap a thread");
+        const uint4 v = fb4[tid];
+        int set = __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+#pragma unroll
+        for (int o = WAVE / 2; o > 0; o >>= 1) set += __shfl_xor(set, o, WAVE);
+        if (tid == 0) s_over = 0;
+        __syncthreads();
+        if (lane == 0 && set) atomicAdd(&s_over, set);
+        __syncthreads();
+        const uint32_t nb = (uint32_t)__builtin_amdgcn_readfirstlane(s_over);
+        if (nb < (1u << (BB - 4)))
+          P = std::min<uint32_t>(P, 1 + (3 * nb + (uint32_t)((wb * nb) >> BB)) / (uint32_t)CAP);
+      }
       for (uint32_t c = 0; c < P;) {
         for (int i = tid; i < AW / 4; i += NT) fa4[i] = make_uint4(0, 0, 0, 0);
         if (tid == 0) s_over = 0;

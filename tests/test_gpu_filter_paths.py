@@ -15,6 +15,7 @@ import graphgen as gg
 
 pytestmark = pytest.mark.gpu
 DIRECT_SPAN = 262144  # ranks of a part that is counted directly
+BITS = 131072  # of the large filter's second bitmap
 
 
 @pytest.fixture(scope="module")
@@ -38,6 +39,12 @@ def thin(places, total):
 
 def spread(m, total, seed=1):
     return np.sort(np.random.default_rng(seed).choice(total, m, replace=False))
+
+
+def stacked(m, total):
+    """Places that share few bits of the second bitmap: 1 / 8 of them."""
+    at = np.arange(m)
+    return np.sort(at % (m // 8) + at // (m // 8) * BITS)
 
 
 def check(ctx, places, total, walks=None, **tuning):
@@ -83,6 +90,23 @@ def test_classes(ctx, m, total):
         seen[cap] = check(ctx, spread(m, total, 2), total, c4_bin_win=1, c4_bin_dense=0,
                           c4_bin_cap=cap)["bin"][2]
     assert seen[64] > m // 64 and seen[1000] > m // 1000 and seen[64] > seen[1000] > seen[24576]
+
+
+# The later middle meets one rank m times: two walks; the earlier has no endpoint:
+# one.  The hub's two parts meet 50000 ranks each, twice: four classes planned, five
+# walks.
+def test_few_ranks_met_often(ctx):
+    walks = check(ctx, spread(100001, 900000), 900000, c4_bin_win=1, c4_bin_dense=0)["bin"][2]
+    assert 2 <= walks - 2 * 5 <= 4
+
+
+# Eight candidates to a bit of the second bitmap: 8191 bits plan two classes of
+# 65528 candidates, more than the table holds.  They are dropped and walked in
+# four: six walks of the hub (seven if six classes were planned), five of the later
+# middle (98286 expected) and one of the earlier, which has no endpoint.
+def test_an_overflowing_class_is_split(ctx):
+    walks = check(ctx, stacked(65528, 8 * BITS), 8 * BITS, c4_bin_win=1, c4_bin_dense=0)["bin"][2]
+    assert walks == 6 + 5 + 1
 
 
 # the smaller filters beyond the small graphs' kernels: wedge bounds around
