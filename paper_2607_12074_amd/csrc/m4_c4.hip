@@ -183,11 +183,26 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int l) {
 
 // Segments [s0, s0 + cnt) of owner row [base, base + nl) into LDS (and their
 // vertices, where VERT), from their first entry >= lo on, an empty one after
-// them.  Called by every thread of the workgroup.
+// them; with pc > 1 (full rows) each is cut below hi and into pc pieces of about
+// equal length, which count as segments.  Called by every thread of the
+// workgroup.
 template <int NT, bool VERT>
 __device__ __forceinline__ void load_segs(const C4Args& A, int64_t base, int nl, int s0, int cnt,
-                                          int32_t lo, int2* sg, int32_t* sv) {
+                                          int32_t lo, int2* sg, int32_t* sv, int pc = 1,
+                                          int32_t hi = 0) {
   if (threadIdx.x == 0) sg[cnt] = make_int2(0, 0);
+  if (__builtin_expect(pc > 1, 0)) {
+    for (int j = threadIdx.x; j < cnt; j += NT) {
+      const int s = s0 + j, k = s % pc;
+      const int32_t v = A.ncol[base + nl - 1 - s / pc];
+      const int64_t rs = A.nptr[v], re = rs + A.dr[v];
+      const int64_t c = lower_index(A.ncol, rs, re, lo);
+      const int64_t len = lower_index(A.ncol, c, re, hi) - c;
+      sg[j] = make_int2((int)(c + len * k / pc), (int)(c + len * (k + 1) / pc));
+      if (VERT) sv[j] = v;
+    }
+    return;
+  }
   for (int j = threadIdx.x; j < cnt; j += NT) {
     const int32_t v = A.ncol[base + nl - 1 - s0 - j];
     if (A.vmeta) {
@@ -607,11 +622,15 @@ __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
       // walks all segments, SEGS at a time; where they all fit they are
       // loaded once per range
       bool loaded = false;
+      // A few long rows would leave most groups of lanes without a segment: two
+      // rows of 140000 entries, orbits 82 ms whole and 12.7 in pieces (43 with a
+      // thread per wedge)
+      const int pc = NT == 1024 && nl <= 32 && wb >= 16384 ? SEGS / nl : 1, np = nl * pc;
       auto walk = [&](auto&& ent, auto&& fin) {
-        for (int s0 = 0; s0 < nl; s0 += SEGS) {
-          const int nc = nl - s0 < SEGS ? nl - s0 : SEGS;
-          if (!loaded) load_segs<NT, CRED>(A, base, nl, s0, nc, lo, sg, sv);
-          loaded = nl <= SEGS;
+        for (int s0 = 0; s0 < np; s0 += SEGS) {
+          const int nc = np - s0 < SEGS ? np - s0 : SEGS;
+          if (!loaded) load_segs<NT, CRED>(A, base, nl, s0, nc, lo, sg, sv, pc, hi);
+          loaded = np <= SEGS;
           if (tid == 0) s_next = 0;
           __syncthreads();
           seg_walk<GL>(A.ncol, hi, nc, &s_next, [&](int i) { return sg[i]; }, ent, fin);

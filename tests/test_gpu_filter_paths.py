@@ -124,3 +124,27 @@ def test_ranged_medium_filter(ctx, m):
     total = 1500000
     rows, elems, walks = check(ctx, spread(m, total), total, c4_bin_win=0, c4_med_win=1)["med"]
     assert rows >= 1 and elems >= 2 * m and walks >= 2
+
+
+# A hub whose endpoints lie in two rows: cut in pieces, so that all groups of lanes
+# walk.  Whole, the filter took 18 times the time of the windows (which count both
+# owners), in pieces 1.4 times; the line is drawn at 8.
+def test_two_long_rows(ctx):
+    import paper_2607_12074_amd as m4
+    m, total = 140001, 2140001
+    g, mid, hub = thin(np.arange(m), total)  # all in the first of the parts
+    base = ctx.get_tuning()
+    ms = {}
+    try:
+        for name, win in (("c4_window", 0), ("c4_bin", 1)):
+            ctx.set_tuning(c4_bin_win=win, c4_bin_dense=0, c4_med_win=0)
+            took = []
+            for _ in range(5):
+                got, st = ctx.count(*g, flags=m4.M4_BASIS_WEDGE | m4.M4_SERIAL, timing=True)
+                took.append(st["ms_kernel"][m4.KERNELS.index(name)])
+            assert got[3] == comb(m + 1, 2)
+            ms[name] = min(took)
+    finally:
+        ctx.set_tuning(**base)
+    print(ms)
+    assert ms["c4_bin"] < 8 * ms["c4_window"]
