@@ -1399,6 +1399,9 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
       k_c4_desc<<<(unsigned)HW, 256, 0, ls>>>(order, start, hoff, P.nptr, P.dlo, P.ncol, vmeta,
                                               P.row_len, C.r1, desc, seg_cnt);
     if (kt) kt->end(M4_K_C4_DESC, ls);
+    // light and tiny owners share a slot, whose one pair of events is put
+    // around both kernels
+    const bool hash = hstart[CB_HASH + 1] > hstart[CB_TINY];
     auto run = [&](int bucket, int slot, int hb, auto&& kernel, int nt, int64_t most, int grab) {
       int64_t cnt = hstart[bucket + 1] - hstart[bucket];
       if (cnt <= 0) return;
@@ -1413,9 +1416,10 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
       A.yb = c4_key_bits(n, hb);
       A.class_cap = bucket == CB_BIN || bucket == CB_WIDE ? tu.c4_bin_cap : 0;
       A.grab = grab;
-      if (kt) kt->begin(slot, ls);
+      const bool timed = kt && slot != M4_K_C4_HASH;
+      if (timed) kt->begin(slot, ls);
       kernel<<<(unsigned)std::min<int64_t>(most, ceil_div(cnt, grab)), nt, 0, ls>>>(A);
-      if (kt) kt->end(slot, ls);
+      if (timed) kt->end(slot, ls);
     };
     auto filter = [&](int bucket, int slot, int hb, auto&& plain, auto&& cred, int nt,
                       int per_cu) {
@@ -1425,8 +1429,10 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
     if (small) {
       // the owners of every bucket above the tiny one: a kernel for all
       hstart[CB_HASH + 1] = hstart[CB_N];
+      if (kt) kt->begin(M4_K_C4_HASH, ls);
       filter(CB_HASH, M4_K_C4_HASH, 1, k_c4_direct<false>, k_c4_direct<true>, 256, 4);
       run(CB_TINY, M4_K_C4_HASH, 1, n8 ? k_c4_tiny<true> : k_c4_tiny<false>, WAVE, waves, 1);
+      if (kt) kt->end(M4_K_C4_HASH, ls);
       return;
     }
     // heavy owners first
@@ -1440,6 +1446,7 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
     filter(CB_MED, M4_K_C4_MED, C4_MED_AB - 5,
            k_c4_filter<256, 8, C4_MED_AB, C4_MED_BB, 128, false>,
            k_c4_filter<256, 8, C4_MED_AB, C4_MED_BB, 128, true>, 256, 6);
+    if (kt && hash) kt->begin(M4_K_C4_HASH, ls);
     filter(CB_HASH, M4_K_C4_HASH, C4_LIGHT_AB - 5,
            k_c4_filter<64, 8, C4_LIGHT_AB, C4_LIGHT_BB, 64, false>,
            k_c4_filter<64, 8, C4_LIGHT_AB, C4_LIGHT_BB, 64, true>, 64, 24);
@@ -1448,6 +1455,7 @@ Launch c4_plan(const Prep& P, const Classes& C, Scal* scal, const Tuning& tu, ui
     const int64_t tiny = hstart[CB_TINY + 1] - hstart[CB_TINY];
     run(CB_TINY, M4_K_C4_HASH, 1, n8 ? k_c4_tiny<true> : k_c4_tiny<false>, WAVE, waves,
         (int)std::max<int64_t>(1, std::min<int64_t>(16, tiny / waves)));
+    if (kt && hash) kt->end(M4_K_C4_HASH, ls);
   };
 }
 

@@ -1,0 +1,25 @@
+"""Kernel slots of the per-kernel times that several kernels share hold the time
+of all of them."""
+import pytest
+
+import graphgen as gg
+
+pytestmark = pytest.mark.gpu
+
+
+# light owners take nearly all of the 4-cycle stage, tiny ones a little: their slot
+# and the row records are the stage but for the gaps between three launches
+@pytest.mark.parametrize("n", [8000, 60000])
+def test_light_and_tiny_owners_are_both_timed(n):
+    import paper_2607_12074_amd as m4
+    ctx = m4.Context(0)
+    g = gg.gnm(n, 20 * n, 5)
+    best = 0.0
+    for _ in range(5):
+        _, st = ctx.count(*g, flags=m4.M4_BASIS_WEDGE | m4.M4_SERIAL, stats=True, timing=True)
+        ms = dict(zip(m4.KERNELS, st["ms_kernel"]))
+        rows = dict(zip(m4.KERNELS, st["k_rows"]))
+        assert rows["c4_hash"] > 0 and not rows["c4_window"] and not rows["c4_bin"]
+        best = max(best, (ms["c4_hash"] + ms["c4_med"] + ms["c4_desc"]) / st["ms_c4"])
+    ctx.close()
+    assert best > 0.7, (ms, st["ms_c4"])
