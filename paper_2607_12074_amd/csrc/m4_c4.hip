@@ -607,8 +607,10 @@ __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
     const int32_t hi = A.parts ? __builtin_amdgcn_readfirstlane(part.z) : u;
     const unsigned long long wb =
         A.parts ? (unsigned long long)part.w : (unsigned long long)bound.x;
-    owners += lo == A.zr1;
-    segs += (unsigned long long)nl;
+    if (lo == A.zr1) {  // an owner's first part
+      owners++;
+      segs += (unsigned long long)nl;
+    }
     unsigned long long own = 0;
     if (NT == 1024 && hi - lo <= C4_DIRECT_SPAN) {
       // a dense part: the first bitmap's words as counters

@@ -148,3 +148,18 @@ def test_two_long_rows(ctx):
         ctx.set_tuning(**base)
     print(ms)
     assert ms["c4_bin"] < 8 * ms["c4_window"]
+
+
+# an owner's lower neighbours are counted once, whatever its parts: two of the hub
+# (three parts), m of each middle (two)
+def test_parts_count_lower_neighbours_once(ctx):
+    import paper_2607_12074_amd as m4
+    m, total = 140001, 1400000
+    base = ctx.get_tuning()
+    try:
+        ctx.set_tuning(c4_bin_win=1, c4_bin_dense=0)
+        _, st = ctx.count(*thin(spread(m, total), total)[0], flags=m4.M4_BASIS_WEDGE, stats=True)
+    finally:
+        ctx.set_tuning(**base)
+    i = m4.KERNELS.index("c4_bin")
+    assert (st["k_rows"][i], st["k_aux"][i]) == (3, 2 + 2 * m)
