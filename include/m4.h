@@ -274,9 +274,10 @@ typedef struct {
                             filter (0 = never, default 6)                     */
   int32_t c4_bin_cap;    /* single graph: endpoints above the filter's bitmaps
                             that one class of a large filtered owner is
-                            planned for (0 = 3/4 of its table, else 64..2^24);
-                            an owner with more is counted in several classes,
-                            one walk over its rows each                       */
+                            planned for (0 = 3/4 of its table of 32768, else
+                            64..2^24, of which values above the table's size
+                            stand for 0); an owner with more is counted in
+                            several classes, one walk over its rows each      */
   int32_t c4_bin_dense;  /* single graph: an owner that c4_bin_win would filter
                             keeps the dense counter windows when its wedge
                             bound is at least this many endpoints per window

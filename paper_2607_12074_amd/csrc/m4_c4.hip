@@ -68,7 +68,8 @@ struct C4Args {
   unsigned long long* n8;  // per-vertex 4-cycle credits (orbit counts), or null
   int yb;                  // filtered owners: bits of a permuted rank
   int grab;                // tiny owners: owners of a run
-  int class_cap;           // candidates a class of a filtered owner is planned for (0: 3/4 of its table)
+  int class_cap;           // candidates a class of a filtered owner is planned for (0, or more
+                           // than its table holds: 3/4 of that)
   // counter zones of the window owners (ranks >= r1): 4-bit counters for
   // ranks [r1, z1) (degree <= 15), 8-bit for [z1, z2) (degree <= 255), 32-bit
   // from z2 on; aw and bw are the words of the first two zones
@@ -572,7 +573,9 @@ template <int NT, int GL, int AB, int BB, int SEGS, bool CRED, bool WIDE = false
 __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
   using Table = FilterTable<AB, WIDE>;
   constexpr int AW = 1 << (AB - 5), BW = 1 << (BB - 5);  // bitmap words
-  const unsigned long long CAP = A.class_cap > 0 ? A.class_cap : Table::N / 4 * 3;
+  // (a larger plan than the table would overflow and be walked for nothing)
+  const unsigned long long CAP =
+      A.class_cap > 0 && A.class_cap <= Table::N ? A.class_cap : Table::N / 4 * 3;
   __shared__ uint4 fa4[AW / 4];
   __shared__ uint4 fb4[BW / 4];
   __shared__ int2 sg[SEGS + 1];

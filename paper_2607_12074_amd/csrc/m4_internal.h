@@ -147,7 +147,7 @@ struct Tuning {
   int c4_bin_win = 6;       // owners above the one-pass medium bound whose endpoints span at
                             // least this many counter windows take the large filter (0: never)
   int c4_bin_cap = 0;       // candidates one class of a large filtered owner is planned for
-                            // (0: 3/4 of its table)
+                            // (0, or more than its table holds: 3/4 of that)
   int c4_bin_dense = 16384; // endpoints per window from which an owner keeps dense windows (0: never)
   int probe_w_far = 64;     // probe_w when the hub tables do not fit in the Infinity Cache
   int tri_wave_far = 64;    // tri_wave_max when the out-lists do not fit in the Infinity Cache

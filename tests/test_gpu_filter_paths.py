@@ -163,3 +163,11 @@ def test_parts_count_lower_neighbours_once(ctx):
         ctx.set_tuning(**base)
     i = m4.KERNELS.index("c4_bin")
     assert (st["k_rows"][i], st["k_aux"][i]) == (3, 2 + 2 * m)
+
+
+# tunings saved when c4_bin_cap was the scratch of a workgroup (2^20 endpoints by
+# default) plan no class that the table cannot hold
+def test_plans_beyond_the_table(ctx):
+    walks = [check(ctx, spread(60000, 600000), 600000, c4_bin_win=1, c4_bin_dense=0,
+                   c4_bin_cap=cap)["bin"][2] for cap in (0, 32769, 1 << 20, 1 << 24)]
+    assert len(set(walks)) == 1
