@@ -28,6 +28,9 @@ M4_NK = 16
 KERNELS = ("build", "tri_global", "tri_1024", "tri_512", "tri_256", "tri_128", "tri_wave",
            "c4_plan", "c4_window", "c4_med", "c4_hash", "closure", "tri_hubs", "c4_desc",
            "c4_bin", "edge")
+# changes when thresholds mean or cost something else, so that results timed with
+# other kernels are not reused
+TUNING_VERSION = 2
 NAMES = ("star", "path", "paw", "cycle", "diamond", "clique")
 BASIS = ("T", "K4", "C4_ni", "S", "P_ni", "Paw_ni", "D_ni", "sum_t")
 
@@ -308,7 +311,8 @@ class Context:
         """Times the threshold candidates on a sample graph (row_ptr, col)
         and/or a packed arena (voff, eoff, row_ptr, col) and keeps the fastest
         in this context.  With cache (a JSON path) a result stored for the
-        same device and sample size class is reused instead of re-timing."""
+        same device, kernels (TUNING_VERSION) and sample size class is reused
+        instead of re-timing."""
         import json
         key = None
         if cache is not None:
@@ -340,7 +344,7 @@ class Context:
 
     def _tune_key(self, graph, batch):
         import math
-        parts = [self.arch]
+        parts = [self.arch, f"v{TUNING_VERSION}"]
         if graph is not None:
             n, nnz = len(graph[0]) - 1, len(graph[1])
             parts.append(f"g{int(math.log2(max(n, 1)))}.{int(math.log2(max(nnz, 1)))}")
