@@ -245,11 +245,13 @@ class Context:
         o = make_opts(fl, budget, cache_rows, self._stream_for(row_ptr, stream), tri_wave_max,
                       c4_light_max, c4_med_max)
         out = (ctypes.c_uint64 * 6)()
-        st = Stats()
+        # some statistics (the bases' estimates) are computed for a caller that
+        # asks for them only
+        st = Stats() if stats or timing else None
         self._check(lib().m4_count_motifs4_ex(self.h, ctypes.byref(g), ctypes.byref(o),
-                                              out, ctypes.byref(st)))
+                                              out, ctypes.byref(st) if st is not None else None))
         counts = tuple(int(x) for x in out)
-        return (counts, st.to_dict()) if (stats or timing) else counts
+        return counts if st is None else (counts, st.to_dict())
 
     def count_noalloc(self, row_ptr, col, *, flags=0, budget=0, stream=None):
         """The six counts through the allocation-free entry point (CSR in

@@ -44,3 +44,12 @@ def test_tunings_of_other_kernels_are_not_reused(ctx, tmp_path):
     again = ctx.autotune(graph=GRAPH, cache=str(cache))
     assert again["cached"] and again["hub_min"] != 32
     assert len(json.loads(cache.read_text())) == 2
+
+
+@pytest.mark.parametrize("asked", [{}, {"stats": True}, {"timing": True}])
+def test_statistics_are_computed_when_asked_for(ctx, asked):
+    got = ctx.count(*GRAPH, **asked)
+    (name, args), = ctx.rec.calls
+    assert name == "m4_count_motifs4_ex"
+    assert (args[4] is not None) == bool(asked)
+    assert got[:1] == ((0,) if not asked else ((0,) * 6,))
