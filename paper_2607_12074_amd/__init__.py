@@ -227,12 +227,22 @@ class Context:
 
     @staticmethod
     def _stream_for(x, stream):
-        if stream is not None:
+        """The stream handle of a call on x.  Called when all of its device
+        arrays (conversions and results too) are made: they may still be
+        written, or their memory read, by what torch has queued on its current
+        stream.  On that stream the call comes after it; on another it is
+        waited for, and so it is on torch's default stream, whose handle is
+        null and stands for the context's own stream, which does not wait for
+        the default one (0.4 us where nothing is queued)."""
+        if not (_is_torch(x) and x.is_cuda):
             return stream
-        if _is_torch(x) and x.is_cuda:
-            import torch
-            return torch.cuda.current_stream(x.device).cuda_stream
-        return None
+        import torch
+        current = torch.cuda.current_stream(x.device)
+        if stream is None:
+            stream = current.cuda_stream
+        if not stream or stream != current.cuda_stream:
+            current.synchronize()
+        return stream
 
     def count(self, row_ptr, col, *, flags=0, budget=0, cache_rows=0, stream=None,
               tri_wave_max=0, c4_light_max=0, c4_med_max=0, stats=False, timing=False):
@@ -268,7 +278,6 @@ class Context:
         inputs, a torch int32 tensor holding uint32 bits for device inputs)."""
         keep = _Keep()
         g = make_csr(row_ptr, col, keep)
-        o = make_opts(flags, 0, 0, self._stream_for(row_ptr, stream), tri_wave_max, 0)
         if g.on_device:
             import torch
             t = torch.empty(max(g.nnz, 1), dtype=torch.int32, device=row_ptr.device)
@@ -276,6 +285,7 @@ class Context:
         else:
             t = np.zeros(max(g.nnz, 1), dtype=np.uint32)
             ptr = t.ctypes.data
+        o = make_opts(flags, 0, 0, self._stream_for(row_ptr, stream), tri_wave_max, 0)
         self._check(lib().m4_edge_triangles(self.h, ctypes.byref(g), ctypes.byref(o), ptr))
         return t[: g.nnz]
 
@@ -285,7 +295,6 @@ class Context:
         uint64 bits for device inputs.  A device budget is rejected."""
         keep = _Keep()
         g = make_csr(row_ptr, col, keep)
-        o = make_opts(flags, budget, 0, self._stream_for(row_ptr, stream))
         n = g.n
         if g.on_device:
             import torch
@@ -294,6 +303,7 @@ class Context:
         else:
             out = np.zeros((max(n, 1), 11), dtype=np.uint64)
             ptr = out.ctypes.data
+        o = make_opts(flags, budget, 0, self._stream_for(row_ptr, stream))
         self._check(lib().m4_count_orbits4(self.h, ctypes.byref(g), ctypes.byref(o), ptr))
         return out[:n]
 
@@ -329,6 +339,9 @@ class Context:
         keep = _Keep()
         g = make_csr(*graph, keep) if graph is not None else None
         b = self._make_batch(*batch, keep=keep) if batch is not None else None
+        for sample in (graph, batch):
+            if sample is not None:
+                self._stream_for(sample[-1], 0)  # autotune runs on the context's stream
         t = Tuning()
         self._check(lib().m4_autotune(self.h, ctypes.byref(g) if g is not None else None,
                                       ctypes.byref(b) if b is not None else None, int(reps),
