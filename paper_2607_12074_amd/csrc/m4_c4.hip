@@ -296,7 +296,7 @@ __global__ __launch_bounds__(WAVE) void k_c4_tiny(C4Args A) {
         load_segs<WAVE, CRED>(A, base, nl, s0, nc, A.zr1, sg, sv);
         if (lane == 0) s_next = 0;
         wave_sync();
-        unsigned part = 0;
+        unsigned part = 0;  // at most the pairs of C4_TINY_MAX endpoints
         seg_walk<8>(A.ncol, u, nc, &s_next, [&](int i) { return sg[i]; },
                     [&](const int32_t(&x)[4], int, int) {
 #pragma unroll
@@ -643,6 +643,7 @@ __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
         }
         walks++;
       };
+      // endpoints of one owner: each CSR entry once at most, so below 2^31
       unsigned dup = 0, valid = 0;
       walk(
           [&](const int32_t(&x)[4], int, int) {

@@ -62,15 +62,20 @@ struct TriShared {
   int16_t scan[KMAX + 1];   // rows that are read
   int32_t qat[NT / WAVE][2 * WAVE];  // per wavefront: places of elements to look up
   int16_t qrow[NT / WAVE][2 * WAVE];  // ... and their rows
+  unsigned long long work[4];  // of all owners: steps, looks, hits, words read
   int next, nscan, item;
 };
 
-// One thread's sums over all of its owners (its work counters stay far below
-// 2^32: all 10^5 threads of a kernel together pass fewer than 10^6 elements a
-// microsecond).
+// One thread's sums.  Over all of its owners: k4 (fewer than 2^44 triangles on
+// 2^30 edges, each with fewer than 2^9 common bits), escan, ksum (at most the
+// edges) and owners (at most the vertices).  Of one owner, added to the
+// workgroup's 64-bit counters after it: steps and looks are at most its 512 rows
+// of fewer than 2^16 entries, wread about twice that.  (In 64-bit registers over
+// all owners they made the kernels spill 60 to 76 bytes a lane.)
 struct TriCounts {
   unsigned long long k4 = 0, escan = 0;
-  uint32_t steps = 0, looks = 0, hits = 0, ksum = 0, wread = 0, owners = 0;
+  uint32_t ksum = 0, owners = 0;
+  uint32_t steps = 0, looks = 0, hits = 0, wread = 0;
 };
 
 template <int KMAX, int NT, bool CRED>
@@ -362,8 +367,8 @@ struct TriCounts64 {
   unsigned long long steps = 0, looks = 0, hits = 0, ksum = 0, wread = 0, escan = 0, owners = 0;
 };
 
-template <int NT, class Counts>
-__device__ __forceinline__ void tri_counts_out(const TriArgs& A, const Counts& C) {
+template <int NT>
+__device__ __forceinline__ void tri_counts_out(const TriArgs& A, const TriCounts64& C) {
   block_add_acc<NT>(A.scal, ACC_K4, C.k4);
   if (A.flags & M4_STATS) {
     block_add_u64<NT>(&A.scal->stat[ST_STEPS], C.steps);
@@ -386,6 +391,8 @@ __global__ __launch_bounds__(NT, 5) void k_tri_lds(TriArgs A) {
   const uint32_t cnt = (uint32_t)(A.start[A.bucket + 1] - b0);
   const int32_t* order = A.order + b0;
   TriCounts C;
+  if (threadIdx.x < 4) S.work[threadIdx.x] = 0;
+  __syncthreads();
   // runs of A.grab owners from the work counter, or (0) owners dealt in turn
   for (uint32_t turn = blockIdx.x;; turn += gridDim.x) {
     uint32_t first = turn;
@@ -397,11 +404,33 @@ __global__ __launch_bounds__(NT, 5) void k_tri_lds(TriArgs A) {
     }
     if (first >= cnt) break;
     uint32_t left = A.grab > 0 ? min((uint32_t)A.grab, cnt - first) : 1;
-    for (; left > 0; left--, first++)
+    for (; left > 0; left--, first++) {
       tri_owner_lds<KMAX, NT, CRED>(A, __builtin_amdgcn_readfirstlane(order[first]), S, C);
+      if (!CRED) {
+        if (A.flags & M4_STATS) {
+          const uint32_t of_owner[4] = {C.steps, C.looks, C.hits, C.wread};
+          for (int i = 0; i < 4; i++)
+            if (of_owner[i]) atomicAdd(&S.work[i], (unsigned long long)of_owner[i]);
+        }
+        C.steps = C.looks = C.hits = C.wread = 0;
+      }
+    }
   }
-  if (threadIdx.x > 0) C.ksum = C.owners = 0;
-  if (!CRED) tri_counts_out<NT>(A, C);
+  if (!CRED) {
+    TriCounts64 T;
+    T.k4 = C.k4;
+    T.escan = C.escan;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      T.ksum = C.ksum;
+      T.owners = C.owners;
+      T.steps = S.work[0];
+      T.looks = S.work[1];
+      T.hits = S.work[2];
+      T.wread = S.work[3];
+    }
+    tri_counts_out<NT>(A, T);
+  }
 }
 
 // Out-degree in (512, 1024]: the bitmap alone nearly fills the LDS.
@@ -590,7 +619,7 @@ __global__ __launch_bounds__(256) void k_tri_small(TriArgs A) {
         if ((mask >> r) & 1) c12 += tr;
       }
       const uint32_t adj = mask | col;
-      unsigned c14 = 0;
+      unsigned c14 = 0;  // at most 16 rows of 16 bits
       for (int r = 0; r < kmax; r++) {
         const uint32_t ar = (uint32_t)__shfl((int)adj, gb + r, WAVE);
         if ((adj >> r) & 1) c14 += __popc(ar & adj);
@@ -607,7 +636,7 @@ __global__ __launch_bounds__(256) void k_tri_small(TriArgs A) {
       if (i == 0 && cu14) atomicAdd(&A.n14[u], cu14 / 6);
     } else {
       uint32_t c = __popc(mask);  // triangles on the owner's edge to a[i]
-      unsigned q4 = 0;
+      unsigned q4 = 0;  // at most 16 rows of 16 bits
       for (int r = 0; r < kmax; r++) {
         const uint32_t mr = (uint32_t)__shfl((int)mask, gb + r, WAVE);
         if ((mr >> i) & 1) {

@@ -23,3 +23,16 @@ def test_light_and_tiny_owners_are_both_timed(n):
         best = max(best, (ms["c4_hash"] + ms["c4_med"] + ms["c4_desc"]) / st["ms_c4"])
     ctx.close()
     assert best > 0.7, (ms, st["ms_c4"])
+
+
+# every triangle is looked up once in the frontier cache, by whichever kernel its
+# owner takes: the counters kept by owner and by workgroup lose none
+@pytest.mark.parametrize("make", [lambda: gg.gnm(20000, 400000, 1), lambda: gg.gnm(1200, 300000, 2),
+                                  lambda: gg.rmat(15, 16, 0.57, 0.19, 0.19, 3)])
+def test_lookups_are_the_triangles(make):
+    import paper_2607_12074_amd as m4
+    ctx = m4.Context(0)
+    _, st = ctx.count(*make(), stats=True)
+    ctx.close()
+    assert st["cache_lookups"] == st["cache_hits"] == st["T"] > 0
+    assert st["intersect_steps"] >= st["T"]
