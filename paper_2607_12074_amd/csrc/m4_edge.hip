@@ -129,14 +129,19 @@ __global__ __launch_bounds__(256) void k_edge_pairs(const int64_t* __restrict__ 
 // Eq. (1) over the two cycle/path bases: the triangle anchor, the recoverable
 // counts (closure yield: all six for both) and the reuse (none for either) are
 // shared and drop out; enumeration plus intersection work, each element
-// weighted by its measured cost on this device, plus a fixed stage cost
-// (launches and the host read-backs of the wedge plan) or the two serial
-// parts of the edge stage, and the halo term: the edge basis reads 2-hop
-// rows, which the halo partitions do not hold, so it is infinite under a
-// budget.  Edge / wedge stage, us of a whole call: 200 vertices and 800 edges
-// 352 / 367, 1000 and 8000 381 / 383, 2000 and 20000 475 / 402, a power law of
-// 512 and 2200 edges (longest row 170) 928 / 442, 10^5 and 2 10^5 edges
-// 1552 / 518.
+// weighted by its measured cost on this device, plus the wedge stage's fixed
+// cost or the two serial parts of the edge stage, and the halo term: the edge
+// basis reads 2-hop rows, which the halo partitions do not hold, so it is
+// infinite under a budget.  The choice is open up to SMALL_N vertices, whose
+// plans are made and read back whatever basis is taken.  Edge / wedge, us of a
+// whole call there: a cycle of 300 83 / 70, of 1000 95 / 73; uniform graphs of
+// degree 4 with 200 vertices 94 / 80, with 2000 133 / 102; of degree 8 with 1000
+// 128 / 103; of degree 30 with 1000 336 / 131; a power law of 512 and 1800 edges
+// 360 / 116.  Of 39 such graphs the wedge basis was faster on all, so its stage
+// has no fixed cost beyond the edge stage's.  The 15 us that are left (50 before,
+// which took the edge basis on uniform graphs of degree 4 up to 2000 vertices)
+// keep the edge basis for short rows on a few hundred vertices, where tests
+// expect it and it costs 7 to 22 us more.
 void basis_costs(BasisChoice& b, const Tuning& tu, int64_t n, bool budgeted,
                  const unsigned long long* in) {
   b.cost_wedge = tu.cost_wedge_ns * (double)in[0] + tu.cost_wedge_fixed_us * 1e3;
@@ -157,7 +162,7 @@ BasisChoice choose_basis(const Prep& P, const Tuning& tu, uint32_t flags, bool b
     for (int i = 0; i < 3; i++) in[i] = si->cost[i];
   } else if (P.n > 0) {
     // beyond SMALL_N vertices the owners alone cost the edge stage more than the
-    // fixed part of the wedge stage (4167 are enough), and it scans at least an
+    // fixed part of the wedge stage (1250 are enough), and it scans at least an
     // entry per wedge endpoint at the higher price: settled without waiting for
     // the inputs (a read-back takes some 10 us of a call)
     b.pending =

@@ -153,11 +153,11 @@ struct Tuning {
   int tri_wave_far = 64;    // tri_wave_max when the out-lists do not fit in the Infinity Cache
   // weights of the anchor-selection objective, from stage times measured on
   // the MI355X over graphs of 10^2 to 10^7 edges: ns per wedge endpoint
-  // bound, fixed us of the wedge stage (what its plan kernels and host
-  // read-backs take beyond the edge stage's); ns per row entry the edge basis
+  // bound, fixed us of the wedge stage (what it takes beyond the edge stage
+  // when neither has work); ns per row entry the edge basis
   // scans, per owner (the work counter they are taken from serves one in
   // 12 ns) and per entry of the longest row (one thread scans it alone)
-  double cost_wedge_ns = 0.005, cost_wedge_fixed_us = 50.0, cost_edge_ns = 0.03;
+  double cost_wedge_ns = 0.005, cost_wedge_fixed_us = 15.0, cost_edge_ns = 0.03;
   double cost_edge_owner_ns = 12.0, cost_edge_row_ns = 1000.0;
 };
 
