@@ -270,8 +270,8 @@ Tuning tuning_for(const m4_ctx* c, const m4_opts* o) {
   if (o && o->tri_wave_max > 0) tu.tri_wave_max = tu.tri_wave_far = o->tri_wave_max;
   if (o && o->c4_light_max > 0) tu.c4_light_max = o->c4_light_max;
   if (o && o->c4_med_max != 0) tu.c4_med_max = o->c4_med_max < 0 ? 0 : o->c4_med_max;
-  tu.c4_light_max = std::max(0, std::min(tu.c4_light_max, C4_HASH_SLOTS / 2));
-  tu.c4_med_max = std::max(0, std::min(tu.c4_med_max, 3 * C4_MED_SLOTS / 4));
+  tu.c4_light_max = std::max(0, std::min(tu.c4_light_max, C4_LIGHT_MAX));
+  tu.c4_med_max = std::max(0, std::min(tu.c4_med_max, C4_MED_CAP));
   // the large filter cuts its rank ranges by the degrees' prefix sums, which
   // the partitions of a budgeted call do not hold
   if (o && o->device_budget_bytes > 0) tu.c4_bin_win = 0;

@@ -442,8 +442,6 @@ size_t build_tmp_bytes(int64_t n, int64_t nnz) {
   add(radix_tmp_elems(n, 8) * 8);
   add(scan_tmp_elems(n) * 8);
   add(scan_tmp_elems(n) * 8);
-  add(64 * 4);
-  add(64 * 8);
   return b + 4096;
 }
 

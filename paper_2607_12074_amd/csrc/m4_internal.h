@@ -44,9 +44,9 @@ constexpr int TRI_LDS_MAX = 1024;
 // 4-cycle window: 32768 words (128 KiB of LDS) of zoned counters.
 constexpr int C4_WIN_WORDS = 32768;
 constexpr int C4_TINY_MAX = 256;      // tiny owners: one wavefront, a table of twice the bound
-constexpr int C4_HASH_SLOTS = 4096;   // twice the largest wedge bound of the light bucket
-constexpr int C4_MED_SLOTS = 16384;   // 4/3 of the largest bound of the medium bucket's first rule
-constexpr int C4_MED_MAX = 65536;     // largest wedge bound of the medium bucket
+constexpr int C4_LIGHT_MAX = 2048;    // largest wedge bound of the light bucket
+constexpr int C4_MED_CAP = 12288;     // ... of the medium bucket's first rule
+constexpr int C4_MED_MAX = 65536;     // ... of the medium bucket
 // Entries of slack after the last row of a rank-space CSR, so that 16-byte
 // vector loads aligned below a cursor may run past the end of the array.
 constexpr int NCOL_PAD = 256;
@@ -138,7 +138,6 @@ struct Tuning {
   int tri_wave_max = 64;    // <= WAVE
   int c4_light_max = 2048;  // wedge bound for the hash bucket
   int c4_med_max = 12288;   // wedge bound for the one-pass medium hash (0: no medium bucket)
-  int grid_mult = 8;        // persistent blocks per CU for light kernels
   int batch_variant = 0;    // batched kernel: 0 = 1024 threads / 96 KiB, 1 = 512 / 40 KiB
   int batch_light = 128;    // batched kernel: wedge bound of the wavefront hash
   int hub_min = 128;        // out-degree from which a vertex gets a hub table (0: none)
@@ -255,7 +254,6 @@ const int* row_class_thresholds();
 using Launch = std::function<void(hipStream_t)>;
 
 // m4_tri.hip
-size_t tri_tmp_bytes(int64_t n, int64_t nnz, int dplus_max_bound);
 // big_scratch(bytes) returns device memory for the hub tables and for owners
 // whose bitmap does not fit in LDS (only called when those exist).
 // credits, if given, takes the launch that adds the per-vertex credits of the

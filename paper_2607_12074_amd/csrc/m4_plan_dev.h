@@ -20,11 +20,6 @@ __device__ __forceinline__ uint32_t tri_bucket(int k, int small_max, int wave_ma
   return k <= TRI_LDS_MAX ? TK_1024 : TK_GLOBAL;
 }
 
-// Owners with wedge bounds in (12288, C4_MED_MAX] join the medium bucket when
-// their endpoints are thin over many windows; the rule counts ranges of
-// C4_MED_CAP endpoints against windows.
-constexpr int64_t C4_MED_CAP = 3 * C4_MED_SLOTS / 4;
-
 // Filtered owners: log2 of the bits of the first and second LDS bitmap of
 // each bucket (the first holds 2^(bits - 5) table slots afterwards).
 constexpr int C4_LIGHT_AB = 15, C4_LIGHT_BB = 13;
@@ -63,8 +58,8 @@ __device__ __forceinline__ int64_t c4_windows(const int64_t* zb, int64_t r1, int
 // bitmap filter sized to their bound.  Beyond the one-pass medium bound a
 // dense window costs a pass over the owner's lower neighbours, so an owner
 // goes to the filter of the ranged medium bucket only when its endpoints are
-// thin over many windows (16 windows >= med_win ranges; med_win 0: never), to
-// the large filter when they span at least bin_win windows and average fewer
+// thin over many windows (16 windows >= med_win ranges of C4_MED_CAP endpoints;
+// med_win 0: never), to the large filter when they span at least bin_win windows and average fewer
 // than bin_dense endpoints per window, and else keeps the dense windows.  A
 // filter needs its counts to fit beside the key (lower neighbours below its
 // limit); with credits (orbit counts) there are no dense windows and the

@@ -787,13 +787,6 @@ extern "C" uint32_t m4_internal_sig_key(uint32_t j, uint32_t slot, uint32_t mplu
   return sig_key(j, slot, mplus, mminus);
 }
 
-size_t tri_tmp_bytes(int64_t n, int64_t nnz, int kmax_global) {
-  (void)nnz;
-  return (size_t)n * 8 + radix_tmp_elems(n, 4) * 8 + 16 * 8 + 8192 +
-         (size_t)(kmax_global > 0 ? 64 : 0) *
-             ((size_t)kmax_global * ((kmax_global + 63) / 64) * 8 + (7 * (size_t)kmax_global + 2) * 4);
-}
-
 namespace {
 // out-list records and hub tables: resident runs only (a partition holds only
 // its halo rows)

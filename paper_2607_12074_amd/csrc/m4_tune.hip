@@ -55,10 +55,10 @@ extern "C" int m4_get_tuning(const m4_ctx* ctx, m4_tuning* out) {
 extern "C" int m4_set_tuning(m4_ctx* ctx, const m4_tuning* t) {
   if (!ctx || !t) return M4_EINVAL;
   if (t->tri_wave_max < 2 || t->tri_wave_max > 64 || t->c4_light_max < 1 ||
-      t->c4_light_max > C4_HASH_SLOTS / 2 || (t->batch_variant != 0 && t->batch_variant != 1) ||
+      t->c4_light_max > C4_LIGHT_MAX || (t->batch_variant != 0 && t->batch_variant != 1) ||
       t->batch_light < 1 || t->batch_light > 256 ||
       (t->hub_min != 0 && (t->hub_min < 4 || t->hub_min > 65536)) || t->c4_med_max < 0 ||
-      t->c4_med_max > 3 * C4_MED_SLOTS / 4 || t->probe_w < 1 || t->probe_w > 256 ||
+      t->c4_med_max > C4_MED_CAP || t->probe_w < 1 || t->probe_w > 256 ||
       t->c4_med_win < 0 || t->c4_med_win > 65536 || t->c4_bin_win < 0 || t->c4_bin_win > 65536 ||
       (t->c4_bin_cap != 0 && (t->c4_bin_cap < 64 || t->c4_bin_cap > (1 << 24))) ||
       (t->c4_bin_dense != 0 && (t->c4_bin_dense < 64 || t->c4_bin_dense > (1 << 20))) ||
