@@ -53,17 +53,17 @@ __device__ __forceinline__ int64_t c4_windows(const int64_t* zb, int64_t r1, int
 }
 
 // Bucket of owner u with wedge bound w > 0 and nl lower neighbours of degree
-// above 1.  Owners up
-// to C4_TINY_MAX wedges take one wavefront and a table, the ones above a
-// bitmap filter sized to their bound.  Beyond the one-pass medium bound a
-// dense window costs a pass over the owner's lower neighbours, so an owner
-// goes to the filter of the ranged medium bucket only when its endpoints are
-// thin over many windows (16 windows >= med_win ranges of C4_MED_CAP endpoints;
-// med_win 0: never), to the large filter when they span at least bin_win windows and average fewer
-// than bin_dense endpoints per window, and else keeps the dense windows.  A
-// filter needs its counts to fit beside the key (lower neighbours below its
-// limit); with credits (orbit counts) there are no dense windows and the
-// large filter takes the rest, or its variant with 64-bit slots.
+// above 1.  Owners up to C4_TINY_MAX wedges take one wavefront and a table, the
+// ones above a bitmap filter sized to their bound.  Beyond the one-pass medium
+// bound a dense window costs a pass over the owner's lower neighbours, so an
+// owner goes to the filter of the ranged medium bucket only when its endpoints
+// are thin over many windows (16 windows >= med_win ranges of C4_MED_CAP
+// endpoints; med_win 0: never), to the large filter when they span at least
+// bin_win windows and average fewer than bin_dense endpoints per window, and
+// else keeps the dense windows.  A filter needs its counts to fit beside the key
+// (lower neighbours below its limit); with credits (orbit counts) there are no
+// dense windows and the large filter takes the rest, or its variant with 64-bit
+// slots.
 struct C4Plan {
   int light_max, med_max, med_win, bin_win, bin_dense;
   const int64_t* zb;
