@@ -237,7 +237,7 @@ class Context:
         if not (_is_torch(x) and x.is_cuda):
             return stream
         import torch
-        current = torch.cuda.current_stream(x.device)
+        current = torch.cuda.current_stream(x.get_device())
         if stream is None:
             stream = current.cuda_stream
         if not stream or stream != current.cuda_stream:

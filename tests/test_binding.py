@@ -71,6 +71,9 @@ def on_device(events, handle):
         def contiguous(self):
             return self
 
+        def get_device(self):
+            return 0
+
         def numel(self):
             return self.values.size
 
