@@ -582,7 +582,7 @@ __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
   __shared__ int32_t wq[NT / WAVE][2 * WAVE];  // per wavefront: candidates to count
   __shared__ int32_t sv[CRED ? SEGS : 1];
   __shared__ int s_item, s_next, s_over;
-  __shared__ unsigned s_dup;
+  __shared__ unsigned s_dup, s_bits;
   uint32_t* fa = reinterpret_cast<uint32_t*>(fa4);
   uint32_t* fb = reinterpret_cast<uint32_t*>(fb4);
   const int tid = threadIdx.x, lane = tid & (WAVE - 1);
@@ -623,7 +623,7 @@ __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
       // ---- 1. the bitmaps
       for (int i = tid; i < AW / 4; i += NT) fa4[i] = make_uint4(0, 0, 0, 0);
       for (int i = tid; i < BW / 4; i += NT) fb4[i] = make_uint4(0, 0, 0, 0);
-      if (tid == 0) s_dup = 0;
+      if (tid == 0) s_dup = s_bits = 0;
       // walks all segments, SEGS at a time; where they all fit they are
       // loaded once per range
       bool loaded = false;
@@ -696,11 +696,9 @@ __global__ __launch_bounds__(NT) void k_c4_filter(C4Args A) {
         int set = __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
 #pragma unroll
         for (int o = WAVE / 2; o > 0; o >>= 1) set += __shfl_xor(set, o, WAVE);
-        if (tid == 0) s_over = 0;
+        if (lane == 0 && set) atomicAdd(&s_bits, (unsigned)set);
         __syncthreads();
-        if (lane == 0 && set) atomicAdd(&s_over, set);
-        __syncthreads();
-        const uint32_t nb = (uint32_t)__builtin_amdgcn_readfirstlane(s_over);
+        const uint32_t nb = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_bits);
         if (nb < (1u << (BB - 4)))
           P = std::min<uint32_t>(P, 1 + (3 * nb + (uint32_t)((wb * nb) >> BB)) / (uint32_t)CAP);
       }
