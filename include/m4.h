@@ -22,6 +22,9 @@
  *   - The caller owns every input and output buffer.  The library keeps no
  *     caller pointer after a call returns.
  *   - Device pointers refer to memory of the context's device.
+ *   - Inputs in device memory are complete, or written on the stream the call
+ *     runs on: a context's own stream waits for no other, the null stream
+ *     included.
  *   - A context is not thread-safe: one host thread per context at a time.
  *   - Nothing throws across this boundary.
  */

@@ -498,23 +498,23 @@ __global__ __launch_bounds__(256) void k_c4_direct(C4Args A) {
 // An owner with more than C4_BIN_RANGE endpoints is counted in parts: rank
 // ranges of about equal numbers of endpoints, each by any workgroup, so that
 // no single owner keeps one CU busy after the others have ended.  A part with
-// more candidates than the table holds
-// is counted in P classes of a second hash, one walk each; a class that
-// overflows the table is dropped, split in two and walked again, so every
-// owner ends.
-// Bound by vector issue (about 135 instructions per 256 entries, half of the
-// issue slots) and, at 16 wavefronts a CU, by the latency of a walk's one load
-// in flight.  Scale-24 web graph (268 M edges): the 395 K large owners (21.5 G
-// endpoints, about 2.5 walks each) 91 ms, 209 ms when their endpoints were
-// sorted into bins in device memory; the 698 K medium ones (1.76 G) 8.8 ms,
-// 33 ms in 16384-slot tables with a search per endpoint; light and tiny ones
-// 4.5 ms, 18 ms.  Parts of 98 K / 131 K / 196 K endpoints: 97 / 91 / 104 ms;
-// direct counters for parts of up to 33 K / 131 K / 262 K / 524 K ranks: 98 /
-// 95 / 91 / 99 ms; 512-thread workgroups, two a CU with half the bitmap:
-// 167 ms (at 103).  Whole owners instead of parts: 103 ms, and the credits of
-// the web 2^21 graph 51 ms instead of 20, of the social 2^18 graph 38 instead
-// of 2.6 (one hub kept one CU busy); with one global atomic per wedge into n
-// counters per workgroup they took 336 and 19 ms.
+// more candidates than the table holds is counted in P classes of a second
+// hash, one walk each; a class that overflows the table is dropped, split in two
+// and walked again, so every owner ends.
+// Bound by vector issue (52 % of the CU's cycles) and, at 16 wavefronts a CU, by
+// the latency of a walk's one load in flight.  Scale-24 web graph (268 M edges):
+// the 395 K large owners (21.5 G endpoints, about 2.5 walks each) 83 ms, 209 ms
+// when their endpoints were sorted into bins in device memory; the 698 K medium
+// ones (1.76 G) 7.5 ms, 33 ms in 16384-slot tables with a search per endpoint;
+// light and tiny ones 2.5 and 2.6 ms, 18 ms together.  While the lanes without an
+// endpoint shared a word (91, 8.8 and 4.1 ms, a third of the large ones' LDS
+// cycles more in conflicts): parts of 98 K / 131 K / 196 K endpoints 97 / 91 /
+// 104 ms; direct counters for parts of up to 33 K / 131 K / 262 K / 524 K ranks
+// 98 / 95 / 91 / 99 ms; 512-thread workgroups, two a CU with half the bitmap,
+// 167 ms (at 103); whole owners instead of parts 103 ms, and the credits of the
+// web 2^21 graph 51 ms instead of 20, of the social 2^18 graph 38 instead of 2.6
+// (one hub kept one CU busy); with one global atomic per wedge into n counters
+// per workgroup they took 336 and 19 ms.
 template <int AB, bool WIDE>
 struct FilterTable {
   using Slot = std::conditional_t<WIDE, unsigned long long, uint32_t>;
